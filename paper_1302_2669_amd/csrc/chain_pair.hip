@@ -32,24 +32,17 @@ constexpr uint32_t HALF_LO = 0x0000FFFFu;
 __host__ __device__ constexpr uint32_t pair_fields(int n) {
   return field_mask(n, 0) | (field_mask(n, 0) << 16);
 }
-// nibble-LSB mask of the sites of one row in both halves
+// nibble-top mask of the sites of one row in both halves
 __host__ __device__ constexpr uint32_t pair_sites(int par, int limit) {
-  return site_nibbles(par, limit, 0) | (site_nibbles(par, limit, 0) << 16);
+  return site_tops(par, limit, 0) | (site_tops(par, limit, 0) << 16);
 }
 
 // Blocks BLK of two chains' streams together (both keyed by the same seed).
 template <int BLK>
 __device__ __forceinline__ void block_two(const ChainRng& A, const ChainRng& B, uint4& a,
                                           uint4& b) {
-  constexpr uint64_t pb = (uint64_t)PHILOX_M0 * (uint64_t)(uint32_t)BLK;
-  constexpr uint32_t hb = (uint32_t)(pb >> 32), lb = (uint32_t)pb;
-  uint32_t qh, ql, rh, rl;
-  mulhilo(PHILOX_M1, hb ^ A.ctr3_sw ^ A.k1, qh, ql);
-  mulhilo(PHILOX_M1, hb ^ B.ctr3_sw ^ B.k1, rh, rl);
-  a = make_uint4(qh ^ A.sid_lo ^ (A.k0 + PHILOX_W0), ql, A.sw_hi ^ lb ^ (A.k1 + PHILOX_W1),
-                 A.sw_lo);
-  b = make_uint4(rh ^ B.sid_lo ^ (B.k0 + PHILOX_W0), rl, B.sw_hi ^ lb ^ (B.k1 + PHILOX_W1),
-                 B.sw_lo);
+  a = A.template after_two<BLK>();
+  b = B.template after_two<BLK>();
   philox_rounds2(a, b, A.k0, A.k1, 2);
 }
 
@@ -95,8 +88,8 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
   uint32_t st[R];
 #pragma unroll
   for (int r = 0; r < R; ++r)
-    st[r] = (a.init_rows[A.it.rows_off + r * 4 + A.cls] & HALF_LO) |
-            (a.init_rows[B.it.rows_off + r * 4 + B.cls] << 16);
+    st[r] = reg_code((a.init_rows[A.it.rows_off + r * 4 + A.cls] & HALF_LO) |
+                     (a.init_rows[B.it.rows_off + r * 4 + B.cls] << 16));
   int32_t nA = a.init_n[A.it.orig * 4 + A.cls];
   int32_t nB = a.init_n[B.it.orig * 4 + B.cls];
   int64_t SA = 0, SB = 0, AA = 0, AB = 0;
@@ -107,12 +100,21 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
   rB.init(a.k0, a.k1, B.it.sid, ((uint32_t)B.cls << 28) | ((uint32_t)(B.kt + 1) << 20) |
                                     (uint32_t)B.chain);
 
+  // the top bit of every nibble, as in the one-chain kernel
+  uint32_t site_bit[8];
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    site_bit[m] = 8u << (4 * m);
+    asm volatile("" : "+v"(site_bit[m]));
+  }
+
   for (int sweep = g.sweep_begin; sweep < g.sweep_end; ++sweep) {
     rA.begin_sweep((uint32_t)sweep);
     rB.begin_sweep((uint32_t)sweep);
     uint4 bA = make_uint4(0, 0, 0, 0), bB = make_uint4(0, 0, 0, 0);
-    int32_t dA = 0, dB = 0;   // weight changes of the current phase
+    uint32_t dA = 0, dB = 0;  // 8 x the sum of Delta n + 4 over the phase's accepted moves
     int32_t cA = 0, cB = 0;   // accepted moves of the sweep
+    int32_t pA = 0, pB = 0;   // of them, before the current phase
 
     // as in the one-chain kernel: no computation of a later row is hoisted
     // above the end of the current one
@@ -122,9 +124,11 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
       asm volatile("" : "+v"(dA), "+v"(dB), "+v"(cA), "+v"(cB));
     };
     auto end_phase = [&]() {
-      nA += dA;
-      nB += dB;
+      nA += (int32_t)(dA >> 3) - 4 * (cA - pA);
+      nB += (int32_t)(dB >> 3) - 4 * (cB - pB);
       dA = dB = 0;
+      pA = cA;
+      pB = cB;
       if (sweep >= g.burn) {
         SA += nA;
         SB += nB;
@@ -132,40 +136,37 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
     };
 
     // Accept decisions of one row of both chains (nibble m of `sum`: site m
-    // of A, nibble 4 + m: site m of B); leaves the nibble-LSB accept mask.
+    // of A, nibble 4 + m: site m of B); returns the accepted sites as the top
+    // bits of their nibbles.
     auto decide_row = [&](auto PAR, auto NSITE, auto D0, auto LIMIT, uint32_t sum) -> uint32_t {
       constexpr int par = decltype(PAR)::value, nsite = decltype(NSITE)::value;
       constexpr int d0 = decltype(D0)::value, limit = decltype(LIMIT)::value;
-      uint32_t ra = 0, rb = 0;
+      uint32_t rej = 0;
       static_for<nsite>([&](auto MM) {
         constexpr int m = decltype(MM)::value;
         constexpr int d = d0 + m;
         if constexpr ((d & 3) == 0) block_two<d / 4>(rA, rB, bA, bB);
         const uint32_t ta = lds_tbl[(sum >> (4 * m)) & 15u][col];
         const uint32_t tb = lds_tbl[(sum >> (16 + 4 * m)) & 15u][256 + col];
-        ra = push_accept(ra, word_of(bA, d & 3), ta);
-        rb = push_accept(rb, word_of(bB, d & 3), tb);
+        const uint32_t ra = reject_bit(word_of(bA, d & 3), ta, site_bit[m]);
+        const uint32_t rb = reject_bit(word_of(bB, d & 3), tb, site_bit[4 + m]);
+        if constexpr (m == 0) rej = ra | rb;
+        else rej = rej | ra | rb;
       });
-      // bit m: site m of A, bit 4 + m: site m of B
-      const uint32_t bits = (__builtin_bitreverse32(ra) >> (32 - nsite)) |
-                            ((__builtin_bitreverse32(rb) >> (32 - nsite)) << 4);
       constexpr uint32_t sites = pair_sites(par, limit);
-      const uint32_t low = ~(sum + 0x33333333u) >> 3;   // nibble LSB: t <= 4
-      const uint32_t acc = (spread_nibbles(bits & 0xFFu) | low) & sites;
-      const uint32_t nm = (acc << 4) - acc;
-      const uint32_t kept = sum & nm;
-      const int32_t ka = (int32_t)__builtin_popcount(acc & HALF_LO);
-      const int32_t kb = (int32_t)__builtin_popcount(acc >> 16);
-      dA += (int32_t)nibble_sum(kept & HALF_LO, 0u) - 4 * ka;
-      dB += (int32_t)nibble_sum(kept >> 16, 0u) - 4 * kb;
-      cA += ka;
-      cB += kb;
+      const uint32_t acc = bitop3<0x2A>(sum + 0x33333333u, rej, sites);   // ~(a & b) & c
+      const uint32_t aA = acc & HALF_LO, aB = acc & ~HALF_LO;
+      dA = __builtin_amdgcn_udot8(sum, aA, dA, false);
+      dB = __builtin_amdgcn_udot8(sum, aB, dB, false);
+      cA += (int32_t)__builtin_popcount(aA);
+      cB += (int32_t)__builtin_popcount(aB);
       return acc;
     };
 
     // ---------------- stars: colours 0 and 1 ----------------
     static_for<2>([&](auto PH) {
       constexpr int phi = decltype(PH)::value;
+      uint32_t cN = c_star_of<NOISE>(st[0]);   // carried from row to row, as in the one-chain kernel
       static_for<L - 1>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int par = (i + phi) & 1;
@@ -173,21 +174,21 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
         constexpr int rank0 = star_row_rank<L>(i, phi);
         uint32_t cO = c_star_of<NOISE>(st[2 * i + 1]);
         if constexpr (NOISE == 1) cO |= 0x55555555u & ~pair_fields(L - 1);   // pad: c = 1
-        const uint32_t cN = c_star_of<NOISE>(st[2 * i]);
         const uint32_t cS = c_star_of<NOISE>(st[2 * i + 2]);
         // west neighbours; fields 0 and 8 read the padding value 1
         const uint32_t cWest = ((cO << 2) & ~0x00030003u) | 0x00010001u;
         constexpr uint32_t M = 0x33333333u;
         const uint32_t sum = ((cN >> (2 * par)) & M) + ((cS >> (2 * par)) & M) +
                              ((cO >> (2 * par)) & M) + ((cWest >> (2 * par)) & M);
+        cN = cS;
         const uint32_t acc = decide_row(std::integral_constant<int, par>{},
                                         std::integral_constant<int, nsite>{},
                                         std::integral_constant<int, phi * S + rank0>{},
                                         std::integral_constant<int, L>{}, sum);
-        const uint32_t ax = acc << (2 * par);
+        const uint32_t ax = shift_by<2 * par - 2>(acc);
         st[2 * i] ^= ax;
         st[2 * i + 2] ^= ax;
-        st[2 * i + 1] ^= (ax | (ax >> 2)) & pair_fields(L - 1) & 0x55555555u;
+        st[2 * i + 1] ^= (ax | (ax >> 2)) & pair_fields(L - 1) & 0xAAAAAAAAu;
         fence();
       });
       end_phase();
@@ -196,6 +197,7 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
     // ---------------- plaquettes: colours 2 and 3 ----------------
     static_for<2>([&](auto PH) {
       constexpr int phi = 2 + decltype(PH)::value;
+      uint32_t cN = 0x55555555u;
       static_for<L>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int par = (i + phi - 2) & 1;
@@ -203,22 +205,24 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
         constexpr int rank0 = plaq_row_rank<L>(i, phi - 2);
         if constexpr (nsite > 0) {
           const uint32_t cE = c_plaq_of<NOISE>(st[2 * i]);
-          uint32_t cN = 0x55555555u, cS = 0x55555555u;
-          if constexpr (i > 0) cN = c_plaq_of<NOISE>(st[2 * i - 1]);
+          uint32_t cS = 0x55555555u;
           if constexpr (i < L - 1) cS = c_plaq_of<NOISE>(st[2 * i + 1]);
           const uint32_t cEast = cE >> 2;   // a site's east field stays in its half
           constexpr uint32_t M = 0x33333333u;
           const uint32_t sum = ((cN >> (2 * par)) & M) + ((cS >> (2 * par)) & M) +
                                ((cE >> (2 * par)) & M) + ((cEast >> (2 * par)) & M);
+          cN = cS;
           const uint32_t acc = decide_row(std::integral_constant<int, par>{},
                                           std::integral_constant<int, nsite>{},
                                           std::integral_constant<int, phi * S + rank0>{},
                                           std::integral_constant<int, L - 1>{}, sum);
-          const uint32_t az = acc << (2 * par + 1);
+          const uint32_t az = shift_by<2 * par - 3>(acc);
           if constexpr (i > 0) st[2 * i - 1] ^= az;
           if constexpr (i < L - 1) st[2 * i + 1] ^= az;
           st[2 * i] ^= az | (az << 2);
           fence();
+        } else if constexpr (i < L - 1) {   // L = 2: a row without sites of this colour
+          cN = c_plaq_of<NOISE>(st[2 * i + 1]);
         }
       });
       end_phase();
@@ -239,12 +243,12 @@ __device__ __forceinline__ void run_pair(const RunArgs& a, const GroupDesc& g, i
   if (a.final_rows && A.chain == 0 && A.kt == g.K - 1) {
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      a.final_rows[A.it.rows_off + r * 4 + A.cls] = (st[r] & HALF_LO) | ~HALF_LO;
+      a.final_rows[A.it.rows_off + r * 4 + A.cls] = (row_code(st[r]) & HALF_LO) | ~HALF_LO;
   }
   if (a.final_rows && has_b && B.chain == 0 && B.kt == g.K - 1) {
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      a.final_rows[B.it.rows_off + r * 4 + B.cls] = (st[r] >> 16) | ~HALF_LO;
+      a.final_rows[B.it.rows_off + r * 4 + B.cls] = (row_code(st[r]) >> 16) | ~HALF_LO;
   }
 }
 

@@ -73,6 +73,12 @@ __device__ __forceinline__ uint32_t xor3_key(uint32_t a, uint32_t b, uint32_t k)
   return r;
 }
 
+// Three-input bit operation: bit 4a + 2b + c of TABLE for bits a, b, c.
+template <uint32_t TABLE>
+__device__ __forceinline__ uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, TABLE);
+}
+
 __device__ __forceinline__ uint4 philox_round(uint4 c, uint32_t k0, uint32_t k1) {
   uint32_t h0, l0, h1, l1;
   mulhilo(PHILOX_M0, c.x, h0, l0);
@@ -164,19 +170,21 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
 // folds away.
 struct ChainRng {
   uint32_t k0, k1;
-  uint32_t sid_hi, sid_lo;   // M1 * sid
-  uint32_t ctr3;
+  uint32_t sid_hi, sid_x;    // M1 * sid, the low word ^ (k0 + W0)
+  uint32_t ctr3;             // counter word 3 ^ k1
   uint32_t ctr3_sw;          // ctr3, made opaque once per sweep (see begin_sweep)
-  uint32_t sw_hi, sw_lo;     // M0 * (sid_hi ^ sweep ^ k0), per sweep
+  uint32_t sw_x, sw_lo;      // M0 * (sid_hi ^ sweep ^ k0), the high word ^ (k1 + W1), per sweep
 
   __device__ __forceinline__ void init(uint32_t key0, uint32_t key1, uint32_t sid, uint32_t c3) {
     k0 = key0;
     k1 = key1;
-    ctr3 = c3;
-    mulhilo(PHILOX_M1, sid, sid_hi, sid_lo);
+    ctr3 = c3 ^ key1;
+    mulhilo(PHILOX_M1, sid, sid_hi, sid_x);
+    sid_x ^= key0 + PHILOX_W0;
   }
   __device__ __forceinline__ void begin_sweep(uint32_t sweep) {
-    mulhilo(PHILOX_M0, sid_hi ^ sweep ^ k0, sw_hi, sw_lo);
+    mulhilo(PHILOX_M0, sid_hi ^ sweep ^ k0, sw_x, sw_lo);
+    sw_x ^= k1 + PHILOX_W1;
     // The second-round product of every block depends only on (blk, ctr3);
     // without this the compiler hoists all of them out of the sweep loop and
     // keeps two live registers per block, which costs far more occupancy
@@ -184,42 +192,34 @@ struct ChainRng {
     ctr3_sw = ctr3;
     asm volatile("" : "+v"(ctr3_sw));
   }
+  // Block BLK's counter after two rounds; after round 0 it is
+  // (sid_hi ^ sweep ^ k0, sid_lo, hi0 ^ ctr3 ^ k1, lo0).
   template <int BLK>
-  __device__ __forceinline__ uint4 block() const {
+  __device__ __forceinline__ uint4 after_two() const {
     constexpr uint64_t pb = (uint64_t)PHILOX_M0 * (uint64_t)(uint32_t)BLK;
     constexpr uint32_t hi0 = (uint32_t)(pb >> 32), lo0 = (uint32_t)pb;
-    // after round 0: (sid_hi ^ sweep ^ k0, sid_lo, hi0 ^ ctr3 ^ k1, lo0)
     uint32_t qh, ql;
-    mulhilo(PHILOX_M1, hi0 ^ ctr3_sw ^ k1, qh, ql);
-    const uint4 c = make_uint4(qh ^ sid_lo ^ (k0 + PHILOX_W0), ql,
-                               sw_hi ^ lo0 ^ (k1 + PHILOX_W1), sw_lo);
-    return philox_rounds(c, k0, k1, 2);
+    mulhilo(PHILOX_M1, hi0 ^ ctr3_sw, qh, ql);
+    return make_uint4(qh ^ sid_x, ql, sw_x ^ lo0, sw_lo);
+  }
+  template <int BLK>
+  __device__ __forceinline__ uint4 block() const {
+    return philox_rounds(after_two<BLK>(), k0, k1, 2);
   }
   // Blocks BLK and BLK + 1 together (identical words to two block() calls).
   template <int BLK>
   __device__ __forceinline__ void block_pair(uint4& b0, uint4& b1) const {
-    constexpr uint64_t pa = (uint64_t)PHILOX_M0 * (uint64_t)(uint32_t)BLK;
-    constexpr uint64_t pc = (uint64_t)PHILOX_M0 * (uint64_t)(uint32_t)(BLK + 1);
-    constexpr uint32_t ha = (uint32_t)(pa >> 32), la = (uint32_t)pa;
-    constexpr uint32_t hc = (uint32_t)(pc >> 32), lc = (uint32_t)pc;
-    uint32_t qh, ql, rh, rl;
-    mulhilo(PHILOX_M1, ha ^ ctr3_sw ^ k1, qh, ql);
-    mulhilo(PHILOX_M1, hc ^ ctr3_sw ^ k1, rh, rl);
-    b0 = make_uint4(qh ^ sid_lo ^ (k0 + PHILOX_W0), ql, sw_hi ^ la ^ (k1 + PHILOX_W1), sw_lo);
-    b1 = make_uint4(rh ^ sid_lo ^ (k0 + PHILOX_W0), rl, sw_hi ^ lc ^ (k1 + PHILOX_W1), sw_lo);
+    b0 = after_two<BLK>();
+    b1 = after_two<BLK + 1>();
     philox_rounds2(b0, b1, k0, k1, 2);
   }
   // Blocks BLK .. BLK + 3 together.
   template <int BLK>
   __device__ __forceinline__ void block_quad(uint4 (&b)[4]) const {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint64_t pa = (uint64_t)PHILOX_M0 * (uint64_t)(uint32_t)(BLK + i);
-      const uint32_t ha = (uint32_t)(pa >> 32), la = (uint32_t)pa;
-      uint32_t qh, ql;
-      mulhilo(PHILOX_M1, ha ^ ctr3_sw ^ k1, qh, ql);
-      b[i] = make_uint4(qh ^ sid_lo ^ (k0 + PHILOX_W0), ql, sw_hi ^ la ^ (k1 + PHILOX_W1), sw_lo);
-    }
+    b[0] = after_two<BLK>();
+    b[1] = after_two<BLK + 1>();
+    b[2] = after_two<BLK + 2>();
+    b[3] = after_two<BLK + 3>();
     philox_rounds4(b, k0, k1, 2);
   }
 };
