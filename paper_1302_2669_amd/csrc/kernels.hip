@@ -137,7 +137,7 @@ hipError_t launch_unpack(int L, int noise, const uint32_t* rows, int64_t count, 
 }
 
 // ---------------------------------------------------------------------------
-// Estimator and decision (Eq. main, Sec. IV.A), one thread per syndrome, FP64
+// Estimator and decision (Eq. main, Sec. IV.A), FP64
 // in a fixed order with no contraction:
 //   mean_{E,k} = (sum_c S) / (C * 4 * sweeps)   (mean final weight if sweeps = 0;
 //                n_stab samples per sweep instead of 4 for the random scan)
@@ -150,10 +150,30 @@ hipError_t launch_unpack(int L, int noise, const uint32_t* rows, int64_t count, 
 // Decision by the integer key sum_{k<K} w_k S_{E,k} + S_{E,K} (all I_E share
 // f0 and the denominator), ties to the lowest class.
 // ---------------------------------------------------------------------------
+//
+// P lanes per class, 4 P per syndrome: the integer sums over replicas are split
+// over the lanes, every lane of a class then runs the same FP64 sequence, and
+// the correction's bytes are written by consecutive lanes.  With one thread per
+// syndrome a lone syndrome waited on n_q dependent byte stores (40 us at L = 13,
+// now 5) and a full batch wrote uncoalesced (65536: 171 us, now 50).  A wave per
+// syndrome (P = 16) is the shortest for one; full batches take P = 4, a quarter
+// of the waves (launch_decide).
 #pragma clang fp contract(off)
-__global__ void __launch_bounds__(128) decide_kernel(const DecideArgs a) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ int64_t shfl64(int64_t v, int lane) {
+  const int lo = __shfl((int)(uint32_t)v, lane), hi = __shfl((int)(v >> 32), lane);
+  return (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+__device__ __forceinline__ double shfl_f64(double v, int lane) {
+  return __longlong_as_double(shfl64(__double_as_longlong(v), lane));
+}
+
+template <int P>
+__global__ void __launch_bounds__(256) decide_kernel(const DecideArgs a) {
+  const int64_t s = (int64_t)blockIdx.x * (blockDim.x / (4 * P)) + threadIdx.x / (4 * P);
   if (s >= a.n) return;
+  // lane of the wave, of the syndrome's 4 P, and their first
+  const int wave_lane = threadIdx.x & 63, lane = wave_lane % (4 * P), first = wave_lane - lane;
+  const int e = lane / P, part = lane % P;
   GroupDesc g;
   int64_t orig, chain_off, rows_off, corr_off;
   double beta_bar, beta_star;
@@ -187,63 +207,67 @@ __global__ void __launch_bounds__(128) decide_kernel(const DecideArgs a) {
   const double nq = (double)(2 * L * L - 2 * L + 1);
   const double f0 = noise ? nq : 0.75 * nq;
   const double log_z0 = (double)(2 * L * (L - 1)) * a.ln2;
-  double logz[4];
-  int64_t key[4];
-  for (int e = 0; e < 4; ++e) {
-    const int64_t base = chain_off + (int64_t)e * K * C;
-    double acc = f0;
-    int64_t kk = 0;
-    double mean_last = 0.0, mean_first = 0.0;
-    for (int k = 0; k < K; ++k) {
-      int64_t sum = 0;
-      for (int c = 0; c < C; ++c)
-        sum += counted ? a.S[base + (int64_t)k * C + c] : (int64_t)a.n_final[base + (int64_t)k * C + c];
-      const double mean = (double)sum / denom;
-      if (k == 0) mean_first = mean;
-      if (k + 1 < K) {
-        acc = acc + ((k + 1) % 2 == 1 ? 4.0 : 2.0) * mean;
-        kk += ((k + 1) % 2 == 1 ? 4 : 2) * sum;
-      } else {
-        acc = acc + mean;
-        kk += sum;
-        mean_last = mean;
-      }
-    }
-    double integral;
-    if (K == 1) {
-      integral = (beta_star / 2.0) * (f0 + mean_first) + (beta_bar - beta_star) * mean_first;
+  const int64_t base = chain_off + (int64_t)e * K * C;
+  double acc = f0;
+  int64_t kk = 0;
+  double mean_last = 0.0, mean_first = 0.0;
+  for (int k = 0; k < K; ++k) {
+    int64_t sum = 0;
+    for (int c = part; c < C; c += P)
+      sum += counted ? a.S[base + (int64_t)k * C + c] : (int64_t)a.n_final[base + (int64_t)k * C + c];
+    for (int d = 1; d < P; d <<= 1) sum += shfl64(sum, wave_lane ^ d);
+    const double mean = (double)sum / denom;
+    if (k == 0) mean_first = mean;
+    if (k + 1 < K) {
+      acc = acc + ((k + 1) % 2 == 1 ? 4.0 : 2.0) * mean;
+      kk += ((k + 1) % 2 == 1 ? 4 : 2) * sum;
     } else {
-      const double h = beta_bar / (double)K;
-      integral = (acc * h) / 3.0;
+      acc = acc + mean;
+      kk += sum;
+      mean_last = mean;
     }
-    logz[e] = log_z0 - integral;
-    key[e] = kk;
-    if (a.mean_n) a.mean_n[orig * 4 + e] = mean_last;
   }
-  double m = logz[0];
-  for (int e = 1; e < 4; ++e) m = logz[e] > m ? logz[e] : m;
-  double ex[4];
-  for (int e = 0; e < 4; ++e) ex[e] = exp(logz[e] - m);
-  const double tot = ((ex[0] + ex[1]) + ex[2]) + ex[3];
-  for (int e = 0; e < 4; ++e) a.class_prob[orig * 4 + e] = ex[e] / tot;
+  double integral;
+  if (K == 1) {
+    integral = (beta_star / 2.0) * (f0 + mean_first) + (beta_bar - beta_star) * mean_first;
+  } else {
+    const double h = beta_bar / (double)K;
+    integral = (acc * h) / 3.0;
+  }
+  const double logz = log_z0 - integral;
+  double m = shfl_f64(logz, first);
+  int64_t key = shfl64(kk, first);
   int best = 0;
-  for (int e = 1; e < 4; ++e)
-    if (key[e] < key[best]) best = e;
+  for (int o = 1; o < 4; ++o) {
+    const double z = shfl_f64(logz, first + P * o);
+    m = z > m ? z : m;
+    const int64_t other = shfl64(kk, first + P * o);
+    if (other < key) {
+      key = other;
+      best = o;
+    }
+  }
+  const double ex = exp(logz - m);
+  const double tot = ((shfl_f64(ex, first) + shfl_f64(ex, first + P)) + shfl_f64(ex, first + 2 * P)) +
+                     shfl_f64(ex, first + 3 * P);
   // a gate's class route: the decision composed with the predicted class
   // (classes are the two logical parities, so composition is XOR)
   if (a.flip) best ^= a.flip[orig] & 3;
-  a.chosen[orig] = (uint8_t)best;
+  if (part == 0) {
+    if (a.mean_n) a.mean_n[orig * 4 + e] = mean_last;
+    a.class_prob[orig * 4 + e] = ex / tot;
+    if (lane == 0) a.chosen[orig] = (uint8_t)best;
+  }
 
   if (a.correction && a.final_rows) {
-    const int W = words_per_row(L);
+    const int W = words_per_row(L), side = 2 * L - 1, n_qubits = 2 * L * L - 2 * L + 1;
     uint8_t* out = a.correction + corr_off;
-    int q = 0;
-    for (int r = 0; r < 2 * L - 1; ++r) {
-      const int fields = (r & 1) ? L - 1 : L;
-      for (int f = 0; f < fields; ++f) {
-        const uint32_t word = a.final_rows[rows_off + (r * W + f / 16) * 4 + best];
-        out[q++] = (uint8_t)((word >> (2 * (f % 16))) & 3u);
-      }
+    const uint32_t* rows = a.final_rows + rows_off + best;
+    // qubit q: even row 2i holds L of them, odd row 2i + 1 L - 1
+    for (int q = lane; q < n_qubits; q += 4 * P) {
+      const int i = q / side, at = q - i * side;
+      const int r = 2 * i + (at >= L), f = at >= L ? at - L : at;
+      out[q] = (uint8_t)((rows[(r * W + f / 16) * 4] >> (2 * (f % 16))) & 3u);
     }
   }
 }
@@ -251,7 +275,10 @@ __global__ void __launch_bounds__(128) decide_kernel(const DecideArgs a) {
 
 hipError_t launch_decide(const DecideArgs& a, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(decide_kernel, dim3((unsigned)((a.n + 127) / 128)), dim3(128), 0, s, a);
+  if (a.n >= 16384)   // at P = 16 that is 16 waves per SIMD of 256 CUs
+    hipLaunchKernelGGL(decide_kernel<4>, dim3((unsigned)((a.n + 15) / 16)), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(decide_kernel<16>, dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -1,0 +1,55 @@
+"""Kernel variants chosen by size, at the sizes where they can go wrong, through
+the C-ABI: every integer output bit-exact with the oracle or with the mapping
+already pinned to it."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_1302_2669_amd as mc  # noqa: E402
+from oracle import decoder, geometry, sampler  # noqa: E402
+
+from paper_1302_2669_amd.inputs import SEED_L9  # noqa: E402
+
+DEV = "cuda"
+
+
+def setup_module(module):
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+
+
+def to_np(d):
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in d.items()}
+
+
+@pytest.mark.parametrize("L,chains,K", [(4, 17, 1), (9, 33, 2), (3, 1, 4)])
+def test_estimator_lane_sums(L, chains, K):
+    # replica counts around the 16 lanes a class's sums are spread over
+    p, n = 0.12, 5
+    lat = geometry.Lattice(L)
+    syn, _, _ = sampler.sample(lat, p, SEED_L9 + L, np.arange(n))
+    g = to_np(mc.decode_batch(torch.from_numpy(syn).to(DEV), L, p, 2, SEED_L9, chains=chains,
+                              n_temps=K, want_sums=True))
+    o = decoder.decode(L, syn, p, 2, SEED_L9, chains_per_class=chains, n_temps=K)
+    for k in ("sum_n", "accepts", "chosen", "correction"):
+        assert np.array_equal(g[k], o[k]), k
+    np.testing.assert_allclose(g["class_prob"], o["class_prob"], rtol=1e-12, atol=0)
+    np.testing.assert_allclose(g["mean_n"], o["mean_n"], rtol=1e-12, atol=0)
+
+
+def test_estimator_full_batches():
+    # four lanes per class from 16384 syndromes on: every syndrome as in a small batch
+    L, p, n = 3, 0.12, 16385
+    syn, _, _ = mc.sample_errors(L, p, 11, n)
+    big = to_np(mc.decode_batch(syn, L, p, 3, 11, chains=5, n_temps=2))
+    for lo in (0, 12000, n - 1000):
+        ids = torch.arange(lo, lo + 1000)
+        small = to_np(mc.decode_batch(syn[lo:lo + 1000], L, p, 3, 11, chains=5, n_temps=2,
+                                      syndrome_ids=ids))
+        for k in small:
+            assert np.array_equal(big[k][lo:lo + 1000], small[k]), k
