@@ -6,15 +6,24 @@
 // order; it is not the throughput path.
 //
 // Mapping.  One lane per chain as in the colour-phased kernels, but a random
-// site needs its rows by a runtime index, so each lane's packed configuration
-// lives in LDS, word-major with the workgroup's lanes side by side
-// (word k of lane l at [k][l]: any rows, no bank conflicts), plus one spare
-// word per lane.  The site table holds each qubit's word index and bit
-// offset, so a step issues its four word reads at once (a missing neighbour
-// reads the spare word), looks the weight change of each code up in a
-// 2-bit-field constant, and applies an accepted move with four LDS XORs
-// (two qubits of a site may share a word).  Workgroups are two waves; no
-// barrier after the set-up.
+// site needs its rows by a runtime index, so each lane's configuration lives
+// in LDS, one word (L <= 15) or one 64-bit word per grid row, row-major with
+// the wave's 64 lanes side by side (no bank conflicts).  A site touches one
+// qubit of the row above, two neighbouring ones of its own row and one of the
+// row below: three reads at one address with fixed offsets.  To make that hold
+// at the boundaries there is a padding row above and below, and odd rows are
+// stored one field up, so that field j and j + 1 of its own row are the site's
+// neighbours for stars and plaquettes alike.  Padding is Y: a star's move does
+// not change its weight whatever the x part, nor a plaquette's whatever the z
+// part, and no other move reaches that padding, so it may be flipped along.
+//
+// What bounds it.  A step is a serial chain (read, weight change, write), and
+// everything before it, the draws, the site's table entry and the number of
+// acceptance thresholds the draw reaches, depends on no state.  So a lane
+// takes its steps in batches of four: while the reads of a step are in
+// flight it works on the draws of the next batch (half a Philox block per
+// step).  4096 syndromes x 16 chains x 169 sweeps at L = 13, one wave per SIMD:
+// 25.8 -> 9.8 ms, 1175 -> 445 cycles per step.
 //
 // Randomness: step t of a sweep uses block t >> 1 of Philox4x32-10 at counter
 // (t >> 1, sweep, syndrome_id, 2<<30 | cls<<28 | temp<<20 | chain): word
@@ -28,63 +37,84 @@
 namespace mcmc {
 namespace {
 
-// two waves per workgroup share one copy of the site table, so that a CU
-// holds more chains' configurations (5 waves per SIMD at L = 13 instead of 4);
-// the largest code (L = 25) still fits the default 64 KB of dynamic LDS
-constexpr int RS_LANES = 128;
-constexpr uint32_t RS_NONE = 0xFFFFu;
+constexpr int RS_LANES = 64;
+// steps per batch: two Philox blocks; n_stab = 2 L (L - 1) is a multiple of 4
+constexpr int RS_BATCH = 4;
+// codes with one 32-bit word per row, the field past an odd row's end included
+constexpr int RS_NARROW_L_MAX = 15;
 
-// Per site: its 3-4 qubits as 16-bit codes, two per word: the qubit's word
-// of the packed configuration (grid row * words per row + field / 16) << 5 |
-// its bit offset 2 (field % 16); RS_NONE for a missing neighbour of a
-// boundary stabilizer (word indices stay below 2^11, so no code equals it).
-struct SiteQubits {
-  uint32_t q01, q23;
+template <bool WIDE>
+struct RowWord {
+  using type = uint32_t;
+};
+template <>
+struct RowWord<true> {
+  using type = uint64_t;
 };
 
-__device__ __forceinline__ uint32_t qcode(int W, int row, int field) {
-  return ((uint32_t)(row * W + (field >> 4)) << 5) | (uint32_t)(2 * (field & 15));
-}
-
-__device__ SiteQubits site_qubits(int L, int s) {
+// Table entry of a site (center row r, first field j of the row's pair):
+//   x: bits 0-5 shift of the pair (2 j), 8-14 (narrow) or 9-14 (wide) row
+//      offset in LDS (r 256 or r 512 bytes, the row above), 16-21 shift of
+//      the fields above and below;
+//   y: bits 0-5 and 8-13 the same shifts plus the flipped part's bit t (0:
+//      x, star; 1: z, plaquette), 16-17 2 - 2t, 24-31 the flipped part's bits
+//      of the four gathered codes (missing neighbours left out under
+//      bit/phase flips, where their padding would count).
+template <int NOISE, bool WIDE>
+__device__ uint2 site_entry(int L, int s) {
   const int nstar = L * (L - 1);
-  const int W = words_per_row(L);
-  uint32_t q[4] = {RS_NONE, RS_NONE, RS_NONE, RS_NONE};
-  int k = 0;
-  if (s < nstar) {  // star (i, j) at grid (2i+1, 2j)
-    const int i = s / L, j = s % L;
-    q[k++] = qcode(W, 2 * i, j);
-    q[k++] = qcode(W, 2 * i + 2, j);
-    if (j > 0) q[k++] = qcode(W, 2 * i + 1, j - 1);
-    if (j < L - 1) q[k++] = qcode(W, 2 * i + 1, j);
-  } else {          // plaquette (i, j) at grid (2i, 2j+1)
-    const int t = s - nstar;
-    const int i = t / (L - 1), j = t % (L - 1);
-    if (i > 0) q[k++] = qcode(W, 2 * i - 1, j);
-    if (i < L - 1) q[k++] = qcode(W, 2 * i + 1, j);
-    q[k++] = qcode(W, 2 * i, j);
-    q[k++] = qcode(W, 2 * i, j + 1);
+  const bool star = s < nstar;
+  const int k = star ? s : s - nstar, w = star ? L : L - 1;
+  const int i = k / w, j = k % w, t = star ? 0 : 1;
+  const int r = star ? 2 * i + 1 : 2 * i;
+  // odd rows are stored one field up: a plaquette's neighbours above and below
+  const int pair = 2 * j, single = star ? 2 * j : 2 * j + 2;
+  uint32_t own = star ? 0x55u : 0xAAu;
+  if (NOISE == 1) {   // gathered: above, below, first and second of the pair
+    if (star && j == 0) own &= ~0x30u;
+    if (star && j == L - 1) own &= ~0xC0u;
+    if (!star && i == 0) own &= ~0x03u;
+    if (!star && i == L - 1) own &= ~0x0Cu;
   }
-  SiteQubits r;
-  r.q01 = q[0] | (q[1] << 16);
-  r.q23 = q[2] | (q[3] << 16);
-  return r;
+  uint2 e;
+  e.x = (uint32_t)pair | ((uint32_t)(r * (WIDE ? 512 : 256))) | ((uint32_t)single << 16);
+  e.y = (uint32_t)(pair + t) | ((uint32_t)(single + t) << 8) | ((uint32_t)(2 - 2 * t) << 16) |
+        (own << 24);
+  return e;
 }
 
-template <int NOISE>
-__global__ void __launch_bounds__(RS_LANES) chains_random_kernel(const RunArgs a) {
-  extern __shared__ uint32_t rs_lds[];
+// acc + (u >= thr).
+__device__ __forceinline__ uint32_t count_reached(uint32_t acc, uint32_t u, uint32_t thr) {
+  asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
+      : "+v"(acc)
+      : "v"(u), "v"(thr)
+      : "vcc");
+  return acc;
+}
+
+// One step ahead of its turn: its site's entry and, as a negative number, how
+// many of the four thresholds its draw stays below (Delta n is accepted iff
+// it is at most that).
+struct Step {
+  uint2 site;
+  uint32_t minus_q;
+};
+
+template <int NOISE, bool WIDE>
+__global__ void __launch_bounds__(RS_LANES) __attribute__((amdgpu_waves_per_eu(4)))
+chains_random_kernel(const RunArgs a) {
+  using Row = typename RowWord<WIDE>::type;
+  extern __shared__ __align__(16) uint32_t rs_lds[];
   const GroupDesc g = a.g0;
   const int L = g.L;
   const int W = words_per_row(L);
   const int R = 2 * L - 1;
   const int RW = R * W;
   const int nstab = 2 * L * (L - 1);
-  const int nstar = L * (L - 1);
   const int lane = threadIdx.x;
-  SiteQubits* sites = reinterpret_cast<SiteQubits*>(rs_lds);
-  uint32_t* st = rs_lds + 2 * nstab;             // [RW][RS_LANES]
-  for (int s = lane; s < nstab; s += RS_LANES) sites[s] = site_qubits(L, s);
+  uint2* sites = reinterpret_cast<uint2*>(rs_lds);
+  Row* rows = reinterpret_cast<Row*>(rs_lds + 2 * nstab);   // [R + 2][RS_LANES]
+  for (int s = lane; s < nstab; s += RS_LANES) sites[s] = site_entry<NOISE, WIDE>(L, s);
   __syncthreads();
 
   const int64_t t = (int64_t)blockIdx.x * RS_LANES + lane;
@@ -99,118 +129,144 @@ __global__ void __launch_bounds__(RS_LANES) chains_random_kernel(const RunArgs a
   const int64_t out = item * per_item + rem;
   const int64_t rows_off = item * RW * 4;
   const uint32_t sid = a.syndrome_ids ? a.syndrome_ids[item] : (uint32_t)item;
+  uint32_t thr[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) thr[k] = a.table0[kt][k];
 
-  const uint32_t thr1 = a.table0[kt][0], thr2 = a.table0[kt][1], thr3 = a.table0[kt][2],
-                 thr4 = a.table0[kt][3];
-
-  int32_t n;
-  int64_t Ssum = 0, Acnt = 0;
-  if (a.resume_rows) {
-    for (int k = 0; k < RW; ++k)
-      st[k * RS_LANES + lane] = a.resume_rows[(int64_t)k * a.total_chains + out];
-    n = a.resume_n[out];
-    Ssum = a.resume_S[out];
-    Acnt = a.resume_A[out];
-  } else {
-    for (int k = 0; k < RW; ++k) st[k * RS_LANES + lane] = a.init_rows[rows_off + k * 4 + cls];
-    n = a.init_n[item * 4 + cls];
-  }
-
-  const uint32_t ctr3 = (2u << 30) | ((uint32_t)cls << 28) | ((uint32_t)(kt + 1) << 20) |
-                        (uint32_t)chain;
-  // missing neighbours of boundary stabilizers read and "flip" a spare word
-  // of the lane (with a zero mask), so that every step issues its four reads
-  // and four XORs without branches
-  const int sink = RW * RS_LANES + lane;
-  for (int sweep = g.sweep_begin; sweep < g.sweep_end; ++sweep) {
-    const bool counted = sweep >= g.burn;
-    // The draws and the site entry of step t + 1 are taken while step t is
-    // processed (the site table is read-only), so that their latency
-    // overlaps the current step.
-    uint4 blk = philox4x32_10(make_uint4(0u, (uint32_t)sweep, sid, ctr3), a.k0, a.k1);
-    int s = (int)__umulhi(blk.x, (uint32_t)nstab);
-    uint32_t u_acc = blk.y;
-    SiteQubits sq = sites[s];
-    for (int step = 0; step < nstab; ++step) {
-      int s_next = 0;
-      uint32_t acc_next = 0;
-      SiteQubits sq_next = sq;
-      if (step + 1 < nstab) {
-        uint32_t u_site_next;
-        if (((step + 1) & 1) == 0) {
-          blk = philox4x32_10(make_uint4((uint32_t)((step + 1) >> 1), (uint32_t)sweep, sid, ctr3),
-                              a.k0, a.k1);
-          u_site_next = blk.x;
-          acc_next = blk.y;
-        } else {
-          u_site_next = blk.z;
-          acc_next = blk.w;
-        }
-        s_next = (int)__umulhi(u_site_next, (uint32_t)nstab);
-        sq_next = sites[s_next];
-      }
-      const bool star = s < nstar;
-      const uint32_t qc[4] = {sq.q01 & 0xFFFFu, sq.q01 >> 16, sq.q23 & 0xFFFFu, sq.q23 >> 16};
-      int addr[4];
-      uint32_t sh[4];
-      bool valid[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        valid[k] = qc[k] != RS_NONE;
-        addr[k] = valid[k] ? (int)(qc[k] >> 5) * RS_LANES + lane : sink;
-        sh[k] = qc[k] & 31u;
-      }
-      uint32_t word[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) word[k] = st[addr[k]];
-      // change of the qubit's weight when the site's Pauli is applied, plus
-      // one, in 2-bit fields by its code (x + 2z): depolarizing, the weight
-      // (1 - other)(1 - 2 own) of own = the part the site flips (x for a star,
-      // z for a plaquette); bit/phase flips, 1 - 2 own
-      const uint32_t lut = NOISE == 1 ? (star ? 0x22u : 0x0Au) : (star ? 0x52u : 0x46u);
-      int delta = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t code = (word[k] >> sh[k]) & 3u;
-        const int term = (int)((lut >> (2u * code)) & 3u) - 1;
-        delta += valid[k] ? term : 0;
-      }
-      // threshold of delta = 1..4 (delta <= 0 is accepted whatever it is)
-      const uint32_t t12 = delta == 1 ? thr1 : thr2;
-      const uint32_t t34 = delta == 3 ? thr3 : thr4;
-      const uint32_t thr = delta <= 2 ? t12 : t34;
-      const bool accept = (delta <= 0) | (u_acc < thr);
-      if (accept) {
-        const uint32_t bit = star ? 1u : 2u;
-        // read-modify-writes in LDS order: two qubits of a site may share a word
-#pragma unroll
-        for (int k = 0; k < 4; ++k) atomicXor(&st[addr[k]], valid[k] ? bit << sh[k] : 0u);
-        n += delta;
-        ++Acnt;
-      }
-      if (counted) Ssum += n;
-      s = s_next;
-      sq = sq_next;
-      u_acc = acc_next;
+  rows[lane] = ~(Row)0;
+  rows[(R + 1) * RS_LANES + lane] = ~(Row)0;
+  for (int r = 0; r < R; ++r) {
+    Row v = ~(Row)0;
+    for (int w = W - 1; w >= 0; --w) {
+      const int k = r * W + w;
+      const uint32_t word = a.resume_rows ? a.resume_rows[(int64_t)k * a.total_chains + out]
+                                          : a.init_rows[rows_off + k * 4 + cls];
+      if constexpr (WIDE) v = w == 1 ? ((Row)word << 32) | 0xFFFFFFFFu : (v & ~(Row)0xFFFFFFFFu) | word;
+      else v = word;
     }
+    rows[(r + 1) * RS_LANES + lane] = (r & 1) ? (v << 2) | 3u : v;
+  }
+  int32_t n = a.resume_rows ? a.resume_n[out] : a.init_n[item * 4 + cls];
+  int64_t Ssum = a.resume_rows ? a.resume_S[out] : 0;
+  int64_t Acnt = a.resume_rows ? a.resume_A[out] : 0;
+
+  ChainRng rng;
+  rng.init(a.k0, a.k1, sid, (2u << 30) | ((uint32_t)cls << 28) | ((uint32_t)(kt + 1) << 20) |
+                                (uint32_t)chain);
+  // block b of the sweep begun last (b the same in every lane)
+  auto block = [&](uint32_t b) -> uint4 {
+    uint32_t hi0, lo0, qh, ql;
+    mulhilo(PHILOX_M0, b, hi0, lo0);
+    mulhilo(PHILOX_M1, hi0 ^ rng.ctr3, qh, ql);
+    uint4 v = make_uint4(qh ^ rng.sid_x, ql, rng.sw_x ^ lo0, rng.sw_lo);
+#pragma unroll
+    for (uint32_t r = 2; r < 10; ++r) v = philox_round(v, a.k0 + r * PHILOX_W0, a.k1 + r * PHILOX_W1);
+    return v;
+  };
+  auto step_of = [&](uint32_t u_site, uint32_t u_acc) -> Step {
+    Step s;
+    s.site = sites[__umulhi(u_site, (uint32_t)nstab)];
+    s.minus_q = (uint32_t)-4;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s.minus_q = count_reached(s.minus_q, u_acc, thr[k]);
+    return s;
+  };
+
+  char* const at0 = reinterpret_cast<char*>(rows) + lane * sizeof(Row);
+  constexpr uint32_t kShift = WIDE ? 63u : 31u;
+  Step cur[RS_BATCH], next[RS_BATCH];
+  if (g.sweep_begin < g.sweep_end) {
+    rng.begin_sweep((uint32_t)g.sweep_begin);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint4 v = block((uint32_t)h);
+      next[2 * h] = step_of(v.x, v.y);
+      next[2 * h + 1] = step_of(v.z, v.w);
+    }
+  }
+  for (int sweep = g.sweep_begin; sweep < g.sweep_end; ++sweep) {
+    int32_t moves = 0;
+    int64_t sum = 0;
+    for (int first = 0; first < nstab; first += RS_BATCH) {
+#pragma unroll
+      for (int k = 0; k < RS_BATCH; ++k) cur[k] = next[k];
+      // the batch after this one: of this sweep or the first of the next
+      uint32_t b = (uint32_t)(first + RS_BATCH) >> 1;
+      if (first + RS_BATCH == nstab) {
+        rng.begin_sweep((uint32_t)sweep + 1);
+        b = 0;
+      }
+      uint4 v;
+      int32_t batch_sum = 0;
+#pragma unroll
+      for (int k = 0; k < RS_BATCH; ++k) {
+        const uint2 e = cur[k].site;
+        Row* p = reinterpret_cast<Row*>(at0 + (e.x & (WIDE ? 0x7E00u : 0x7F00u)));
+        const Row up = p[0], mid = p[RS_LANES], down = p[2 * RS_LANES];
+        __builtin_amdgcn_sched_barrier(0);
+        // while they arrive: a block of the next batch, or its two steps
+        if (k % 2 == 0) {
+          v = block(b + k / 2);
+        } else {
+          next[k - 1] = step_of(v.x, v.y);
+          next[k] = step_of(v.z, v.w);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the four codes: above, below, the pair
+        const uint32_t single = e.x >> 16;
+        uint32_t code = ((uint32_t)(up >> (single & kShift)) & 3u) |
+                        (((uint32_t)(down >> (single & kShift)) & 3u) << 2);
+        code |= ((uint32_t)(mid >> (e.x & kShift)) & 15u) << 4;
+        // Delta n = (qubits whose weight the move changes) - 2 (those of them
+        // with the flipped part set): every valid qubit under bit/phase
+        // flips, else those without the other part
+        const uint32_t own = e.y >> 24;
+        uint32_t live = own;
+        if constexpr (NOISE == 0) live = own & ~((code << 1) >> ((e.y >> 16) & 3u));
+        const int32_t over = (int32_t)__builtin_popcount(live) + (int32_t)cur[k].minus_q -
+                             2 * (int32_t)__builtin_popcount(code & live);
+        if (over <= 0) {
+          const Row ms = (Row)1 << ((e.y >> 8) & kShift), mp = (Row)5 << (e.y & kShift);
+          p[0] = up ^ ms;
+          p[RS_LANES] = mid ^ mp;
+          p[2 * RS_LANES] = down ^ ms;
+          n += over - (int32_t)cur[k].minus_q;
+          ++moves;
+        }
+        batch_sum += n;
+      }
+      sum += batch_sum;
+    }
+    if (sweep >= g.burn) Ssum += sum;
+    Acnt += moves;
   }
 
   a.S_out[out] = Ssum;
   a.A_out[out] = Acnt;
   a.n_out[out] = n;
-  if (a.state_rows)
-    for (int k = 0; k < RW; ++k)
-      a.state_rows[(int64_t)k * a.total_chains + out] = st[k * RS_LANES + lane];
-  if (a.final_rows && chain == 0 && kt == K - 1)
-    for (int k = 0; k < RW; ++k) a.final_rows[rows_off + k * 4 + cls] = st[k * RS_LANES + lane];
+  for (int r = 0; r < R; ++r) {
+    Row v = rows[(r + 1) * RS_LANES + lane];
+    if (r & 1) v >>= 2;
+    for (int w = 0; w < W; ++w) {
+      const uint32_t word = (uint32_t)(v >> (32 * w)) | ~field_mask((r & 1) ? L - 1 : L, w);
+      if (a.state_rows) a.state_rows[(int64_t)(r * W + w) * a.total_chains + out] = word;
+      if (a.final_rows && chain == 0 && kt == K - 1)
+        a.final_rows[rows_off + (r * W + w) * 4 + cls] = word;
+    }
+  }
+}
+
+template <int NOISE, bool WIDE>
+hipError_t launch_random(const RunArgs& a, unsigned blocks, size_t lds, hipStream_t s) {
+  hipLaunchKernelGGL((chains_random_kernel<NOISE, WIDE>), dim3(blocks), dim3(RS_LANES), lds, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 size_t random_scan_lds_bytes(int L) {
-  const int nstab = 2 * L * (L - 1);
-  return (size_t)2 * nstab * sizeof(uint32_t) +
-         (size_t)(words_per_config(L) + 1) * RS_LANES * sizeof(uint32_t);
+  const size_t row = L <= RS_NARROW_L_MAX ? 4 : 8;
+  return (size_t)(2 * L * (L - 1)) * sizeof(uint2) + (size_t)(2 * L + 1) * RS_LANES * row;
 }
 
 hipError_t launch_chains_random(const RunArgs& a, hipStream_t s) {
@@ -219,11 +275,12 @@ hipError_t launch_chains_random(const RunArgs& a, hipStream_t s) {
   const int64_t blocks = (T + RS_LANES - 1) / RS_LANES;
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
   const size_t lds = random_scan_lds_bytes(a.g0.L);
+  const bool wide = a.g0.L > RS_NARROW_L_MAX;
   if (a.noise == MCMC_NOISE_BITPHASE)
-    hipLaunchKernelGGL(chains_random_kernel<1>, dim3((unsigned)blocks), dim3(RS_LANES), lds, s, a);
-  else
-    hipLaunchKernelGGL(chains_random_kernel<0>, dim3((unsigned)blocks), dim3(RS_LANES), lds, s, a);
-  return hipGetLastError();
+    return wide ? launch_random<1, true>(a, (unsigned)blocks, lds, s)
+                : launch_random<1, false>(a, (unsigned)blocks, lds, s);
+  return wide ? launch_random<0, true>(a, (unsigned)blocks, lds, s)
+              : launch_random<0, false>(a, (unsigned)blocks, lds, s);
 }
 
 }  // namespace mcmc

@@ -27,6 +27,30 @@ def to_np(d):
     return {k: v.cpu().numpy() for k, v in d.items()}
 
 
+# random scan: 32-bit rows up to L = 15 (odd rows one field up), 64-bit above;
+# 65 chains span two waves, the second almost empty
+@pytest.mark.parametrize("noise,p", [(0, 0.17), (1, 0.11)])
+@pytest.mark.parametrize("L,n,chains,K", [(2, 5, 13, 1), (4, 17, 1, 2), (14, 2, 3, 1),
+                                          (15, 3, 2, 1), (16, 3, 2, 1), (24, 2, 1, 2)])
+def test_random_scan_row_widths(L, n, chains, K, noise, p):
+    lat = geometry.Lattice(L)
+    syn, _, _ = sampler.sample(lat, p, SEED_L9 + L, np.arange(n), noise=noise)
+    s = torch.from_numpy(syn).to(DEV)
+    args = dict(chains=chains, n_temps=K, noise=noise, random_scan=True, want_sums=True)
+    first = mc.decode_batch(s, L, p, 1, SEED_L9, chain_state=True, **args)
+    out = mc.decode_batch(s, L, p, 2, SEED_L9, resume_from=(first["chain_state"], 1), **args)
+    st, w = mc.unpack_chain_state(out.pop("chain_state"), n, L, p, 2, SEED_L9, chains, K,
+                                  noise=noise)
+    g = to_np(out)
+    o = decoder.decode(L, syn, p, 2, SEED_L9, chains_per_class=chains, n_temps=K, noise=noise,
+                       scan=decoder.SCAN_RANDOM)
+    for k in ("sum_n", "accepts", "chosen", "correction"):
+        assert np.array_equal(g[k], o[k]), k
+    assert np.array_equal(st.cpu().numpy(), o["states"])
+    assert np.array_equal(w.cpu().numpy(), o["n_final"].astype(np.int32))
+    np.testing.assert_allclose(g["class_prob"], o["class_prob"], rtol=1e-12, atol=0)
+
+
 @pytest.mark.parametrize("L,chains,K", [(4, 17, 1), (9, 33, 2), (3, 1, 4)])
 def test_estimator_lane_sums(L, chains, K):
     # replica counts around the 16 lanes a class's sums are spread over
