@@ -35,7 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "spacetime_common.h"
+#include "spacetime_lanes.h"
 
 namespace mcmc {
 namespace {
@@ -370,6 +370,9 @@ hipError_t dispatch_fast(const SpaceTimeArgs& a, hipStream_t s) {
 
 hipError_t launch_spacetime_chains(const SpaceTimeArgs& a, hipStream_t s) {
   if (a.n_tasks == 0) return hipSuccess;
+  if (spacetime_lanes_take(a))
+    return a.L <= ST_LANES_SMALL_L_MAX ? launch_spacetime_lanes_small(a, s)
+                                       : launch_spacetime_lanes_large(a, s);
   if (a.L <= ST_FAST_L_MAX) return dispatch_fast<2>(a, s);
   return dispatch_window<SPACETIME_WIN_L_MIN>(a, s);
 }

@@ -1,0 +1,10 @@
+// Space-time chains with one lane per interval, L = 10 .. 12 (spacetime_lanes.h).
+#include "spacetime_lanes.h"
+
+namespace mcmc {
+
+hipError_t launch_spacetime_lanes_large(const SpaceTimeArgs& a, hipStream_t s) {
+  return dispatch_lanes<ST_LANES_SMALL_L_MAX + 1, SPACETIME_FAST_L_MAX>(a, s);
+}
+
+}  // namespace mcmc

@@ -11,6 +11,7 @@ torch = pytest.importorskip("torch")
 
 import paper_1302_2669_amd as mc  # noqa: E402
 from oracle import decoder, geometry, sampler  # noqa: E402
+from oracle import spacetime as stm  # noqa: E402
 
 from paper_1302_2669_amd.inputs import SEED_L9  # noqa: E402
 
@@ -77,3 +78,20 @@ def test_estimator_full_batches():
                                       syndrome_ids=ids))
         for k in small:
             assert np.array_equal(big[k][lo:lo + 1000], small[k]), k
+
+
+# space-time chains, one lane per interval up to L = 12 and 16 rounds: the skew
+# spans two words from round 8 on, lanes are left over where T does not divide
+# 64, and 17 rounds fall back to one lane per chain
+@pytest.mark.parametrize("L,T,n,chains", [(2, 16, 3, 3), (3, 9, 2, 4), (5, 8, 2, 2), (6, 7, 3, 1),
+                                          (7, 7, 3, 2), (8, 16, 1, 1), (9, 13, 1, 1), (10, 5, 1, 2),
+                                          (12, 16, 1, 1), (4, 17, 2, 1), (9, 1, 5, 3)])
+def test_spacetime_lanes(L, T, n, chains):
+    p, pm, sweeps = 0.06, 0.09, 3 if L < 8 else 2
+    obs, _, _, _ = stm.sample(geometry.Lattice(L), p, pm, T, SEED_L9 + L, np.arange(n))
+    g = to_np(mc.decode_spacetime(torch.from_numpy(obs).to(DEV), L, p, pm, sweeps, SEED_L9,
+                                  chains=chains, burn=1, want_sums=True))
+    o = stm.decode(L, obs, p, pm, sweeps, SEED_L9, chains_per_class=chains, burn=1)
+    for k in ("sum_n", "sum_m", "accepts", "chosen", "correction"):
+        assert np.array_equal(g[k], o[k]), k
+    np.testing.assert_allclose(g["class_prob"], o["class_prob"], rtol=1e-12, atol=0)
