@@ -6,6 +6,7 @@
 
 
 #include "../../include/mcmcdec.h"
+#include "chain_choice.h"
 #include "device_common.h"
 #include "host_common.h"
 #include "internal.h"
@@ -329,9 +330,19 @@ static int decode_batch(const uint8_t* syndromes, const uint32_t* syndrome_ids, 
   if (random_scan) {
     st = hip_status(launch_chains_random(a, s));
   } else {
-    const int range = range_of(L);
-    const int64_t waves = std::min<int64_t>(a.n_tiles, default_waves(range, device_cus()));
-    st = hip_status(launch_chains(range, a, (int)waves, 256, s));
+    const int range = range_of(L), cus = device_cus();
+    const int64_t total = a.g0.sweep_end - a.g0.sweep_begin;
+    // traces come from the one-lane kernels alone
+    if (!a.trace && lone_pays(L, T, total, 4 * cus)) {
+      st = hip_status(launch_chains_lone(a, s));
+    } else if (!a.trace && split_pays(L, T, total, 4 * cus)) {
+      a.n_tiles = (T + split_tile(L) - 1) / split_tile(L);
+      const int64_t waves = std::min<int64_t>(a.n_tiles, (int64_t)cus * 4 * SPLIT_WAVES);
+      st = hip_status(launch_chains_split(a, range_is_wide(range), (int)waves, s));
+    } else {
+      const int64_t waves = std::min<int64_t>(a.n_tiles, default_waves(range, cus));
+      st = hip_status(launch_chains(range, a, (int)waves, 256, s));
+    }
   }
   if (st != MCMC_OK) return st;
 

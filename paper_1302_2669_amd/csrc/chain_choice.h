@@ -1,0 +1,54 @@
+// Choice between the chain mappings: one chain per lane (chain_body.h), split
+// over L lanes (chain_split.h), one chain per wave (chain_lone.hip).
+//
+// The unit is SIMD cycles per update of 64 chains, measured on full and partly
+// filled chips (canonical starts, p = 0.1, L from 3 to 25).
+#pragma once
+
+#include <math.h>
+
+#include "internal.h"
+
+namespace mcmc {
+
+// One chain per lane, w waves on the SIMD: a lone wave waits 2.7 times as long
+// as it issues; from two waves on each adds its issue time.  Short rows leave
+// less to amortise a row's fixed work over.  L = 13, measured and estimated: 1
+// wave 186 / 181, 2 217 / 208, 3 272 / 275, 5 406 / 408; L = 5: 187 / 227, 249 /
+// 260, 337 / 344, 521 / 512.
+inline double one_lane_issue(int L) {
+  return (64.0 + 500.0 / (L * L)) * (L > 16 ? 1.07 : 1.0);
+}
+inline double one_lane_cycles(int L, double w) {
+  return one_lane_issue(L) * (w <= 1.0 ? 2.7 : w + 1.1);
+}
+
+// Split over L lanes, a wave's sweep: its lanes' Philox blocks with their
+// counts (250 cycles a block) and four phases of one or two row words.
+// Measured and estimated: L = 3 203 / 204, 5 139 / 140, 9 97 / 99, 13 106 / 106,
+// 16 86 / 86, 17 116 / 118, 21 93 / 89, 25 112 / 107.
+inline double split_cycles(int L) {
+  const int blocks = L / 2, words = (L + 15) / 16;
+  const double sweep = 250.0 * blocks + 4.0 * (110.0 * words + 26.0);
+  return sweep * 64.0 / (split_tile(L) * 2.0 * L * (L - 1));
+}
+
+// Whether a batch of `chains` equal chains of `sweeps` sweeps runs faster
+// split: one-lane waves come whole to a SIMD, the split work spreads evenly,
+// but its waves take some 40000 cycles longer to set up (3000 syndromes at L = 6
+// without a sweep: 171 us one-lane, 193 split).
+inline bool split_pays(int L, int64_t chains, int64_t sweeps, int simds) {
+  const double W = (double)chains / ((double)TILE * simds);
+  const double gain = one_lane_cycles(L, ceil(W)) - (split_cycles(L) * W + 20.0);
+  return gain * (double)sweeps * 2.0 * L * (L - 1) > 40000.0;
+}
+
+// One chain per wave (codes whose draws fill the lanes, LONE_L_MIN) pays up to
+// two waves per SIMD: 1966 chains at L = 13 234 us against 255 split, 2560 288
+// against 262.
+inline bool lone_pays(int L, int64_t chains, int64_t sweeps, int simds) {
+  return L >= LONE_L_MIN && chains <= 2 * (int64_t)simds &&
+         split_pays(L, chains, sweeps, simds);
+}
+
+}  // namespace mcmc

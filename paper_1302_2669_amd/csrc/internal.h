@@ -55,6 +55,8 @@ struct TileDesc {
 };
 
 constexpr int TILE = 64;        // tasks per tile (one wave)
+// tasks of a split tile: the chains one wave holds, one on L lanes each
+__host__ __device__ constexpr int split_tile(int L) { return 64 / L; }
 
 struct RunArgs {
   // explicit plan, or all nullptr for a uniform batch
@@ -89,6 +91,10 @@ struct RunArgs {
   int16_t* trace;                // [chain][trace_len] or nullptr
   int64_t trace_len;
   int32_t noise;                 // MCMC_NOISE_*: selects the kernel family
+  // split launches: a uniform batch's tasks start at split_from; a plan's tiles
+  // holds n_split groups, each with the number of tiles before it in first_task
+  int64_t split_from;
+  int32_t n_split;
 };
 
 // Persistent chain kernels, one per L range, each with the register budget
@@ -120,6 +126,16 @@ hipError_t launch_chains(int range, const RunArgs& a, int waves, int wg, hipStre
 constexpr int PAIR_L_MAX = 8;
 constexpr int PAIR_WAVES = 5;
 hipError_t launch_chains_pair(const RunArgs& a, int waves, int wg, hipStream_t s);
+// Chains split over L lanes each, in split tiles: tasks split_from .. of a
+// uniform batch (a.g0) or a plan's groups (a.tiles, a.n_split), of codes with
+// one-word rows (wide = false, L <= 16) or two-word rows.  No trace.
+constexpr int SPLIT_WAVES = 4;   // the kernels' register-limited waves per SIMD
+hipError_t launch_chains_split(const RunArgs& a, bool wide, int waves, hipStream_t s);
+hipError_t launch_chains_split_flip(const RunArgs& a, bool wide, int waves, hipStream_t s);
+// One chain per wave (a uniform batch of few chains, a.g0; no trace), codes
+// from LONE_L_MIN: below it a sweep's draws are at most two blocks per lane of L.
+constexpr int LONE_L_MIN = 6;
+hipError_t launch_chains_lone(const RunArgs& a, hipStream_t s);
 // Random-scan chains of a uniform batch (g0, table0, a.noise; no trace):
 // one 64-lane workgroup per 64 chains, each lane's state in LDS.
 hipError_t launch_chains_random(const RunArgs& a, hipStream_t s);

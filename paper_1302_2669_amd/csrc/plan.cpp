@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "../../include/mcmcdec.h"
+#include "chain_choice.h"
 #include "device_common.h"
 #include "host_common.h"
 #include "internal.h"
@@ -86,6 +87,11 @@ struct mcmc_plan {
   // the two-chains-per-lane kernel (pair_first[m], pair_tiles[m])
   int64_t small_tiles[2] = {0}, pair_first[2] = {0}, pair_tiles[2] = {0};
   std::vector<int> group_noise;      // noise model of each group
+  std::vector<char> group_split;     // whether its chains are split over lanes
+  // the split groups by noise model and row width (one-word rows 0, two-word
+  // rows 1): their entries in `tiles`, one per group, and their tiles
+  int64_t split_first[4] = {0}, split_tiles[4] = {0};
+  int32_t split_groups[4] = {0};
   int64_t total_chains = 0, total_rows = 0, total_updates = 0;
   size_t corr_bytes = 0;
   // device copies
@@ -195,6 +201,19 @@ int enqueue(mcmc_plan* p, const uint8_t* syn, double* prob, double* mean_n, int6
 
   const mcmc_tuning& tu = p->tuning;
   const int cus = device_cus();
+  // the split chains of row width `wide` under noise model m
+  auto run_split = [&](int m, int wide, hipStream_t on) -> int {
+    const int k = 2 * m + wide;
+    if (p->split_tiles[k] == 0) return MCMC_OK;
+    RunArgs ra = a;
+    ra.noise = m;
+    ra.tiles = p->d_tiles + p->split_first[k];
+    ra.n_tiles = p->split_tiles[k];
+    ra.n_split = p->split_groups[k];
+    ra.queue = queue + mcmc_plan::kSlots + 2 + k;
+    const int64_t waves = std::min<int64_t>(ra.n_tiles, (int64_t)cus * 4 * SPLIT_WAVES);
+    return hip_status(launch_chains_split(ra, wide != 0, (int)waves, on));
+  };
   auto run_range = [&](int slot, hipStream_t on) -> int {
     const int r = slot % N_RANGES, m = slot / N_RANGES;
     // the small codes of range 0 under the two-chains-per-lane mapping
@@ -233,6 +252,10 @@ int enqueue(mcmc_plan* p, const uint8_t* syn, double* prob, double* mean_n, int6
   bool used[N_RANGES] = {false};
   for (int slot = 0; slot < mcmc_plan::kSlots; ++slot)
     if (p->range_tiles[slot] != 0) used[slot % N_RANGES] = true;
+  // split chains with two-word rows run beside the widest range, the others
+  // before the narrowest
+  if (p->split_tiles[1] + p->split_tiles[3] != 0) used[N_RANGES - 1] = true;
+  if (p->split_tiles[0] + p->split_tiles[2] != 0) used[0] = true;
   bool narrow = false, wide = false;
   for (int r = 0; r < N_RANGES; ++r)
     if (used[r]) (range_is_wide(r) ? wide : narrow) = true;
@@ -255,6 +278,10 @@ int enqueue(mcmc_plan* p, const uint8_t* syn, double* prob, double* mean_n, int6
   }
   for (int r = N_RANGES - 1; r >= 0; --r) {   // longest tiles first
     for (int m = 0; m < 2; ++m) {
+      if (r == 0 || r == N_RANGES - 1) {
+        st = run_split(m, r != 0, side_of[r] >= 0 ? p->side[side_of[r]] : s);
+        if (st != MCMC_OK) return st;
+      }
       st = run_range(m * N_RANGES + r, side_of[r] >= 0 ? p->side[side_of[r]] : s);
       if (st != MCMC_OK) return st;
     }
@@ -356,12 +383,51 @@ void clear_plan(mcmc_plan* p) {
   p->total_chains = p->total_rows = p->total_updates = 0;
   for (int r = 0; r < mcmc_plan::kSlots; ++r) p->range_first[r] = p->range_tiles[r] = 0;
   for (int m = 0; m < 2; ++m) p->small_tiles[m] = p->pair_first[m] = p->pair_tiles[m] = 0;
+  for (int k = 0; k < 4; ++k) p->split_first[k] = p->split_tiles[k] = p->split_groups[k] = 0;
+  p->group_split.clear();
 }
 
 int build_plan(mcmc_plan* p, const mcmc_item* items, int64_t n) {
   const int st = build_plan_into(p, items, n);
   if (st != MCMC_OK) clear_plan(p);
   return st;
+}
+
+// Which groups run split over lanes.  A plan of one group decides as a uniform
+// batch.  With several the longest ones are split, as many as give the
+// shortest estimated execution: the larger of the work over all SIMDs and the
+// longest one-lane tile, which shares its SIMD with other waves.
+void choose_split(mcmc_plan* p) {
+  const size_t n = p->groups.size();
+  const int simds = 4 * device_cus();
+  p->group_split.assign(n, 0);
+  if (n == 1) {
+    p->group_split[0] =
+        split_pays(p->groups[0].L, p->groups[0].n_tasks, p->groups[0].sweep_end, simds);
+    return;
+  }
+  auto updates = [&](size_t gi) {
+    return (double)p->groups[gi].sweep_end * n_stab(p->groups[gi].L);
+  };
+  double work = 0.0;
+  for (size_t gi = 0; gi < n; ++gi)
+    work += (double)p->groups[gi].n_tasks / TILE * updates(gi) * one_lane_issue(p->groups[gi].L);
+  // groups are in descending cost: the longest one-lane tile is the first
+  // group's that is not split
+  double best = 0.0;
+  size_t best_count = 0;
+  for (size_t k = 0; k <= n; ++k) {   // groups 0 .. k - 1 split
+    const double tile = k < n ? updates(k) * one_lane_cycles(p->groups[k].L, 2.0) : 0.0;
+    const double t = std::max(work / simds, tile);
+    if (k == 0 || t < best) {
+      best = t;
+      best_count = k;
+    }
+    if (k == n) break;
+    const GroupDesc& g = p->groups[k];
+    work += (double)g.n_tasks / TILE * updates(k) * (split_cycles(g.L) - one_lane_issue(g.L));
+  }
+  for (size_t gi = 0; gi < best_count; ++gi) p->group_split[gi] = 1;
 }
 
 int build_plan_into(mcmc_plan* p, const mcmc_item* items, int64_t n) {
@@ -375,6 +441,8 @@ int build_plan_into(mcmc_plan* p, const mcmc_item* items, int64_t n) {
   p->total_chains = p->total_rows = p->total_updates = 0;
   for (int r = 0; r < mcmc_plan::kSlots; ++r) p->range_first[r] = p->range_tiles[r] = 0;
   for (int m = 0; m < 2; ++m) p->small_tiles[m] = p->pair_first[m] = p->pair_tiles[m] = 0;
+  for (int k = 0; k < 4; ++k) p->split_first[k] = p->split_tiles[k] = p->split_groups[k] = 0;
+  p->group_split.clear();
 
   // groups: (L, K, C, burn, sweeps) -> items, in order of first appearance
   // (a batch has few distinct keys: linear search with a last-hit cache)
@@ -501,6 +569,7 @@ int build_plan_into(mcmc_plan* p, const mcmc_item* items, int64_t n) {
     p->groups.push_back(g);
     p->group_noise.push_back(std::get<5>(k));
   }
+  choose_split(p);
   // tiles per launch slot (kernel range and noise model), each slot longest
   // first (groups are already in descending cost order)
   for (int slot = 0; slot < mcmc_plan::kSlots; ++slot) {
@@ -511,7 +580,7 @@ int build_plan_into(mcmc_plan* p, const mcmc_item* items, int64_t n) {
       const int64_t before = (int64_t)p->tiles.size();
       for (size_t gi = 0; gi < p->groups.size(); ++gi) {
         const GroupDesc& g = p->groups[gi];
-        if (range_of(g.L) != r || p->group_noise[gi] != m) continue;
+        if (range_of(g.L) != r || p->group_noise[gi] != m || p->group_split[gi]) continue;
         if ((g.L <= PAIR_L_MAX) != (part == 1)) continue;
         for (int64_t f = 0; f < g.n_tasks; f += TILE)
           p->tiles.push_back(TileDesc{(int32_t)gi, g.L, f});
@@ -524,11 +593,22 @@ int build_plan_into(mcmc_plan* p, const mcmc_item* items, int64_t n) {
     p->pair_first[m] = (int64_t)p->tiles.size();
     for (size_t gi = 0; gi < p->groups.size(); ++gi) {
       const GroupDesc& g = p->groups[gi];
-      if (g.L > PAIR_L_MAX || p->group_noise[gi] != m) continue;
+      if (g.L > PAIR_L_MAX || p->group_noise[gi] != m || p->group_split[gi]) continue;
       for (int64_t f = 0; f < g.n_tasks; f += 2 * TILE)
         p->tiles.push_back(TileDesc{(int32_t)gi, g.L, f});
     }
     p->pair_tiles[m] = (int64_t)p->tiles.size() - p->pair_first[m];
+  }
+  for (int k = 0; k < 4; ++k) {
+    p->split_first[k] = (int64_t)p->tiles.size();
+    for (size_t gi = 0; gi < p->groups.size(); ++gi) {
+      const GroupDesc& g = p->groups[gi];
+      if (!p->group_split[gi] || p->group_noise[gi] != k / 2 || (g.L > 16) != (k % 2 != 0)) continue;
+      p->tiles.push_back(TileDesc{(int32_t)gi, g.L, p->split_tiles[k]});
+      p->split_tiles[k] += (g.n_tasks + split_tile(g.L) - 1) / split_tile(g.L);
+      ++p->split_groups[k];
+    }
+    if (p->split_tiles[k] > 0x7FFFFFFF) return MCMC_ERANGE;
   }
   if ((int64_t)p->tiles.size() > 0xFFFFFFFFll) return MCMC_ERANGE;
 

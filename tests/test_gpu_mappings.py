@@ -52,6 +52,50 @@ def test_random_scan_row_widths(L, n, chains, K, noise, p):
     np.testing.assert_allclose(g["class_prob"], o["class_prob"], rtol=1e-12, atol=0)
 
 
+# The chain mappings of a uniform batch: a trace keeps every chain on one lane
+# (pinned to the oracle elsewhere); without one the batch runs one chain per
+# wave (few chains), split over lanes (up to about 1.7 waves per SIMD of 256
+# CUs), or whole one-lane waves with a split rest.  All integers are equal.
+def decode_pair(L, n, chains, K, noise, sweeps, burn=0, resume=False):
+    p = 0.11 if noise else 0.16
+    syn, _, _ = mc.sample_errors(L, p, 5 + L, n, noise=noise)
+    args = dict(chains=chains, n_temps=K, burn=burn, noise=noise, want_sums=True)
+    outs = []
+    for trace in (False, True):
+        if resume:
+            first = mc.decode_batch(syn, L, p, 1, 9, chain_state=True, trace=trace, **args)
+            out = mc.decode_batch(syn, L, p, sweeps, 9, trace=trace,
+                                  resume_from=(first["chain_state"], burn + 1), **args)
+        else:
+            out = mc.decode_batch(syn, L, p, sweeps, 9, chain_state=True, trace=trace, **args)
+        out.pop("trace", None)
+        st, w = mc.unpack_chain_state(out.pop("chain_state"), n, L, p, sweeps, 9, chains, K, burn,
+                                      noise=noise)
+        outs.append({**to_np(out), "states": st.cpu().numpy(), "weights": w.cpu().numpy()})
+    for k in outs[1]:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("noise", [0, 1])
+@pytest.mark.parametrize("L", list(range(2, 26)))
+def test_few_chains(L, noise):
+    decode_pair(L, 3, 3, 1, noise, 3, burn=1)       # 36 chains: one per wave from L = 6
+    decode_pair(L, 2, 5, 2, noise, 2, resume=True)
+
+
+@pytest.mark.parametrize("noise", [0, 1])
+@pytest.mark.parametrize("L", list(range(2, 26)))
+def test_split_chains(L, noise):
+    decode_pair(L, 231, 7, 1, noise, 2)             # 6468 chains, a ragged last tile
+
+
+@pytest.mark.parametrize("L,noise,chains", [(2, 0, 65), (6, 1, 65), (9, 0, 100), (13, 0, 100),
+                                            (13, 1, 65), (16, 0, 65), (17, 1, 65), (21, 0, 100),
+                                            (25, 0, 80)])
+def test_one_lane_waves_with_a_split_rest(L, noise, chains):
+    decode_pair(L, 513, chains, 1, noise, 1)        # 2.0 to 3.1 one-lane waves per SIMD
+
+
 @pytest.mark.parametrize("L,chains,K", [(4, 17, 1), (9, 33, 2), (3, 1, 4)])
 def test_estimator_lane_sums(L, chains, K):
     # replica counts around the 16 lanes a class's sums are spread over
