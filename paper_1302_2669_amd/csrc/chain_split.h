@@ -10,7 +10,7 @@
 // rows it shares with its neighbours move by one-lane DPP shifts (a star row
 // reads the even row of lane i + 1 and flips it, a plaquette row the odd row
 // of lane i - 1).  A phase is then a few dozen instructions instead of L rows
-// of them: 16 chains at L = 13 take 1.9 us per sweep, 4001 x 16 chains 3.4 ms
+// of them: 16 chains at L = 13 take 1.9 us per sweep, 4001 x 16 chains 3.6 ms
 // instead of 5.3 with flips and 169 sweeps.
 //
 // Draws.  The 2 L (L - 1) draws of a sweep are the L (L - 1) / 2 Philox

@@ -18,8 +18,8 @@
 //                          scalar)
 //
 // Problem (one anyon type, one line parity): vertices 0..nv-1 are the lit
-// sites in ascending site order (crd = i << 8 | j), then NEAR (crd 0xff00) if
-// the parity is odd, then FAR (crd 0xff01) if the number of lit sites plus
+// sites in ascending site order, then NEAR if
+// the parity is odd, then FAR if the number of lit sites plus
 // the parity is odd.  Matching weight of a pair (twice the d 2^53 + 2 t of
 // the plain definition, which orders matchings the same way):
 // W = d 2^54 + 4 t with d the shortest-path distance
@@ -69,7 +69,18 @@ namespace mcmc {
 namespace mw {
 
 constexpr uint16_t NEAR_ID = 4094, FAR_ID = 4095;
-constexpr uint16_t CRD_NEAR = 0xff00, CRD_FAR = 0xff01, CRD_DUMMY = 0xff02;
+// A vertex's place, four bytes: row i, column j, its distances to the near and
+// far boundary.  With the boundary vertices at these places one expression
+// gives every pair's distance: min(|di| + |dj|, near + near', far + far') is
+// near or far for a lit site and NEAR or FAR (200 rows away), and L for NEAR
+// and FAR (FAR's column is L).
+MW_HD constexpr uint32_t place(uint32_t i, uint32_t j, uint32_t nr, uint32_t fr) {
+  return i | (j << 8) | (nr << 16) | (fr << 24);
+}
+constexpr uint32_t BOUNDARY_ROW = 200, NOWHERE = 100;
+constexpr uint32_t PLACE_NEAR = place(BOUNDARY_ROW, 0, 0, NOWHERE);
+constexpr uint32_t PLACE_FAR = place(BOUNDARY_ROW, 0, NOWHERE, 0);   // + L << 8
+constexpr uint32_t PLACE_DUMMY = place(255, 0, NOWHERE, NOWHERE);
 // weight of the dummy vertex's pairs other than the one with FAR: never tight
 constexpr int64_t W_NEVER = (int64_t)1 << 61;
 constexpr int64_t INF = (int64_t)1 << 62;
@@ -90,10 +101,12 @@ MW_HD int capacity(int L) { return ((L * (L - 1) + 2) + 3) & ~3; }
 // bytes of one problem's state (nodes: nn = cap + cap / 2)
 MW_HD size_t region_bytes(int cap) {
   // int64: u, best, key [cap], z [cap/2] (blossom b at z[b - cap])
-  // int16: crd, mate, top, bestS, list, slist [cap], freel [cap/2]
+  // uint32: pos [cap]
+  // int16: mate, top, bestS, list [cap], freel [cap/2]
   //        par, lab, tS, tT, base, bfirst, cnext, cprev, cex, cey, mark,
   //        tid [nn]
-  //        stack [2 nn] ((node, vertex) pairs)
+  //        stack [2 nn] ((node, vertex) pairs; recompute's S list [cap] outside
+  //        the rotations)
   return (size_t)cap * 83;
 }
 
@@ -102,12 +115,12 @@ struct Solver {
   WV wv;
   int64_t *u, *best, *z;
   uint64_t* key;
-  uint16_t* crd;
+  uint32_t* pos;
   int16_t *mate, *top, *bestS, *freel, *list, *slist;
   int16_t *par, *lab, *tS, *tT, *base, *bfirst, *cnext, *cprev, *cex, *cey, *mark, *tid;
   int16_t* stk;
   int nv, cap, nn, L, nfree, k_lit;
-  bool star, fail;
+  bool star, fail, dummy;   // dummy: vertex nv - 1 is the dummy
 
   MW_FN void carve(uint8_t* r, int cap_) {
     cap = cap_;
@@ -117,49 +130,52 @@ struct Solver {
     best = p64 + cap;
     key = reinterpret_cast<uint64_t*>(p64 + 2 * cap);
     z = p64 + 3 * cap;
-    int16_t* p16 = reinterpret_cast<int16_t*>(p64 + 3 * cap + cap / 2);
-    crd = reinterpret_cast<uint16_t*>(p16); p16 += cap;
+    pos = reinterpret_cast<uint32_t*>(p64 + 3 * cap + cap / 2);
+    int16_t* p16 = reinterpret_cast<int16_t*>(pos + cap);
     mate = p16; p16 += cap;
     top = p16; p16 += cap;
     bestS = p16; p16 += cap;
     list = p16; p16 += cap;
-    slist = p16; p16 += cap;
     freel = p16; p16 += cap / 2;
     int16_t** node[12] = {&par, &lab, &tS, &tT, &base, &bfirst, &cnext, &cprev, &cex, &cey,
                           &mark, &tid};
     for (int k = 0; k < 12; ++k) { *node[k] = p16; p16 += nn; }
     stk = p16;
+    slist = stk;
   }
-  MW_FN bool is_boundary(int v) const { return crd[v] >= CRD_NEAR; }
+  MW_FN bool is_boundary(int v) const { return (pos[v] & 255) >= BOUNDARY_ROW; }
+  MW_FN uint32_t place_far() const { return PLACE_FAR + ((uint32_t)L << 8); }
   // an element every lane reads at the same index, as a wave-uniform value
   MW_FN int rd(const int16_t* a, int i) const { return wv.uni((int)a[i]); }
   MW_FN int64_t rd(const int64_t* a, int i) const { return wv.uni64(a[i]); }
 
   // ---------------------------------------------------------------- weights
   MW_FN void near_far(int v, int& nr, int& fr) const {
-    const int i = crd[v] >> 8, j = crd[v] & 255;
-    if (star) { nr = i + 1; fr = L - 1 - i; } else { nr = j + 1; fr = L - 1 - j; }
+    nr = (int)((pos[v] >> 16) & 255);
+    fr = (int)(pos[v] >> 24);
   }
-  MW_FN int dist(int a, int b) const {
-    const bool ba = is_boundary(a), bb = is_boundary(b);
-    if (!ba && !bb) {
-      int na, fa, nb, fb;
-      near_far(a, na, fa);
-      near_far(b, nb, fb);
-      const int di = (crd[a] >> 8) - (crd[b] >> 8), dj = (crd[a] & 255) - (crd[b] & 255);
-      const int man = (di < 0 ? -di : di) + (dj < 0 ? -dj : dj);
-      const int via = na + nb < fa + fb ? na + nb : fa + fb;
-      return man < via ? man : via;
-    }
-    if (!ba) { int na, fa; near_far(a, na, fa); return crd[b] == CRD_NEAR ? na : fa; }
-    if (!bb) { int nb, fb; near_far(b, nb, fb); return crd[a] == CRD_NEAR ? nb : fb; }
-    return L;
+  // A slack is the unit of every pass over the pairs (47000 of them per type at
+  // L = 25, p = 0.1), so the distance has no branch on the kind of vertex (65536
+  // syndromes at L = 13 7.1 -> 6.2 ms, 4096 at L = 25 9.1 -> 7.6 ms).
+  MW_FN static uint32_t distance(uint32_t pa, uint32_t pb) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const uint32_t man = __builtin_amdgcn_sad_u8(pa & 0xFFFFu, pb & 0xFFFFu, 0u);
+#else
+    const int di = (int)(pa & 255) - (int)(pb & 255);
+    const int dj = (int)((pa >> 8) & 255) - (int)((pb >> 8) & 255);
+    const uint32_t man = (uint32_t)((di < 0 ? -di : di) + (dj < 0 ? -dj : dj));
+#endif
+    const uint32_t via = (pa >> 16) + (pb >> 16);   // near sum (at most 200), far sum above it
+    const uint32_t vn = via & 255, vf = via >> 8;
+    const uint32_t m = vn < vf ? vn : vf;
+    return man < m ? man : m;
   }
   MW_FN int64_t weight(int a, int b) const {
-    if ((crd[a] | crd[b]) >= CRD_DUMMY && (crd[a] == CRD_DUMMY || crd[b] == CRD_DUMMY))
-      return (crd[a] == CRD_FAR || crd[b] == CRD_FAR) ? 0 : W_NEVER;
+    const uint32_t pa = pos[a], pb = pos[b];
+    if (dummy && (pa == PLACE_DUMMY || pb == PLACE_DUMMY))
+      return (pa == place_far() || pb == place_far()) ? 0 : W_NEVER;
     const uint64_t t = (key[a] * key[b]) >> 21;
-    return ((int64_t)dist(a, b) << 54) + 4 * (int64_t)t;
+    return (int64_t)(((uint64_t)distance(pa, pb) << 54) + 4 * t);
   }
   MW_FN int64_t slack(int a, int b) const {
     MW_COUNT(slack);
@@ -521,7 +537,9 @@ struct Solver {
     // (every slack stays >= 0; slacks are even, so u stays even) and is
     // matched along the edge that became tight when that edge's other end is
     // still exposed (exposed ends first among equal slacks)
-    for (int v = 0; v < nv; ++v) {
+    const int exposed = collect([&](int y) { return mate[y] < 0; });
+    for (int e = 0; e < exposed; ++e) {
+      const int v = rd(list, e);
       if (rd(mate, v) >= 0) continue;
       int64_t key = INF;
       int idx = 0x7fff;
@@ -565,10 +583,11 @@ struct Solver {
     const bool odd = (k & 1) != 0;
     const int va = odd ? k + 1 : k, vb = va + 1;  // the two new vertices
     if (wv.lane == 0) {
-      crd[va] = CRD_NEAR; key[va] = splitmix64(NEAR_ID);
-      if (odd) { crd[vb] = CRD_DUMMY; key[vb] = 0; }
-      else { crd[vb] = CRD_FAR; key[vb] = splitmix64(FAR_ID); }
+      pos[va] = PLACE_NEAR; key[va] = splitmix64(NEAR_ID);
+      if (odd) { pos[vb] = PLACE_DUMMY; key[vb] = 0; }
+      else { pos[vb] = place_far(); key[vb] = splitmix64(FAR_ID); }
     }
+    dummy = odd;
     for (int v = va + wv.lane; v <= vb; v += WV::N) {
       mate[v] = -1; top[v] = (int16_t)v; par[v] = -1; base[v] = (int16_t)v;
       mark[v] = 0; bfirst[v] = -1;
@@ -754,6 +773,7 @@ struct Solver {
     L = L_;
     star = star_;
     fail = false;
+    dummy = false;
     const int nsite = L * (L - 1);
     const int first = star ? 0 : nsite, nc = star ? L : L - 1;
     int k = 0;
@@ -763,14 +783,15 @@ struct Solver {
       const int slot = wv.compact(lit, k);
       if (lit) {
         key[slot] = splitmix64((uint64_t)(first + t));
-        crd[slot] = (uint16_t)(((t / nc) << 8) | (t % nc));
+        const uint32_t i = (uint32_t)(t / nc), j = (uint32_t)(t % nc), at = star ? i : j;
+        pos[slot] = place(i, j, at + 1, (uint32_t)(L - 1) - at);
       }
     }
     k_lit = k;
     int n = k;
     if (wv.lane == 0) {
-      if (parity) { key[n] = splitmix64(NEAR_ID); crd[n] = CRD_NEAR; }
-      if ((k + parity) & 1) { key[n + parity] = splitmix64(FAR_ID); crd[n + parity] = CRD_FAR; }
+      if (parity) { key[n] = splitmix64(NEAR_ID); pos[n] = PLACE_NEAR; }
+      if ((k + parity) & 1) { key[n + parity] = splitmix64(FAR_ID); pos[n + parity] = place_far(); }
     }
     n += parity + ((k + parity) & 1);
     nv = n;
@@ -795,22 +816,25 @@ struct Solver {
     else for (int k = 0; k < L; ++k) wv.xor_word(&pl[2 * k], 1u);
   }
 
+  MW_FN int row_of(int v) const { return (int)(pos[v] & 255); }
+  MW_FN int col_of(int v) const { return (int)((pos[v] >> 8) & 255); }
+
   // XOR the solved part into plane pl (bit f of word r = field f of grid row
   // r).  A problem that hit a bound gets the canonical part instead (every
   // anyon's string to the near boundary, and the logical if the parity needs
   // it).
   MW_FN void paint(uint32_t* pl, int parity) {
     if (fail) {
-      for (int a = wv.lane; a < k_lit; a += WV::N) paint_side(pl, crd[a] >> 8, crd[a] & 255, 0);
+      for (int a = wv.lane; a < k_lit; a += WV::N) paint_side(pl, row_of(a), col_of(a), 0);
       if (wv.lane == 0 && (k_lit & 1) != parity) paint_logical(pl);
       return;
     }
     for (int a = wv.lane; a < nv; a += WV::N) {
       const int b = mate[a];
-      if (b < a || crd[a] == CRD_DUMMY || crd[b] == CRD_DUMMY) continue;
+      if (b < a || pos[a] == PLACE_DUMMY || pos[b] == PLACE_DUMMY) continue;
       const bool ba = is_boundary(a), bb = is_boundary(b);
       if (!ba && !bb) {
-        const int i1 = crd[a] >> 8, j1 = crd[a] & 255, i2 = crd[b] >> 8, j2 = crd[b] & 255;
+        const int i1 = row_of(a), j1 = col_of(a), i2 = row_of(b), j2 = col_of(b);
         int na, fa, nb, fb;
         near_far(a, na, fa);
         near_far(b, nb, fb);
@@ -831,7 +855,7 @@ struct Solver {
           paint_side(pl, i2, j2, side);
         }
       } else if (!ba) {
-        paint_side(pl, crd[a] >> 8, crd[a] & 255, crd[b] == CRD_NEAR ? 0 : 1);
+        paint_side(pl, row_of(a), col_of(a), pos[b] == PLACE_NEAR ? 0 : 1);
       } else {
         paint_logical(pl);
       }
