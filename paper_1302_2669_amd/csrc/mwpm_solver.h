@@ -195,16 +195,12 @@ struct Solver {
     fail = true;
     return x;
   }
-  // the S node above S node B in its tree, -1 for a root
+  // the S node above S node B in its tree, -1 for a root: an S node's tS is
+  // the vertex of that node its T node hangs from (two reads; by way of its
+  // mate and T node it would be five, each waiting on the one before)
   MW_FN int s_parent(int B) const {
-    const int m = rd(mate, rd(base, B));
-    if (m < 0) return -1;
-    return rd(top, rd(tS, rd(top, m)));
-  }
-  // (x in X, y in the tree parent of X)
-  MW_FN void up_edge(int X, int& x, int& y) const {
-    if (rd(lab, X) == S) { x = rd(base, X); y = rd(mate, x); }
-    else { x = rd(tT, X); y = rd(tS, X); }
+    const int v = rd(tS, B);
+    return v < 0 ? -1 : rd(top, v);
   }
   // index of child c along B's cycle from its base child
   MW_FN int cycle_index(int B, int c) {
@@ -297,12 +293,12 @@ struct Solver {
     for (int g = 0; g <= cap && !fail; ++g) {
       const int B = rd(top, v);
       const int t0 = rd(mate, rd(base, B));
-      rotate(B, v);
+      if (B >= cap) rotate(B, v);   // a vertex is its own base
       mate[v] = (int16_t)w;
       if (t0 < 0) return;
       const int Tn = rd(top, t0);
       const int s = rd(tS, Tn), t = rd(tT, Tn);
-      rotate(Tn, t);
+      if (Tn >= cap) rotate(Tn, t);
       mate[t] = (int16_t)s;
       v = s;
       w = t;
@@ -313,41 +309,50 @@ struct Solver {
   // a new blossom from the tight edge (i, j) between two S nodes of one tree
   MW_FN void shrink(int i, int j) {
     const int Bi = rd(top, i), Bj = rd(top, j);
-    int A = -1, g = 0;
-    for (int x = Bi; x >= 0 && g <= cap; x = s_parent(x), ++g) mark[x] = 1;
-    g = 0;
-    for (int x = Bj; x >= 0 && g <= cap; x = s_parent(x), ++g)
-      if (rd(mark, x)) { A = x; break; }
-    g = 0;
-    for (int x = Bi; x >= 0 && g <= cap; x = s_parent(x), ++g) mark[x] = 0;
-    if (A < 0 || nfree <= 0) { fail = true; return; }
+    // The lowest common S node A: both paths are walked at once, each node
+    // marked with its place in its list (stk: Bi's path, from cap Bj's), until
+    // one meets a node the other has passed.  The walk is the only serial part;
+    // the edges of the cycle are then set by one lane per S node.
+    int A = -1, ni = 0, nj = 0, ki = 0, kj = 0;   // lists, and their lengths below A
+    for (int x = Bi, y = Bj; A < 0; ) {
+      if ((x < 0 && y < 0) || ni > cap || nj > cap) { fail = true; return; }
+      const int mx = x >= 0 ? rd(mark, x) : 0, my = y >= 0 ? rd(mark, y) : 0;
+      ki = ni;
+      kj = nj;
+      if (mx) { A = x; kj = mx - 1; break; }
+      if (my) { A = y; ki = my - 1; break; }
+      if (x == y) { A = x; break; }
+      const int px = x >= 0 ? s_parent(x) : -1, py = y >= 0 ? s_parent(y) : -1;
+      if (x >= 0) { stk[ni] = (int16_t)x; mark[x] = (int16_t)++ni; x = px; }
+      if (y >= 0) { stk[cap + nj] = (int16_t)y; mark[y] = (int16_t)++nj; y = py; }
+    }
+    wv.sync();
+    for (int k = wv.lane; k < ni; k += WV::N) mark[stk[k]] = 0;
+    for (int k = wv.lane; k < nj; k += WV::N) mark[stk[cap + k]] = 0;
+    if (nfree <= 0) { fail = true; return; }
     const int b = rd(freel, --nfree);
-    for (int X = Bi, gg = 0; X != A; ++gg) {  // going up from Bi: edge kept at X
-      if (gg > 2 * cap) { fail = true; return; }
-      int x, y;
-      up_edge(X, x, y);
-      const int P = rd(top, y);
-      cnext[X] = (int16_t)P; cprev[P] = (int16_t)X;
-      cex[X] = (int16_t)x; cey[X] = (int16_t)y;
-      X = P;
+    wv.sync();
+    // an S node X, its T node M (x in X, y in M) and the S node P above (tx in
+    // M, ty in P); the edge is kept at the lower node going up from Bi and at
+    // the upper one going down to Bj
+    for (int k = wv.lane; k < ki + kj; k += WV::N) {
+      const bool up = k < ki;
+      const int X = stk[up ? k : cap + k - ki];
+      const int16_t x = base[X], y = mate[x], M = top[y], tx = tT[M], ty = tS[M], P = top[ty];
+      if (up) {
+        cnext[X] = M; cprev[M] = (int16_t)X; cex[X] = x; cey[X] = y;
+        cnext[M] = P; cprev[P] = M; cex[M] = tx; cey[M] = ty;
+      } else {
+        cnext[M] = (int16_t)X; cprev[X] = M; cex[M] = y; cey[M] = x;
+        cnext[P] = M; cprev[M] = P; cex[P] = ty; cey[P] = tx;
+      }
+      par[X] = par[M] = (int16_t)b;
     }
-    for (int X = Bj, gg = 0; X != A; ++gg) {  // going down to Bj: edge kept at the parent
-      if (gg > 2 * cap) { fail = true; return; }
-      int x, y;
-      up_edge(X, x, y);
-      const int P = rd(top, y);
-      cnext[P] = (int16_t)X; cprev[X] = (int16_t)P;
-      cex[P] = (int16_t)y; cey[P] = (int16_t)x;
-      X = P;
-    }
+    wv.sync();
     cnext[Bj] = (int16_t)Bi; cprev[Bi] = (int16_t)Bj;
     cex[Bj] = (int16_t)j; cey[Bj] = (int16_t)i;
-    int c = A, gg = 0;
-    do {
-      par[c] = (int16_t)b;
-      c = rd(cnext, c);
-      if (++gg > 2 * cap) { fail = true; return; }
-    } while (c != A);
+    par[A] = (int16_t)b;
+    tS[b] = (int16_t)rd(tS, A);
     bfirst[b] = (int16_t)A;
     base[b] = (int16_t)rd(base, A);
     z[b - cap] = 0;
@@ -395,7 +400,7 @@ struct Solver {
     const int16_t tree = (int16_t)rd(tid, B);
     lab[c] = T; tS[c] = (int16_t)s; tT[c] = (int16_t)t; tid[c] = tree;
     const bool fwd = (k & 1) != 0;
-    int pos = c;
+    int pos = c, above = s;   // above: the vertex T node pos hangs from
     for (g = 0; pos != first; ++g) {
       if (g > cap) { fail = true; return; }
       const int a = rd(fwd ? cnext : cprev, pos);
@@ -403,11 +408,17 @@ struct Solver {
       int ex, ey;  // ex in a, ey in b
       if (fwd) { ex = rd(cex, a); ey = rd(cey, a); } else { ex = rd(cey, b); ey = rd(cex, b); }
       lab[a] = S;
+      tS[a] = (int16_t)above;
+      above = ex;
       mark[a] = 1;
       lab[b] = T; tS[b] = (int16_t)ex; tT[b] = (int16_t)ey;
       tid[a] = tid[b] = tree;
       pos = b;
     }
+    // the S node below B now hangs from the base child's T node
+    const int below = rd(mate, rd(base, B));
+    if (below < 0) { fail = true; return; }
+    tS[rd(top, below)] = (int16_t)above;
     base[B] = -1;
     lab[B] = FREE;
     freel[nfree++] = (int16_t)B;
@@ -560,7 +571,7 @@ struct Solver {
       wv.sync();
     }
     for (int v = wv.lane; v < nv; v += WV::N)
-      if (mate[v] < 0) { lab[v] = S; tid[v] = (int16_t)v; }
+      if (mate[v] < 0) { lab[v] = S; tid[v] = (int16_t)v; tS[v] = -1; }
     wv.sync();
     {
       const int cnt = collect([&](int y) { (void)y; return true; });
@@ -605,7 +616,7 @@ struct Solver {
     for (int x = wv.lane; x < nn; x += WV::N) lab[x] = FREE;
     wv.sync();
     for (int v = wv.lane; v < nv; v += WV::N)
-      if (mate[v] < 0) { lab[top[v]] = S; tid[top[v]] = (int16_t)v; }
+      if (mate[v] < 0) { lab[top[v]] = S; tid[top[v]] = (int16_t)v; tS[top[v]] = -1; }
     wv.sync();
     const int cnt = collect([&](int y) { (void)y; return true; });
     recompute(cnt);
@@ -698,9 +709,13 @@ struct Solver {
           tid[Bj] = tree;
           const int Bm = rd(top, mb);
           lab[Bm] = S;
+          tS[Bm] = (int16_t)i;
           tid[Bm] = tree;
           wv.sync();
-          const int cnt = collect([&](int y) { return top[y] == Bm; });
+          int cnt = 1;
+          if (Bm >= cap) cnt = collect([&](int y) { return top[y] == Bm; });
+          else if (wv.lane == 0) list[0] = (int16_t)Bm;
+          wv.sync();
           refresh(cnt);
         } else {
           const int ri = rd(tid, rd(top, i)), rj = rd(tid, Bj);
