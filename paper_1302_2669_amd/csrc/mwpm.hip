@@ -140,6 +140,9 @@ size_t mwpm_lds(int cap) {
 // syndromes.
 constexpr int MWPM_FAST_CAP = 64;
 
+// From this capacity on a compute unit's LDS holds at most 6 workgroups.
+constexpr int MWPM_WIDE_CAP = 156;
+
 // Capacity of the launch after it (5 waves per SIMD at most): the problems
 // of the typical syndromes of the larger codes (lit sites of one type up to
 // about 2/5 of them, at least 85); the rare larger syndromes go to a last
@@ -162,12 +165,16 @@ __device__ __forceinline__ int max_vertices(int k) { return (k & 1) ? k + 3 : k 
 // z parts): parity 0 from the start, then parity 1 from parity 0's solution;
 // problem p = 2 type + parity paints plane p.  A launch takes the syndromes
 // whose larger problem needs more than `lo` and at most `hi` vertices, in a
-// state sized for `cap`.  WPE is the register budget in waves per SIMD: 7
-// (72 VGPRs, some spills) for the launch of capacity MWPM_FAST_CAP, whose
-// LDS allows 7; 5 (96 VGPRs, a few spills) for the larger capacities, whose
-// LDS allows at most 5 (at 4 waves, 117 VGPRs and none, the kernel is 15%
-// slower; at 8, 64 VGPRs, the scalar spills make it 28% slower than at 7).
-template <int WPE, int CAP>
+// state sized for `cap`.  WPE is the register budget in waves per SIMD, U the
+// vertices a lane takes at once:
+//   7, 1 (72 VGPRs, some spills) for the launch of capacity MWPM_FAST_CAP, whose
+//     LDS allows 7 waves (at 8, 64 VGPRs, the scalar spills cost 28%);
+//   5, 2 (96 VGPRs) for capacities whose LDS allows 5 to 3, problems of up to
+//     two vertices a lane (8000 syndromes at L = 17, p = 0.15: 3.4 ms with
+//     U = 1, 3.2 with 2, 3.7 with 3);
+//   3, 3 (168 VGPRs) from MWPM_WIDE_CAP, whose LDS holds no more waves (4096 at
+//     L = 25, p = 0.1: 6.1, 5.9 and 5.5 ms).
+template <int WPE, int CAP, int U>
 __global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(WPE)))
 init_mwpm_kernel(const StartArgs a, int cap_arg, int waves, int lo, int hi) {
   // CAP != 0: the capacity as a compile-time constant, so that every solver
@@ -200,7 +207,7 @@ init_mwpm_kernel(const StartArgs a, int cap_arg, int waves, int lo, int hi) {
   if (threadIdx.x < 4) wsum[threadIdx.x] = 0;
   __syncthreads();
   if (wave < waves) {
-    mw::Solver<Wave64> m;
+    mw::Solver<Wave64, U> m;
     m.wv.lane = threadIdx.x & 63;
     m.carve(mw_lds + wave * region, cap);
     for (int t = wave; t < 2; t += waves) {
@@ -282,28 +289,22 @@ Overlap* overlap_entry(bool create) {
   return &o;
 }
 
+constexpr int kMaxTiers = 5;
+
 hipError_t launch_tier(const StartArgs& a, int cap, int lo, int hi, hipStream_t s) {
   const size_t lds = mwpm_lds(cap);
   // the capacity compiled in only where the launch's is exactly that one
   // (smaller codes have smaller single-tier capacities)
-  const bool fast = cap <= MWPM_FAST_CAP, fixed = cap == MWPM_FAST_CAP;
-  const void* fn = fixed  ? reinterpret_cast<const void*>(init_mwpm_kernel<7, MWPM_FAST_CAP>)
-                   : fast ? reinterpret_cast<const void*>(init_mwpm_kernel<7, 0>)
-                          : reinterpret_cast<const void*>(init_mwpm_kernel<5, 0>);
+  auto* fn = cap == MWPM_FAST_CAP  ? init_mwpm_kernel<7, MWPM_FAST_CAP, 1>
+             : cap < MWPM_FAST_CAP ? init_mwpm_kernel<7, 0, 1>
+             : cap < MWPM_WIDE_CAP ? init_mwpm_kernel<5, 0, 2>
+                                   : init_mwpm_kernel<3, 0, 3>;
   if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)lds);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  if (fixed)
-    hipLaunchKernelGGL((init_mwpm_kernel<7, MWPM_FAST_CAP>), dim3((unsigned)a.n), dim3(128), lds,
-                       s, a, cap, mwpm_waves(cap), lo, hi);
-  else if (fast)
-    hipLaunchKernelGGL((init_mwpm_kernel<7, 0>), dim3((unsigned)a.n), dim3(128), lds, s, a, cap,
-                       mwpm_waves(cap), lo, hi);
-  else
-    hipLaunchKernelGGL((init_mwpm_kernel<5, 0>), dim3((unsigned)a.n), dim3(128), lds, s, a, cap,
-                       mwpm_waves(cap), lo, hi);
+  hipLaunchKernelGGL(fn, dim3((unsigned)a.n), dim3(128), lds, s, a, cap, mwpm_waves(cap), lo, hi);
   return hipGetLastError();
 }
 
@@ -319,20 +320,30 @@ hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create) 
   const int L = a.items ? a.max_L : a.L;
   if (L < MCMC_L_MIN || L > MCMC_L_MAX) return hipErrorInvalidValue;
   // capacity tiers: the 7-wave launch, the typical syndromes of the larger
-  // codes, a fully lit code
+  // codes, a fully lit code.  Batches of many rounds of the middle one (its LDS
+  // holds 3 workgroups per compute unit at L = 25) also take the capacities
+  // between at which 10 and 6 fit: 4096 syndromes at L = 25 need 40 to 190
+  // vertices depending on p, and each further launch only costs its workgroups'
+  // look at the syndrome (18 us) and its own tail, which a small batch feels.
   const int full = mw::capacity(L), mid = mwpm_small_capacity(L);
-  int caps[3], nt = 0;
+  int caps[kMaxTiers], nt = 0;
   if (mid > MWPM_FAST_CAP) caps[nt++] = MWPM_FAST_CAP;
+  if (a.n >= 3072)
+    for (int c : {88, MWPM_WIDE_CAP})
+      if (2 * mid >= 3 * c) caps[nt++] = c;
   caps[nt++] = mid;
   if (full > mid) caps[nt++] = full;
-  int lo[3], hi[3];
+  int lo[kMaxTiers], hi[kMaxTiers];
   for (int t = 0; t < nt; ++t) {
     lo[t] = t ? caps[t - 1] : 0;
     hi[t] = t + 1 < nt ? caps[t] : 0x7fffffff;
   }
   if (nt == 1) return launch_tier(a, caps[0], lo[0], hi[0], s);
-  // the later tiers on the side stream, launched first so that their few long
-  // workgroups start at once; without a side stream, in order on s
+  // the middle tier and then the full code's on the side stream, launched first
+  // so that their few long workgroups start at once (the full code's last: its
+  // workgroups' look at every syndrome holds the most LDS; first it made 8000
+  // syndromes at L = 15 take 1.16 ms instead of 0.92); the smaller ones, largest
+  // first, on s; without a side stream, in order on s
   std::lock_guard<std::mutex> lock(g_overlap_mu);
   hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cap_status) != hipSuccess) cap_status = hipStreamCaptureStatusNone;
@@ -341,9 +352,11 @@ hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create) 
   if (o) {
     if ((e = hipEventRecord(o->fork, s)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(o->side, o->fork, 0)) != hipSuccess) return e;
-    for (int t = 1; t < nt; ++t)
+    const int first_aside = full > mid ? nt - 2 : nt - 1;
+    for (int t = first_aside; t < nt; ++t)
       if ((e = launch_tier(a, caps[t], lo[t], hi[t], o->side)) != hipSuccess) return e;
-    if ((e = launch_tier(a, caps[0], lo[0], hi[0], s)) != hipSuccess) return e;
+    for (int t = first_aside - 1; t >= 0; --t)
+      if ((e = launch_tier(a, caps[t], lo[t], hi[t], s)) != hipSuccess) return e;
     if ((e = hipEventRecord(o->join, o->side)) != hipSuccess) return e;
     return hipStreamWaitEvent(s, o->join, 0);
   }

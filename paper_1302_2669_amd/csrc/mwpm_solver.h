@@ -110,7 +110,12 @@ MW_HD size_t region_bytes(int cap) {
   return (size_t)cap * 83;
 }
 
-template <class WV>
+// U: vertices a lane takes at once in the passes over them.  A pass is a short
+// chain of dependent LDS reads; with U > 1 the reads of U vertices (out-of-range
+// ones read vertex 0 and change nothing) are in flight together, which is what
+// a problem of more than N vertices waits for.  A problem that fits one lane
+// per vertex takes U = 1.
+template <class WV, int U = 1>
 struct Solver {
   WV wv;
   int64_t *u, *best, *z;
@@ -170,18 +175,21 @@ struct Solver {
     const uint32_t m = vn < vf ? vn : vf;
     return man < m ? man : m;
   }
-  MW_FN int64_t weight(int a, int b) const {
-    const uint32_t pa = pos[a], pb = pos[b];
+  // weight of the pair at places pa, pb with keys ka, kb
+  MW_FN int64_t pair_weight(uint32_t pa, uint64_t ka, uint32_t pb, uint64_t kb) const {
+    const uint64_t t = (ka * kb) >> 21;
+    int64_t w = (int64_t)(((uint64_t)distance(pa, pb) << 54) + 4 * t);
     if (dummy && (pa == PLACE_DUMMY || pb == PLACE_DUMMY))
-      return (pa == place_far() || pb == place_far()) ? 0 : W_NEVER;
-    const uint64_t t = (key[a] * key[b]) >> 21;
-    return (int64_t)(((uint64_t)distance(pa, pb) << 54) + 4 * t);
+      w = (pa == place_far() || pb == place_far()) ? 0 : W_NEVER;
+    return w;
   }
-  MW_FN int64_t slack(int a, int b) const {
-    MW_COUNT(slack);
-    return weight(a, b) - u[a] - u[b];
+  MW_FN int64_t weight(int a, int b) const { return pair_weight(pos[a], key[a], pos[b], key[b]); }
+  // vertices v0 + lane + k N, k < U: index (0 where past the end) and validity
+  MW_FN int vertex(int v0, int k, bool& ok) const {
+    const int v = v0 + k * WV::N + wv.lane;
+    ok = v < nv;
+    return ok ? v : 0;
   }
-
   // ---------------------------------------------------------------- structure
   // the child of node B that holds vertex v
   MW_FN int child_of(int B, int v) {
@@ -215,11 +223,19 @@ struct Solver {
   template <class P>
   MW_FN int collect(P pred) {
     int cnt = 0;
-    for (int y0 = 0; y0 < nv; y0 += WV::N) {
-      const int y = y0 + wv.lane;
-      const bool take = y < nv && pred(y);
-      const int slot = wv.compact(take, cnt);
-      if (take) list[slot] = (int16_t)y;
+    for (int y0 = 0; y0 < nv; y0 += U * WV::N) {
+      bool take[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        bool ok;
+        const int y = vertex(y0, k, ok);
+        take[k] = ok & pred(y);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int slot = wv.compact(take[k], cnt);
+        if (take[k]) list[slot] = (int16_t)(y0 + k * WV::N + wv.lane);
+      }
     }
     wv.sync();
     return cnt;
@@ -234,17 +250,39 @@ struct Solver {
   MW_FN void refresh(int cnt) {
     for (int k = 0; k < cnt; ++k) MW_COUNT(refresh_vertex);
     if (cnt == 0) return;
-    for (int y = wv.lane; y < nv; y += WV::N) {  // in list order, as one offer after another
-      const int ty = top[y];
-      int64_t b = best[y];
-      int bs = -1;
-      for (int k = 0; k < cnt; ++k) {
-        const int x = list[k];
-        if (top[x] == ty) continue;
-        const int64_t sl = slack(x, y);
-        if (sl < b) { b = sl; bs = x; }
+    for (int y0 = 0; y0 < nv; y0 += U * WV::N) {
+      int y[U], ty[U], bs[U];
+      uint32_t py[U];
+      uint64_t ky[U];
+      int64_t uy[U], b[U];
+      bool ok[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        y[i] = vertex(y0, i, ok[i]);
+        ty[i] = top[y[i]];
+        py[i] = pos[y[i]];
+        ky[i] = key[y[i]];
+        uy[i] = u[y[i]];
+        b[i] = best[y[i]];
+        bs[i] = -1;
       }
-      if (bs >= 0) { best[y] = b; bestS[y] = (int16_t)bs; }
+      for (int k = 0; k < cnt; ++k) {  // in list order, as one offer after another
+        const int x = list[k], tx = top[x];
+        const uint32_t px = pos[x];
+        const uint64_t kx = key[x];
+        const int64_t ux = u[x];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          MW_COUNT(slack);
+          const int64_t sl = pair_weight(px, kx, py[i], ky[i]) - ux - uy[i];
+          const bool less = (tx != ty[i]) & (sl < b[i]);
+          b[i] = less ? sl : b[i];
+          bs[i] = less ? x : bs[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (ok[i] & (bs[i] >= 0)) { best[y[i]] = b[i]; bestS[y[i]] = (int16_t)bs[i]; }
     }
     wv.sync();
   }
@@ -365,7 +403,7 @@ struct Solver {
     // vertices outside their node).
     const int cnt = collect([&](int y) {
       const int ty = top[y];
-      return par[ty] == b && lab[ty] == T;
+      return (par[ty] == b) & (lab[ty] == T);
     });
     for (int v = wv.lane; v < nv; v += WV::N)
       if (par[top[v]] == b) top[v] = (int16_t)b;
@@ -376,7 +414,7 @@ struct Solver {
     // inside b.
     const int cnt2 = collect([&](int y) {
       const int s = bestS[y];
-      return top[y] == b && s >= 0 && top[s] == b;
+      return (top[y] == b) & (s >= 0) & (top[s < 0 ? 0 : s] == b);
     });
     recompute(cnt2);
   }
@@ -449,11 +487,19 @@ struct Solver {
     for (int k = 0; k < cnt; ++k) MW_COUNT(recompute_vertex);
     // the S vertices, in ascending order
     int ns = 0;
-    for (int x0 = 0; x0 < nv; x0 += WV::N) {
-      const int x = x0 + wv.lane;
-      const bool take = x < nv && lab[top[x]] == S;
-      const int slot = wv.compact(take, ns);
-      if (take) slist[slot] = (int16_t)x;
+    for (int x0 = 0; x0 < nv; x0 += U * WV::N) {
+      bool take[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        bool ok;
+        const int x = vertex(x0, k, ok);
+        take[k] = ok & (lab[top[x]] == S);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int slot = wv.compact(take[k], ns);
+        if (take[k]) slist[slot] = (int16_t)(x0 + k * WV::N + wv.lane);
+      }
     }
     wv.sync();
     // Each vertex takes an aligned group of 2^lg lanes, lane r of the group
@@ -475,11 +521,31 @@ struct Solver {
       if (k < cnt) {
         y = list[k];
         const int ty = top[y];
-        for (int m = r; m < ns; m += P) {  // ascending x: ties keep the smaller
-          const int x = slist[m];
-          if (top[x] == ty) continue;
-          const int64_t sl = slack(x, y);
-          if (sl < b) { b = sl; bs = x; }
+        const uint32_t py = pos[y];
+        const uint64_t ky = key[y];
+        const int64_t uy = u[y];
+        for (int m = r; m < ns; m += U * P) {  // ascending x: ties keep the smaller
+          int x[U], tx[U];
+          uint32_t px[U];
+          uint64_t kx[U];
+          int64_t ux[U];
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            const int at = m + i * P;
+            x[i] = slist[at < ns ? at : m];   // past the end: the first again, no smaller
+            tx[i] = top[x[i]];
+            px[i] = pos[x[i]];
+            kx[i] = key[x[i]];
+            ux[i] = u[x[i]];
+          }
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            MW_COUNT(slack);
+            const int64_t sl = pair_weight(px[i], kx[i], py, ky) - ux[i] - uy;
+            const bool less = (tx[i] != ty) & (sl < b);
+            b = less ? sl : b;
+            bs = less ? x[i] : bs;
+          }
         }
       }
       wv.seg_argmin(b, bs, lg);
@@ -518,16 +584,37 @@ struct Solver {
     // start: u_v = half the lightest pair at v (W is a multiple of 4, so every
     // u is even and every S vertex keeps the parity of the roots); mutual
     // nearest neighbours are tight and matched
-    for (int v = wv.lane; v < nv; v += WV::N) {
-      int64_t b = INF;
-      int bs = -1;
-      for (int x = 0; x < nv; ++x) {
-        if (x == v) continue;
-        const int64_t w = weight(x, v);
-        if (w < b) { b = w; bs = x; }
+    for (int v0 = 0; v0 < nv; v0 += U * WV::N) {
+      int v[U], bs[U];
+      uint32_t pv[U];
+      uint64_t kv[U];
+      int64_t b[U];
+      bool ok[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        v[i] = vertex(v0, i, ok[i]);
+        pv[i] = pos[v[i]];
+        kv[i] = key[v[i]];
+        b[i] = INF;
+        bs[i] = -1;
       }
-      u[v] = b >> 1;
-      bestS[v] = (int16_t)bs;
+      for (int x = 0; x < nv; ++x) {
+        const uint32_t px = pos[x];
+        const uint64_t kx = key[x];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          const int64_t w = pair_weight(px, kx, pv[i], kv[i]);
+          const bool less = (x != v[i]) & (w < b[i]);
+          b[i] = less ? w : b[i];
+          bs[i] = less ? x : bs[i];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < U; ++i)
+        if (ok[i]) {
+          u[v[i]] = b[i] >> 1;
+          bestS[v[i]] = (int16_t)bs[i];
+        }
     }
     wv.sync();
     int matched = 0;
@@ -554,10 +641,21 @@ struct Solver {
       if (rd(mate, v) >= 0) continue;
       int64_t key = INF;
       int idx = 0x7fff;
-      for (int w = wv.lane; w < nv; w += WV::N) {
-        if (w == v) continue;
-        const int64_t k = (slack(v, w) << 1) | (mate[w] >= 0 ? 1 : 0);
-        if (k < key) { key = k; idx = w; }
+      const uint32_t pv = pos[v];
+      const uint64_t kv = this->key[v];
+      const int64_t uv = u[v];
+      for (int w0 = 0; w0 < nv; w0 += U * WV::N) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          MW_COUNT(slack);
+          bool ok;
+          const int w = vertex(w0, i, ok);
+          const int64_t sl = pair_weight(pv, kv, pos[w], this->key[w]) - uv - u[w];
+          const int64_t k = 2 * sl + (mate[w] >= 0 ? 1 : 0);
+          const bool less = ok & (w != v) & (k < key);
+          key = less ? k : key;
+          idx = less ? w : idx;
+        }
       }
       wv.argmin(key, idx);
       wv.sync();
@@ -650,16 +748,26 @@ struct Solver {
     key = INF;
     idx = 0x7fff;
     bool odd = false;
-    for (int j = wv.lane; j < nv; j += WV::N) {
-      const int16_t l = lab[top[j]];
-      const int64_t b = best[j];
-      if (b >= INF || l == T) continue;
-      int64_t kk = b;
-      if (l == S) {
-        odd |= (b & 1) != 0;  // the slack between two S vertices is even
-        kk = b >> 1;
+    for (int j0 = 0; j0 < nv; j0 += U * WV::N) {
+      int j[U];
+      int16_t l[U];
+      int64_t b[U];
+      bool ok[U];
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        j[i] = vertex(j0, i, ok[i]);
+        l[i] = lab[top[j[i]]];
+        b[i] = best[j[i]];
       }
-      if (kk < key || (kk == key && j < idx)) { key = kk; idx = j; }
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        const bool cand = ok[i] & (b[i] < INF) & (l[i] != T), s = l[i] == S;
+        odd |= cand & s & ((b[i] & 1) != 0);  // the slack between two S vertices is even
+        const int64_t kk = s ? b[i] >> 1 : b[i];
+        const bool less = cand & (kk < key);  // ascending j: ties keep the lowest
+        key = less ? kk : key;
+        idx = less ? j[i] : idx;
+      }
     }
     if (nfree < cap / 2) {  // blossoms exist (indices >= cap)
       for (int b = cap + wv.lane; b < nn; b += WV::N) {
@@ -735,7 +843,8 @@ struct Solver {
             // held by one of them: the others keep theirs, whatever their
             // own label becomes.
             const int cnt = collect([&](int y) {
-              return bestS[y] >= 0 && mark[top[bestS[y]]] != 0;
+              const int s = bestS[y];
+              return (s >= 0) & (mark[top[s < 0 ? 0 : s]] != 0);
             });
             augment_path(i, j);
             augment_path(j, i);
@@ -756,16 +865,27 @@ struct Solver {
         const int64_t delta = key;
         if (delta >= INF) { fail = true; break; }
         MW_COUNT(dual);
-        for (int v = wv.lane; v < nv; v += WV::N) {
-          const int16_t l = lab[top[v]];
-          const int64_t b = best[v];
-          if (l == S) {
-            u[v] += delta;
-            if (b < INF) best[v] = b - 2 * delta;
-          } else if (l == T) {
-            u[v] -= delta;
-          } else if (b < INF) {
-            best[v] = b - delta;
+        for (int v0 = 0; v0 < nv; v0 += U * WV::N) {
+          int v[U];
+          int16_t l[U];
+          int64_t b[U], uv[U];
+          bool ok[U];
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            v[i] = vertex(v0, i, ok[i]);
+            l[i] = lab[top[v[i]]];
+            b[i] = best[v[i]];
+            uv[i] = u[v[i]];
+          }
+#pragma unroll
+          for (int i = 0; i < U; ++i) {
+            // S: u + delta, best - 2 delta; T: u - delta; free: best - delta
+            const int64_t du = l[i] == S ? delta : (l[i] == T ? -delta : 0);
+            const int64_t db = (b[i] >= INF) | (l[i] == T) ? 0 : (l[i] == S ? 2 * delta : delta);
+            if (ok[i]) {
+              u[v[i]] = uv[i] + du;
+              best[v[i]] = b[i] - db;
+            }
           }
         }
         if (nfree < cap / 2) {

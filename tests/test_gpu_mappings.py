@@ -139,3 +139,17 @@ def test_spacetime_lanes(L, T, n, chains):
     for k in ("sum_n", "sum_m", "accepts", "chosen", "correction"):
         assert np.array_equal(g[k], o[k]), k
     np.testing.assert_allclose(g["class_prob"], o["class_prob"], rtol=1e-12, atol=0)
+
+
+def test_matching_tiers_of_large_batches():
+    # from 3072 syndromes the larger codes use capacities between the tiers: the
+    # same starts as in small batches, syndromes on both sides of each capacity
+    for L in (20, 25):
+        n = 3072
+        syn = torch.cat([mc.sample_errors(L, p, 7, n // 6, id_base=int(1000 * p))[0]
+                         for p in (0.03, 0.05, 0.07, 0.10, 0.13, 0.18)])
+        reps = mc.init_representatives(syn, L, mc.MCMC_INIT_MWPM)
+        for lo in range(0, n, 512):
+            small = mc.init_representatives(syn[lo:lo + 512], L, mc.MCMC_INIT_MWPM)
+            torch.cuda.synchronize()
+            assert torch.equal(reps[lo:lo + 512], small), (L, lo)
