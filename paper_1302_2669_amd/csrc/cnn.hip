@@ -10,7 +10,8 @@
 // fp32 accumulation): forward M = pixels, N = 32 output channels,
 // K = 9 taps x input channels; backward-data the same with the taps mirrored
 // and the weight roles transposed; weight gradients M = 32, N = taps x input
-// channels, K = pixels, split over pixel chunks and reduced in a fixed order.
+// channels, K = pixels (v_mfma_f32_32x32x16_bf16), split over samples and
+// reduced in a fixed order.
 // Lane layout of the 16x16x32 MFMA: lane l holds A[l%16][8(l/16)..+7],
 // B[8(l/16)..+7][l%16] and D[4(l/16)+i][l%16], i = 0..3.
 #include <hip/hip_runtime.h>
@@ -26,7 +27,9 @@ namespace {
 
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int CH = 32;
 
@@ -43,29 +46,12 @@ __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ int tap_dy(int t) { return t / 3 - 1; }
 __device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
-
-// ---- input planes ----------------------------------------------------------
-// x0[pixel][8]: 0 lit star (i, j) at (i, j), 1 lit plaquette (i, j) at (i, j),
-// 2 the sample's p, 3..7 zero.
-__global__ void encode_kernel(int L, int64_t B, const uint8_t* __restrict__ syn,
-                              const float* __restrict__ p, bf16* __restrict__ x0) {
-  const int64_t pix = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t P = B * L * L;
-  if (pix >= P) return;
-  const int64_t b = pix / (L * L);
-  const int r = (int)(pix - b * L * L), y = r / L, x = r % L;
-  const uint8_t* s = syn + b * (int64_t)(2 * L * (L - 1));
-  const int ns = L * (L - 1);
-  const float star = (y < L - 1 && s[y * L + x]) ? 1.0f : 0.0f;
-  const float plaq = (x < L - 1 && s[ns + y * (L - 1) + x]) ? 1.0f : 0.0f;
-  bf16* o = x0 + pix * 8;
-  o[0] = (bf16)star;
-  o[1] = (bf16)plaq;
-  o[2] = (bf16)p[b];
-  for (int c = 3; c < 8; ++c) o[c] = (bf16)0.0f;
-}
 
 // ---- parameter casts -------------------------------------------------------
 // wb1 [32][96] (k = tap*8 + ci, ci < 3), wb2/wb3 [32][288] (k = tap*32 + ci),
@@ -92,313 +78,51 @@ __global__ void cast_kernel(int L, const float* __restrict__ prm, const CnnOffse
   }
 }
 
-// ---- convolution as implicit GEMM -------------------------------------------
-// Forward (MIRROR = false): out[p][n] = relu(sum_{tap,ci} in[p + tap][ci] *
-// w[n][tap*CIN + ci] + bias[n]).  Backward data (MIRROR = true): out[p][n] =
-// (sum_{tap,c} in[p - tap][c] * w[n][tap*CIN + c]) * (mask[p][n] > 0).
-// One wave computes 16 pixels x 32 channels; 4 waves per workgroup.
-template <int CIN, bool MIRROR>
-__global__ void __launch_bounds__(256) conv_kernel(int L, int64_t P, const bf16* __restrict__ in,
-                                                   const bf16* __restrict__ w,
-                                                   const float* __restrict__ bias,
-                                                   const bf16* __restrict__ mask,
-                                                   bf16* __restrict__ out) {
-  constexpr int KP = (9 * CIN + 31) / 32 * 32;
-  constexpr int CHUNKS = CIN / 8;
-  const int lane = threadIdx.x & 63;
-  const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t pm = tile * 16 + (lane & 15);
-  const int LL = L * L;
-  int64_t b = 0;
-  int y = 0, x = 0;
-  if (pm < P) {
-    b = pm / LL;
-    const int r = (int)(pm - b * LL);
-    y = r / L;
-    x = r % L;
-  }
-  f32x4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
-  const int grp = lane >> 4;
-  const int n = lane & 15;
-#pragma unroll
-  for (int s = 0; s < KP / 32; ++s) {
-    const int g = 4 * s + grp;
-    const int tap = g / CHUNKS, cc = g % CHUNKS;
-    bf16x8 a = zero8();
-    if (tap < 9 && pm < P) {
-      int dy = tap_dy(tap), dx = tap_dx(tap);
-      if (MIRROR) { dy = -dy; dx = -dx; }
-      const int yy = y + dy, xx = x + dx;
-      if (yy >= 0 && yy < L && xx >= 0 && xx < L)
-        a = load8(in + ((b * LL + yy * L + xx) * CIN + cc * 8));
-    }
-    const bf16x8 w0 = load8(w + (int64_t)n * KP + s * 32 + 8 * grp);
-    const bf16x8 w1 = load8(w + (int64_t)(n + 16) * KP + s * 32 + 8 * grp);
-    // weights as the A operand: D[channel][pixel], so lane (n, grp) ends
-    // with channels 4 grp .. 4 grp + 3 (and + 16) of pixel n
-    acc0 = mfma(w0, a, acc0);
-    acc1 = mfma(w1, a, acc1);
-  }
-  if (pm >= P) return;
-  bf16x8 o;   // channels 4 grp + i at o[i], 16 + 4 grp + i at o[4 + i]
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c0 = 4 * grp + i, c1 = 16 + 4 * grp + i;
-    float v0 = acc0[i], v1 = acc1[i];
-    if (!MIRROR) {
-      v0 = fmaxf(v0 + bias[c0], 0.0f);
-      v1 = fmaxf(v1 + bias[c1], 0.0f);
-    } else {
-      v0 = (float)mask[pm * CH + c0] > 0.0f ? v0 : 0.0f;
-      v1 = (float)mask[pm * CH + c1] > 0.0f ? v1 : 0.0f;
-    }
-    o[i] = (bf16)v0;
-    o[4 + i] = (bf16)v1;
-  }
-  const uint4 ov = __builtin_bit_cast(uint4, o);
-  *reinterpret_cast<uint2*>(out + pm * CH + 4 * grp) = make_uint2(ov.x, ov.y);
-  *reinterpret_cast<uint2*>(out + pm * CH + 16 + 4 * grp) = make_uint2(ov.z, ov.w);
-}
-
-// ---- weight gradients ------------------------------------------------------
-// Workgroup w handles samples [w*G, (w+1)*G) in order and writes
-// part[w][co][c] = sum over its samples and pixels of dpre[p][co] *
-// in[p + tap(c)][ci(c)] (c = tap*CIN + ci < 9*CIN; columns up to KP are zero)
-// and partb[w][co] = sum of dpre[p][co].  Each sample is staged in LDS
-// channel-major on its image padded by one zero pixel on every side
-// ((L+2)^2 positions, rounded up to a multiple of 32): the MFMA k index runs
-// over padded positions, so a tap is a constant offset of dy*(L+2)+dx and no
-// bounds test is needed (padding positions hold zeros in both operands).
-constexpr int WG_THREADS = 256;
-
-struct WgradGeom {
-  int PW, PS, KPAD, DSTR, OFF, ISTR;
-};
-__host__ __device__ inline WgradGeom wgrad_geom(int L) {
-  WgradGeom g;
-  g.PW = L + 2;
-  g.PS = g.PW * g.PW;
-  g.KPAD = (g.PS + 31) / 32 * 32;
-  g.DSTR = g.KPAD + 8;                       // 16-byte rows, 16 lanes on disjoint banks
-  g.OFF = (g.PW + 1 + 7) / 8 * 8;            // room for the most negative tap offset
-  int istr = g.OFF + g.KPAD + g.PW + 1 + 1;
-  istr = (istr + 1) / 2 * 2;
-  if (((istr / 2) & 1) == 0) istr += 2;      // odd word stride: 16 lanes, 16 banks
-  g.ISTR = istr;
-  return g;
-}
-template <int CIN>
-inline size_t wgrad_lds_bytes(int L) {
-  const WgradGeom g = wgrad_geom(L);
-  return ((size_t)CH * g.DSTR + (size_t)CIN * g.ISTR) * 2;
-}
-
-template <int CIN>
-__global__ void __launch_bounds__(WG_THREADS) conv_wgrad_kernel(int L, int64_t B, int G,
-                                                                const bf16* __restrict__ dpre,
-                                                                const bf16* __restrict__ in,
-                                                                float* __restrict__ part,
-                                                                float* __restrict__ partb) {
-  constexpr int KP = (9 * CIN + 31) / 32 * 32;
-  constexpr int NT = KP / 16;                 // column tiles
-  constexpr int TILES = 2 * NT;               // x 2 row tiles of 16 output channels
-  constexpr int TPW = (TILES + 3) / 4;        // tiles per wave
-  extern __shared__ __align__(16) unsigned char wsm[];
-  const WgradGeom gm = wgrad_geom(L);
-  bf16* dT = reinterpret_cast<bf16*>(wsm);            // [CH][DSTR]
-  bf16* iT = dT + CH * gm.DSTR;                       // [CIN][ISTR]
-  __shared__ float runs[8][CH];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = lane >> 4, n = lane & 15;
-  const int LL = L * L;
-  const int64_t s0 = (int64_t)blockIdx.x * G;
-  const int64_t s1 = s0 + G < B ? s0 + G : B;
-  f32x4 acc[TPW];
-#pragma unroll
-  for (int u = 0; u < TPW; ++u) acc[u] = f32x4{0, 0, 0, 0};
-  float bsum = 0.0f;
-  const int nwords = (CH * gm.DSTR + CIN * gm.ISTR) / 2;
-  for (int64_t smp = s0; smp < s1; ++smp) {
-    __syncthreads();
-    for (int i = tid; i < nwords; i += WG_THREADS) reinterpret_cast<uint32_t*>(wsm)[i] = 0u;
-    __syncthreads();
-    const int64_t pix0 = smp * LL;
-    for (int i = tid; i < LL * CH; i += WG_THREADS) {
-      const int r = i / CH, co = i % CH;
-      const int q = (r / L + 1) * gm.PW + (r % L + 1);
-      dT[co * gm.DSTR + q] = dpre[(pix0 + r) * CH + co];
-    }
-    for (int i = tid; i < LL * CIN; i += WG_THREADS) {
-      const int r = i / CIN, ci = i % CIN;
-      const int q = (r / L + 1) * gm.PW + (r % L + 1);
-      iT[ci * gm.ISTR + gm.OFF + q] = in[(pix0 + r) * CIN + ci];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < TPW; ++u) {
-      const int t = wave + 4 * u;
-      if (t >= TILES) continue;
-      const int mt = t / NT, nt = t % NT;
-      const int co = mt * 16 + n;
-      const int c = nt * 16 + n;
-      const bool col_ok = c < 9 * CIN;
-      const int tap = col_ok ? c / CIN : 4, ci = col_ok ? c % CIN : 0;
-      const int shift = tap_dy(tap) * gm.PW + tap_dx(tap);
-      const bf16* arow = dT + co * gm.DSTR + 8 * grp;
-      const bf16* brow = iT + ci * gm.ISTR + gm.OFF + shift + 8 * grp;
-      for (int k = 0; k < gm.KPAD; k += 32) {
-        const bf16x8 a = lds8(arow + k);
-        bf16x8 bb;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) bb[j] = brow[k + j];
-        if (!col_ok) bb = zero8();
-        acc[u] = mfma(a, bb, acc[u]);
-      }
-    }
-    // bias: 8 runs of the padded row per channel, in run order
-    {
-      const int co = tid & 31, run = tid >> 5;
-      const int per = gm.KPAD / 8;
-      float s = 0.0f;
-      for (int j = 0; j < per; ++j) s += (float)dT[co * gm.DSTR + run * per + j];
-      runs[run][co] = s;
-    }
-    __syncthreads();
-    if (tid < CH) {
-      float s = 0.0f;
-      for (int r = 0; r < 8; ++r) s += runs[r][tid];
-      bsum += s;
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < TPW; ++u) {
-    const int t = wave + 4 * u;
-    if (t >= TILES) continue;
-    const int mt = t / NT, nt = t % NT;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      part[((int64_t)blockIdx.x * CH + mt * 16 + 4 * grp + i) * KP + nt * 16 + n] = acc[u][i];
-  }
-  if (tid < CH) partb[(int64_t)blockIdx.x * CH + tid] = bsum;
-}
-
-// Samples per weight-gradient workgroup: enough workgroups to fill the chip
-// twice, at most one sample each for small batches.
-inline int wgrad_group(int64_t B) {
-  const int64_t target = 512;
-  return (int)(B <= target ? 1 : (B + target - 1) / target);
-}
-
-// grad W[co][tap][ci] (ci < cin_real) and grad b[co] from the per-workgroup
-// partials: a workgroup takes 16 outputs (index i: the W entries, then the
-// 32 biases) and 16 row segments; segment g adds rows g, g+16, ... in order,
-// and the 16 segment sums are added in segment order.
-constexpr int RED_OUT = 16, RED_SEG = 16;
-
-template <int CIN>
-__global__ void __launch_bounds__(RED_OUT * RED_SEG) wgrad_reduce_kernel(
-    int64_t rows, int cin_real, const float* __restrict__ part, const float* __restrict__ partb,
-    float* __restrict__ gW, float* __restrict__ gb) {
-  constexpr int KP = (9 * CIN + 31) / 32 * 32;
-  __shared__ float seg_sum[RED_SEG][RED_OUT];
-  const int o = threadIdx.x % RED_OUT, g = threadIdx.x / RED_OUT;
-  const int nW = CH * 9 * cin_real;
-  const int i = blockIdx.x * RED_OUT + o;
-  float acc = 0.0f;
-  if (i < nW) {
-    const int co = i / (9 * cin_real), rem = i % (9 * cin_real);
-    const int c = (rem / cin_real) * CIN + rem % cin_real;
-    for (int64_t k = g; k < rows; k += RED_SEG) acc += part[(k * CH + co) * KP + c];
-  } else if (i < nW + CH) {
-    for (int64_t k = g; k < rows; k += RED_SEG) acc += partb[k * CH + (i - nW)];
-  }
-  seg_sum[g][o] = acc;
-  __syncthreads();
-  if (g == 0 && i < nW + CH) {
-    float t = seg_sum[0][o];
-    for (int j = 1; j < RED_SEG; ++j) t += seg_sum[j][o];
-    if (i < nW) gW[i] = t;
-    else gb[i - nW] = t;
-  }
-}
-
-// ---- head ----------------------------------------------------------------
-// logits[b][o] = sum_f a3[b][f] * whb[o][f] + bh[o], o < 7; 16 samples per
-// wave.  The sum over the L*L pixel steps (32 features each) runs as 8
-// interleaved MFMA chains, chain j taking steps j, j+8, ..., added in chain
-// order at the end; the fused inference kernel uses the same order, so both
-// give the same bits.
-constexpr int HEAD_CHAINS = 8;
-
-// One workgroup of HEAD_CHAINS waves per 16 samples: wave j runs chain j and
-// the chains are added in order through LDS.
-__global__ void __launch_bounds__(64 * HEAD_CHAINS) head_fwd_kernel(
-    int L, int64_t B, const bf16* __restrict__ a3, const bf16* __restrict__ whb,
-    const float* __restrict__ bh, float* __restrict__ logits) {
-  __shared__ float part[HEAD_CHAINS][16][16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, n = lane & 15;
-  const int64_t tile = blockIdx.x;
-  const int64_t bm = tile * 16 + n;
-  const int LL = L * L;
-  const int64_t kh = (int64_t)LL * CH;
-  f32x4 acc = {0, 0, 0, 0};
-  for (int st0 = wave; st0 < LL; st0 += 8 * HEAD_CHAINS) {
-    bf16x8 aq[8], bq[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int st = st0 + j * HEAD_CHAINS;
-      aq[j] = (st < LL && bm < B) ? load8(a3 + bm * kh + st * 32 + 8 * grp) : zero8();
-      bq[j] = (st < LL && n < 7) ? load8(whb + (int64_t)n * kh + st * 32 + 8 * grp) : zero8();
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (st0 + j * HEAD_CHAINS < LL) acc = mfma(aq[j], bq[j], acc);
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) part[wave][4 * grp + i][n] = acc[i];
-  __syncthreads();
-  if (threadIdx.x < 16 * 8) {
-    const int row = threadIdx.x >> 3, o = threadIdx.x & 7;
-    const int64_t bo = tile * 16 + row;
-    if (bo < B && o < 7) {
-      float t = part[0][row][o];
-      for (int j = 1; j < HEAD_CHAINS; ++j) t = t + part[j][row][o];
-      logits[bo * 8 + o] = t + bh[o];
-    }
-  }
-}
-
-// ---- fused inference -----------------------------------------------------
+// ---- forward ---------------------------------------------------------------
 // One workgroup (8 waves) runs S samples through the three convolutions and
-// the head with every activation in LDS; only the syndromes, rates, weights
-// and logits touch global memory.  Same operations in the same order as the
-// layered kernels above (conv: per-pixel tap/chunk k-steps on MFMA, bias,
-// ReLU, bf16; head: 8 interleaved chains), so the logits are identical.
-constexpr int INFER_THREADS = 512;
-constexpr int INFER_WAVES = INFER_THREADS / 64;
-static_assert(INFER_WAVES == HEAD_CHAINS, "both head paths add the same chains in the same order");
+// the head with every activation in LDS; inference touches global memory only
+// for the syndromes, rates, weights and logits, and a training forward
+// (STORE) also writes the planes and the three activations out for the
+// backward pass.  logits[b][o] = sum_f a3[b][f] * whb[o][f] + bh[o], o < 7:
+// the sum over the L*L pixel steps (32 features each) runs as 8 interleaved
+// MFMA chains, wave j taking steps j, j+8, ..., added in chain order.
+//
+// A layer by itself is latency: 86528 pixels of 64 bytes (512 samples of
+// L = 13) are a microsecond or two of traffic, but as one launch per layer,
+// with the weights read again for every 16 pixels, the planes, the layers and
+// the head took 3.7 + 6.6 + 2 x 13.5 + 7.7 us; this kernel takes 18.1.
+constexpr int FWD_THREADS = 512;
+constexpr int FWD_WAVES = FWD_THREADS / 64;
 constexpr int ASTR = 40;      // bf16 per pixel of a 32-channel activation (80 B: 16 lanes
                               // reading 16 B each at this stride hit disjoint banks)
 constexpr int W1STR = 104;    // bf16 per row of conv1 weights (96 used)
 constexpr int W23STR = 296;   // bf16 per row of conv2/conv3 weights (288 used)
-constexpr int INFER_WEIGHT_BYTES = 32 * W1STR * 2 + 2 * 32 * W23STR * 2;
-constexpr int INFER_PART_BYTES = INFER_WAVES * 256 * 4 + 16;   // + a 16-byte zero slot
+constexpr int FWD_PIXEL_BYTES = 2 * ASTR * 2 + 2;   // two activation buffers, the tap mask
+constexpr int HEAD_TRIP = 24;
+constexpr int FWD_WEIGHT_BYTES = 32 * W1STR * 2 + 2 * 32 * W23STR * 2;
+constexpr int FWD_PART_BYTES = FWD_WAVES * 256 * 4 + 3 * CH * 4 + 16;  // + biases, zero slot
 
-
-// One convolution over the group's pixels, LDS to LDS.  Each wave takes two
+// One convolution over the group's pixels, from LDS.  Forward: relu(sum +
+// bias); MIRROR (data gradient): the taps point the other way and the sum is
+// kept where the layer's own input, mask, is positive.  Each wave takes two
 // 16-pixel tiles per trip (four independent MFMA chains).  Weights are the
 // A operand (held in VGPRs for the layer), activations the B operand, so a
 // lane ends with four consecutive channels of one pixel and writes them in
-// one 8-byte store.  A tap outside the image (or a pixel past the group) is
-// read from a 16-byte slot of zeros: the validity of the nine taps of a
-// lane's pixel is a 9-bit mask computed once per tile.
-template <int CIN, int WSTR, int INSTR>
-__device__ __forceinline__ void conv_lds(int L, int LL, int npix, const bf16* in, const bf16* w,
-                                         const float* __restrict__ bias, bf16* out,
-                                         const bf16* zslot) {
+// one 8-byte store: to LDS (out, if TO_LDS) and, for the first nglob
+// pixels, to global memory (gout).  A tap outside the image (or a pixel past
+// the group) is read from a 16-byte slot of zeros: taps[q] holds the validity
+// of the nine taps of pixel q, built once per kernel (tap_masks); mirrored,
+// tap t is tap 8 - t.  Biases are read from LDS as well: a global load at the
+// start of each layer is 0.4 us in which nothing else runs.
+template <int CIN, int WSTR, int INSTR, bool MIRROR, bool TO_LDS>
+__device__ __forceinline__ void conv_lds(int L, int npix, const bf16* in, const bf16* w,
+                                         const float* bias, const uint16_t* taps,
+                                         const bf16* __restrict__ mask, bf16* out,
+                                         bf16* __restrict__ gout, int nglob, const bf16* zslot) {
   constexpr int KP = (9 * CIN + 31) / 32 * 32;
   constexpr int STEPS = KP / 32;
   constexpr int CHUNKS = CIN / 8;
+  constexpr int SGN = MIRROR ? -1 : 1;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, n = lane & 15;
   bf16x8 w0[STEPS], w1[STEPS];
 #pragma unroll
@@ -407,39 +131,39 @@ __device__ __forceinline__ void conv_lds(int L, int LL, int npix, const bf16* in
     w1[st] = lds8(w + (n + 16) * WSTR + st * 32 + 8 * grp);
   }
   float bias0[4], bias1[4];
+  if (!MIRROR) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    bias0[i] = bias[4 * grp + i];
-    bias1[i] = bias[16 + 4 * grp + i];
+    for (int i = 0; i < 4; ++i) {
+      bias0[i] = bias[4 * grp + i];
+      bias1[i] = bias[16 + 4 * grp + i];
+    }
   }
   const int ntiles = (npix + 15) / 16;
-  for (int t0 = wave; t0 < ntiles; t0 += 2 * INFER_WAVES) {
+  for (int t0 = wave; t0 < ntiles; t0 += 2 * FWD_WAVES) {
     int q[2];
     uint32_t valid[2];
+    bf16x4 m0[2], m1[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      q[u] = (t0 + u * INFER_WAVES) * 16 + n;
-      const bool ok = q[u] < npix;
-      const int r = ok ? q[u] % LL : 0;
-      const int y = r / L, x = r - (r / L) * L;
-      uint32_t m = 0;
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int yy = y + tap_dy(tap), xx = x + tap_dx(tap);
-        m |= (uint32_t)(yy >= 0 && yy < L && xx >= 0 && xx < L) << tap;
+      q[u] = (t0 + u * FWD_WAVES) * 16 + n;
+      valid[u] = q[u] < npix ? taps[q[u]] : 0u;
+      if (MIRROR && q[u] < nglob) {
+        m0[u] = *reinterpret_cast<const bf16x4*>(mask + (int64_t)q[u] * CH + 4 * grp);
+        m1[u] = *reinterpret_cast<const bf16x4*>(mask + (int64_t)q[u] * CH + 16 + 4 * grp);
+      } else {
+        m0[u] = m1[u] = bf16x4{0, 0, 0, 0};
       }
-      valid[u] = ok ? m : 0u;
     }
     f32x4 acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
 #pragma unroll
     for (int st = 0; st < STEPS; ++st) {
       const int g = 4 * st + grp;
       const int tap = g / CHUNKS, cc = g % CHUNKS;
-      const int toff = (tap_dy(tap) * L + tap_dx(tap)) * INSTR + cc * 8;
+      const int toff = SGN * (tap_dy(tap) * L + tap_dx(tap)) * INSTR + cc * 8;
       bf16x8 xa[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const bool in_img = tap < 9 && ((valid[u] >> tap) & 1u);
+        const bool in_img = tap < 9 && ((valid[u] >> (MIRROR ? 8 - tap : tap)) & 1u);
         xa[u] = lds8(in_img ? in + q[u] * INSTR + toff : zslot);
       }
 #pragma unroll
@@ -454,55 +178,109 @@ __device__ __forceinline__ void conv_lds(int L, int LL, int npix, const bf16* in
       bf16x8 o;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        o[i] = (bf16)fmaxf(acc[u][0][i] + bias0[i], 0.0f);
-        o[4 + i] = (bf16)fmaxf(acc[u][1][i] + bias1[i], 0.0f);
+        if (MIRROR) {
+          o[i] = (bf16)((float)m0[u][i] > 0.0f ? acc[u][0][i] : 0.0f);
+          o[4 + i] = (bf16)((float)m1[u][i] > 0.0f ? acc[u][1][i] : 0.0f);
+        } else {
+          o[i] = (bf16)fmaxf(acc[u][0][i] + bias0[i], 0.0f);
+          o[4 + i] = (bf16)fmaxf(acc[u][1][i] + bias1[i], 0.0f);
+        }
       }
       const uint4 ov = __builtin_bit_cast(uint4, o);
-      *reinterpret_cast<uint2*>(out + q[u] * ASTR + 4 * grp) = make_uint2(ov.x, ov.y);
-      *reinterpret_cast<uint2*>(out + q[u] * ASTR + 16 + 4 * grp) = make_uint2(ov.z, ov.w);
+      if (TO_LDS) {
+        *reinterpret_cast<uint2*>(out + q[u] * ASTR + 4 * grp) = make_uint2(ov.x, ov.y);
+        *reinterpret_cast<uint2*>(out + q[u] * ASTR + 16 + 4 * grp) = make_uint2(ov.z, ov.w);
+      }
+      if (q[u] < nglob) {
+        bf16* go = gout + (int64_t)q[u] * CH + 4 * grp;
+        *reinterpret_cast<uint2*>(go) = make_uint2(ov.x, ov.y);
+        *reinterpret_cast<uint2*>(go + 16) = make_uint2(ov.z, ov.w);
+      }
     }
   }
 }
 
-__global__ void __launch_bounds__(INFER_THREADS) infer_kernel(
+// q / d for q < 2^16 with inv = 2^32 / d + 1 (d >= 2).
+__host__ __device__ inline uint32_t inverse(uint32_t d) { return 0xFFFFFFFFu / d + 1u; }
+__device__ __forceinline__ int quotient(int q, uint32_t inv) {
+  return (int)__umulhi((uint32_t)q, inv);
+}
+
+// taps[q], bit t: pixel q's tap t lies inside the image.
+__device__ __forceinline__ void tap_masks(int L, int npix, uint32_t inv_LL, uint32_t inv_L,
+                                          uint16_t* taps) {
+  for (int q = threadIdx.x; q < npix; q += FWD_THREADS) {
+    const int r = q - quotient(q, inv_LL) * L * L;
+    const int y = quotient(r, inv_L), x = r - y * L;
+    const uint32_t cols = (x > 0 ? 1u : 0u) | 2u | (x < L - 1 ? 4u : 0u);
+    taps[q] = (uint16_t)((y > 0 ? cols : 0u) | cols << 3 | (y < L - 1 ? cols << 6 : 0u));
+  }
+}
+
+// Two [32][288] weight arrays into LDS rows of W23STR.
+__device__ __forceinline__ void stage_weights(bf16* d0, const bf16* __restrict__ g0, bf16* d1,
+                                              const bf16* __restrict__ g1) {
+  for (int i = threadIdx.x; i < 32 * 36; i += FWD_THREADS) {
+    const int r = i / 36, c = i % 36;
+    *reinterpret_cast<uint4*>(d0 + r * W23STR + c * 8) =
+        *reinterpret_cast<const uint4*>(g0 + r * 288 + c * 8);
+    *reinterpret_cast<uint4*>(d1 + r * W23STR + c * 8) =
+        *reinterpret_cast<const uint4*>(g1 + r * 288 + c * 8);
+  }
+}
+
+// x0[pixel][8]: 0 lit star (i, j) at (i, j), 1 lit plaquette (i, j) at (i, j),
+// 2 the sample's p, 3..7 zero.  acts: x0, a1, a2, a3 of the whole batch
+// (STORE only).
+struct CnnActs {
+  bf16 *x0, *a1, *a2, *a3;
+};
+
+template <bool STORE>
+__global__ void __launch_bounds__(FWD_THREADS) forward_kernel(
     int L, int S, int64_t B, const uint8_t* __restrict__ syn, const float* __restrict__ p,
     const bf16* __restrict__ wb1, const bf16* __restrict__ wb2, const bf16* __restrict__ wb3,
     const bf16* __restrict__ whb, const float* __restrict__ b1, const float* __restrict__ b2,
     const float* __restrict__ b3, const float* __restrict__ bh, float* __restrict__ logits,
-    int64_t n_groups) {
+    int64_t n_groups, CnnActs acts) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int LL = L * L, npix = S * LL, nst = 2 * L * (L - 1), ns = L * (L - 1);
   bf16* w1s = reinterpret_cast<bf16*>(smem);
   bf16* w2s = w1s + 32 * W1STR;
   bf16* w3s = w2s + 32 * W23STR;
   float* part = reinterpret_cast<float*>(w3s + 32 * W23STR);     // [waves][16][16]
-  bf16* zslot = reinterpret_cast<bf16*>(part + INFER_WAVES * 256);
+  float* bias = part + FWD_WAVES * 256;                          // [3][32]
+  bf16* zslot = reinterpret_cast<bf16*>(bias + 3 * CH);
   bf16* bufA = zslot + 8;
   bf16* bufB = bufA + npix * ASTR;
+  uint16_t* taps = reinterpret_cast<uint16_t*>(bufB + npix * ASTR);
+  const uint32_t inv_LL = inverse(LL), inv_L = inverse(L);
   const int tid = threadIdx.x;
 
-  for (int i = tid; i < 32 * 12; i += INFER_THREADS) {
+  for (int i = tid; i < 32 * 12; i += FWD_THREADS) {
     const int r = i / 12, c = i % 12;
     *reinterpret_cast<uint4*>(w1s + r * W1STR + c * 8) =
         *reinterpret_cast<const uint4*>(wb1 + r * 96 + c * 8);
   }
-  for (int i = tid; i < 32 * 36; i += INFER_THREADS) {
-    const int r = i / 36, c = i % 36;
-    *reinterpret_cast<uint4*>(w2s + r * W23STR + c * 8) =
-        *reinterpret_cast<const uint4*>(wb2 + r * 288 + c * 8);
-    *reinterpret_cast<uint4*>(w3s + r * W23STR + c * 8) =
-        *reinterpret_cast<const uint4*>(wb3 + r * 288 + c * 8);
+  stage_weights(w2s, wb2, w3s, wb3);
+  if (tid < CH) {
+    bias[tid] = b1[tid];
+    bias[CH + tid] = b2[tid];
+    bias[2 * CH + tid] = b3[tid];
   }
   if (tid < 8) zslot[tid] = (bf16)0.0f;
+  tap_masks(L, npix, inv_LL, inv_L, taps);
   // persistent: the weights stay in LDS while the workgroup walks its groups
   // of S samples (the barriers between the stages already order every
   // buffer's reuse from one group to the next)
   for (int64_t grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
   const int64_t s0 = grp * S;
   const int nsm = (int)min((int64_t)S, B - s0);
-  // input planes, 8 channels per pixel (the layout of the layered x0)
-  for (int q = tid; q < npix; q += INFER_THREADS) {
-    const int sm = q / LL, r = q - sm * LL, y = r / L, x = r - (r / L) * L;
+  const int64_t pix0 = s0 * LL;
+  const int nglob = STORE ? nsm * LL : 0;
+  // input planes, 8 channels per pixel
+  for (int q = tid; q < npix; q += FWD_THREADS) {
+    const int sm = quotient(q, inv_LL), r = q - sm * LL, y = quotient(r, inv_L), x = r - y * L;
     bf16x8 v = zero8();
     if (sm < nsm) {
       const uint8_t* sy = syn + (s0 + sm) * nst;
@@ -511,13 +289,18 @@ __global__ void __launch_bounds__(INFER_THREADS) infer_kernel(
       v[2] = (bf16)p[s0 + sm];
     }
     *reinterpret_cast<uint4*>(bufA + q * 8) = __builtin_bit_cast(uint4, v);
+    if (STORE && sm < nsm)
+      *reinterpret_cast<uint4*>(acts.x0 + (pix0 + q) * 8) = __builtin_bit_cast(uint4, v);
   }
   __syncthreads();
-  conv_lds<8, W1STR, 8>(L, LL, npix, bufA, w1s, b1, bufB, zslot);
+  conv_lds<8, W1STR, 8, false, true>(L, npix, bufA, w1s, bias, taps, nullptr, bufB,
+                               acts.a1 + pix0 * CH, nglob, zslot);
   __syncthreads();
-  conv_lds<32, W23STR, ASTR>(L, LL, npix, bufB, w2s, b2, bufA, zslot);
+  conv_lds<32, W23STR, ASTR, false, true>(L, npix, bufB, w2s, bias + CH, taps, nullptr, bufA,
+                                    acts.a2 + pix0 * CH, nglob, zslot);
   __syncthreads();
-  conv_lds<32, W23STR, ASTR>(L, LL, npix, bufA, w3s, b3, bufB, zslot);
+  conv_lds<32, W23STR, ASTR, false, true>(L, npix, bufA, w3s, bias + 2 * CH, taps, nullptr, bufB,
+                                    acts.a3 + pix0 * CH, nglob, zslot);
   __syncthreads();
 
   // head: wave j runs chain j over pixel steps j, j+8, ...
@@ -525,19 +308,19 @@ __global__ void __launch_bounds__(INFER_THREADS) infer_kernel(
     const int lane = tid & 63, wave = tid >> 6, grp = lane >> 4, n = lane & 15;
     const int64_t kh = (int64_t)LL * CH;
     f32x4 acc = {0, 0, 0, 0};
-    // eight of this chain's steps per trip: their weight loads (from L2) are
-    // all in flight before the first product; rows 7..15 of the padded head
+    // 24 of this chain's steps per trip (all of them up to L = 13): their
+    // weight loads (from L2) are in flight before the first product; rows 7..15 of the padded head
     // weights are zero and not read
-    for (int st0 = wave; st0 < LL; st0 += 8 * INFER_WAVES) {
-      bf16x8 bq[8];
+    for (int st0 = wave; st0 < LL; st0 += HEAD_TRIP * FWD_WAVES) {
+      bf16x8 bq[HEAD_TRIP];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int st = st0 + j * INFER_WAVES;
+      for (int j = 0; j < HEAD_TRIP; ++j) {
+        const int st = st0 + j * FWD_WAVES;
         bq[j] = (st < LL && n < 7) ? load8(whb + (int64_t)n * kh + st * 32 + 8 * grp) : zero8();
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int st = st0 + j * INFER_WAVES;
+      for (int j = 0; j < HEAD_TRIP; ++j) {
+        const int st = st0 + j * FWD_WAVES;
         if (st < LL) {
           const bf16x8 a = n < nsm ? lds8(bufB + (n * LL + st) * ASTR + 8 * grp) : zero8();
           acc = mfma(a, bq[j], acc);
@@ -552,100 +335,424 @@ __global__ void __launch_bounds__(INFER_THREADS) infer_kernel(
     const int row = tid >> 3, o = tid & 7;
     if (row < nsm && o < 7) {
       float t = part[row * 16 + o];
-      for (int j = 1; j < INFER_WAVES; ++j) t = t + part[j * 256 + row * 16 + o];
+      for (int j = 1; j < FWD_WAVES; ++j) t = t + part[j * 256 + row * 16 + o];
       logits[(s0 + row) * 8 + o] = t + bh[o];
     }
   }
   }
 }
 
-// Loss and dL/dlogits per sample (soft cross-entropy on the 4 class logits,
+// ---- backward --------------------------------------------------------------
+// Loss and dL/dlogits of one sample (soft cross-entropy on the 4 class logits,
 // weighted cross-entropy on the 3 budget logits), averaged over the batch.
-__global__ void loss_kernel(int64_t B, const float* __restrict__ logits,
-                            const float* __restrict__ tgt, const int32_t* __restrict__ budget,
-                            float wb, float* __restrict__ dz, float* __restrict__ loss) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const float* z = logits + b * 8;
+__device__ __forceinline__ float sample_loss(const float* __restrict__ z,
+                                             const float* __restrict__ tgt, int budget, float wb,
+                                             float B, float dz[8]) {
   float m = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
   float e[4], se = 0.0f;
   for (int k = 0; k < 4; ++k) { e[k] = expf(z[k] - m); se += e[k]; }
   float lc = 0.0f;
   for (int k = 0; k < 4; ++k) {
     const float pk = e[k] / se;
-    lc -= tgt[b * 4 + k] * ((z[k] - m) - logf(se));
-    dz[b * 8 + k] = (pk - tgt[b * 4 + k]) / (float)B;
+    lc -= tgt[k] * ((z[k] - m) - logf(se));
+    dz[k] = (pk - tgt[k]) / B;
   }
   const float mb = fmaxf(fmaxf(z[4], z[5]), z[6]);
   float eb[3], sb = 0.0f;
   for (int k = 0; k < 3; ++k) { eb[k] = expf(z[4 + k] - mb); sb += eb[k]; }
-  const int y = min(max(budget[b], 0), 2);
-  const float lb = -((z[4 + y] - mb) - logf(sb));
-  for (int k = 0; k < 3; ++k)
-    dz[b * 8 + 4 + k] = wb * (eb[k] / sb - (k == y ? 1.0f : 0.0f)) / (float)B;
-  dz[b * 8 + 7] = 0.0f;
-  loss[b] = lc + wb * lb;
+  const int y = min(max(budget, 0), 2);
+  const float zy = y == 0 ? z[4] : (y == 1 ? z[5] : z[6]);
+  const float lb = -((zy - mb) - logf(sb));
+  for (int k = 0; k < 3; ++k) dz[4 + k] = wb * (eb[k] / sb - (k == y ? 1.0f : 0.0f)) / B;
+  dz[7] = 0.0f;
+  return lc + wb * lb;
 }
 
-// grad Wh[o][f] = sum_b dz[b][o] a3[b][f]; grad bh[o] = sum_b dz[b][o].
-// grad Wh[o][f] = sum_b dz[b][o] a3[b][f]: the batch is cut into
-// HEAD_SEGS contiguous segments (blockIdx.y), each summed in batch order into
-// hpart[seg][o][f]; head_wgrad_reduce adds the segments in order.
-constexpr int HEAD_SEGS = 8;
+// The data gradients of S samples per workgroup: loss and dz, then
+//   dp3[b][f] = (sum_o dz[b][o] whb[o][f]) * (a3[b][f] > 0), rounded to bf16,
+//   dp2 = conv3's data gradient where a2 > 0, dp1 = conv2's where a1 > 0,
+// each kept in LDS for the next and written out for the weight gradients.
+// Like the forward kernel it holds a sample's whole chain because a launch
+// per stage is all latency: loss, head and the two convolutions took
+// 3.5 + 8.8 + 2 x 13 us for 512 samples of L = 13; this kernel takes 16.5.
+constexpr int BWD_WEIGHT_BYTES = 2 * 32 * W23STR * 2;
+constexpr int BWD_SMALL_BYTES = 16 * 8 * 4 + 16;             // dz and the zero slot
 
-__global__ void head_wgrad_kernel(int L, int64_t B, const float* __restrict__ dz,
-                                  const bf16* __restrict__ a3, float* __restrict__ hpart) {
-  const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kh = (int64_t)L * L * CH;
+__global__ void __launch_bounds__(FWD_THREADS) backward_kernel(
+    int L, int S, int64_t B, const float* __restrict__ logits, const float* __restrict__ tgt,
+    const int32_t* __restrict__ budget, float wb, const bf16* __restrict__ wt2,
+    const bf16* __restrict__ wt3, const bf16* __restrict__ whb, const bf16* __restrict__ a1,
+    const bf16* __restrict__ a2, const bf16* __restrict__ a3, float* __restrict__ dz,
+    float* __restrict__ loss, bf16* __restrict__ dp1, bf16* __restrict__ dp2,
+    bf16* __restrict__ dp3, int64_t n_groups) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int LL = L * L, npix = S * LL;
+  const int64_t kh = (int64_t)LL * CH;
+  bf16* w3s = reinterpret_cast<bf16*>(smem);
+  bf16* w2s = w3s + 32 * W23STR;
+  float* dzs = reinterpret_cast<float*>(w2s + 32 * W23STR);      // [16][8]
+  bf16* zslot = reinterpret_cast<bf16*>(dzs + 16 * 8);
+  bf16* bufA = zslot + 8;
+  bf16* bufB = bufA + npix * ASTR;
+  uint16_t* taps = reinterpret_cast<uint16_t*>(bufB + npix * ASTR);
+  const uint32_t inv_LL = inverse(LL);
+  const int tid = threadIdx.x;
+  stage_weights(w3s, wt3, w2s, wt2);
+  if (tid < 8) zslot[tid] = (bf16)0.0f;
+  tap_masks(L, npix, inv_LL, inverse(L), taps);
+  for (int64_t grp = blockIdx.x; grp < n_groups; grp += gridDim.x) {
+    const int64_t s0 = grp * S;
+    const int nsm = (int)min((int64_t)S, B - s0);
+    const int64_t pix0 = s0 * LL;
+    const int nglob = nsm * LL;
+    if (tid < nsm) {
+      const int64_t b = s0 + tid;
+      float d[8];
+      loss[b] = sample_loss(logits + b * 8, tgt + b * 4, budget[b], wb, (float)B, d);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        dz[b * 8 + k] = d[k];
+        dzs[tid * 8 + k] = d[k];
+      }
+    }
+    __syncthreads();
+    // three chunks of 8 features per thread at a time, their 24 loads in flight together
+    for (int i0 = tid; i0 < nglob * 4; i0 += 3 * FWD_THREADS) {
+      bf16x8 av[3], wv[3][7];
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int i = min(i0 + u * FWD_THREADS, nglob * 4 - 1);
+        const int q = i >> 2, c = (i & 3) * 8, r = q - quotient(q, inv_LL) * LL;
+        av[u] = load8(a3 + (pix0 + q) * CH + c);
+#pragma unroll
+        for (int o = 0; o < 7; ++o) wv[u][o] = load8(whb + o * kh + r * CH + c);
+      }
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const int i = i0 + u * FWD_THREADS;
+        if (i < nglob * 4) {
+          const int q = i >> 2, c = (i & 3) * 8;
+          const float* d = dzs + quotient(q, inv_LL) * 8;
+          float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+          for (int o = 0; o < 7; ++o)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s[j] += d[o] * (float)wv[u][o][j];
+          bf16x8 v;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) v[j] = (bf16)((float)av[u][j] > 0.0f ? s[j] : 0.0f);
+          const uint4 ov = __builtin_bit_cast(uint4, v);
+          *reinterpret_cast<uint4*>(bufA + q * ASTR + c) = ov;
+          *reinterpret_cast<uint4*>(dp3 + (pix0 + q) * CH + c) = ov;
+        }
+      }
+    }
+    __syncthreads();
+    conv_lds<32, W23STR, ASTR, true, true>(L, nglob, bufA, w3s, nullptr, taps, a2 + pix0 * CH,
+                                           bufB, dp2 + pix0 * CH, nglob, zslot);
+    __syncthreads();
+    conv_lds<32, W23STR, ASTR, true, false>(L, nglob, bufB, w2s, nullptr, taps, a1 + pix0 * CH,
+                                            nullptr, dp1 + pix0 * CH, nglob, zslot);
+  }
+}
+
+// ---- weight gradients ------------------------------------------------------
+// grad W[co][tap][ci] = sum_p dpre[p][co] * in[p + tap][ci]: the contraction
+// runs over pixels, which is the outer index of both arrays.  A sample is
+// copied to LDS as it lies (16-byte loads, pixel-major), each image row
+// followed by one zero pixel and the image framed by zero rows, so a tap is a
+// constant offset of dy (L + 1) + dx positions and needs no bounds test.
+// ds_read_b64_tr_b16 turns 4 pixels x 16 channels into MFMA operands on the
+// way out, for any offset.  Channel-major staging pays a transposing store per
+// element and, for the taps' odd offsets, eight 2-byte reads per operand: 512
+// samples of L = 13 took 30 us for each of two layers, 13 for the planes and 20
+// for the head's sums; all of them in this launch take 13.2, bound by the
+// latency of its samples' loads and of the partial sums' stores.
+// v_mfma_f32_32x32x16_bf16, D[co][ci]: lane l holds A[l%32][8(l/32)..+7],
+// B[8(l/32)..+7][l%32] and D[8(i/4) + 4(l/32) + i%4][l%32], i = 0..15.
+//
+// A workgroup of three waves walks G samples: wave w takes the taps of row
+// dy = w - 1 (32 input channels) or taps 4w .. 4w + 3 (the planes: 8 channels
+// a tap, 4 taps to a tile; the columns of "tap" 9 read ones and give the bias
+// gradient).  Its row of partial sums lies in the gradients' order,
+//   [W1 864][b1 32][W2 9216][b2 32][W3 9216][b3 32],
+// each part written by its layer's workgroup.  Adding the tiles of several
+// samples in LDS first (two or four samples at once per workgroup) measured
+// 16.6 and 19.2 us.
+constexpr int WG_THREADS = 192;
+constexpr int N_W1 = CH * 27, N_W23 = CH * 288;
+constexpr int ROW_FLOATS = N_W1 + 2 * N_W23 + 3 * CH;
+
+struct WgradGeom {
+  int PW, KP, MARGIN, lds_bytes;
+};
+__host__ __device__ inline WgradGeom wgrad_geom(int L) {
+  WgradGeom g;
+  g.PW = L + 1;
+  g.KP = (L * g.PW + 15) / 16 * 16;                // positions, a multiple of the MFMA k
+  g.MARGIN = L + 2;                                // positions before and after: the widest tap
+  g.lds_bytes = (g.KP + g.KP + 2 * g.MARGIN) * CH * 2;
+  return g;
+}
+
+__device__ __forceinline__ bf16x4 tr_read(const bf16* p) {
+  typedef bf16x4 __attribute__((address_space(3))) * lds4;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)p);
+}
+// k rows 0..7 of a column: two transposed reads, four positions apart
+__device__ __forceinline__ bf16x8 tr_operand(const bf16* p, int four) {
+  const bf16x4 lo = tr_read(p), hi = tr_read(p + four);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// 16-byte chunks i0, i0 + 192, .. (four per thread) of one sample's two
+// arrays: loaded together, and for the next sample while this one is
+// multiplied.  inp: the LDS position of pixel (0, 0) of the input.
+template <int CIN>
+struct SampleChunks {
+  uint4 d0, d1, d2, d3, v0, v1, v2, v3;
+  __device__ __forceinline__ void load(const bf16* __restrict__ dpre, const bf16* __restrict__ in,
+                                       int64_t pix0, int LL, int i0) {
+    const uint4* d = reinterpret_cast<const uint4*>(dpre + pix0 * CH);
+    const uint4* v = reinterpret_cast<const uint4*>(in + pix0 * CIN);
+    const int last = LL * 4 - 1;
+    const int a = min(i0, last), b = min(a + WG_THREADS, last), c = min(b + WG_THREADS, last),
+              e = min(c + WG_THREADS, last);
+    constexpr int SH = CIN == 32 ? 0 : 2;
+    d0 = d[a]; d1 = d[b]; d2 = d[c]; d3 = d[e];
+    v0 = v[a >> SH]; v1 = v[b >> SH]; v2 = v[c >> SH]; v3 = v[e >> SH];
+  }
+  __device__ __forceinline__ void put(bf16* dT, bf16* inp, int LL, uint32_t inv_L, int i, uint4 d,
+                                      uint4 v) const {
+    if (i < LL * 4) {
+      const int r = i >> 2, c = (i & 3) * 8;
+      const int q = r + quotient(r, inv_L);                  // y (L + 1) + x
+      *reinterpret_cast<uint4*>(dT + q * CH + c) = d;
+      if (CIN == 32) *reinterpret_cast<uint4*>(inp + q * CH + c) = v;
+      else if (c == 0) *reinterpret_cast<uint4*>(inp + q * 8) = v;
+    }
+  }
+  __device__ __forceinline__ void stage(bf16* dT, bf16* inp, int LL, uint32_t inv_L,
+                                        int i0) const {
+    put(dT, inp, LL, inv_L, i0, d0, v0);
+    put(dT, inp, LL, inv_L, i0 + WG_THREADS, d1, v1);
+    put(dT, inp, LL, inv_L, i0 + 2 * WG_THREADS, d2, v2);
+    put(dT, inp, LL, inv_L, i0 + 3 * WG_THREADS, d3, v3);
+  }
+};
+
+// The operands of one k step: 16 positions from k on.
+template <int CIN>
+struct Operands {
+  bf16x8 a, b[CIN == 32 ? 3 : 1];
+  __device__ __forceinline__ void read(const bf16* arow, const bf16* brow, int bstep, int k) {
+    a = tr_operand(arow + k * CH, 4 * CH);
+    if (CIN == 32) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) b[t] = tr_operand(brow + (k + t - 1) * CH, 4 * CH);
+    } else {
+      b[0] = tr_operand(brow + k * bstep, 4 * bstep);
+    }
+  }
+};
+
+template <int CIN>
+__device__ __forceinline__ void wgrad_body(int L, int64_t B, int G, int64_t row,
+                                           const bf16* __restrict__ dpre,
+                                           const bf16* __restrict__ in,
+                                           float* __restrict__ out, unsigned char* smem,
+                                           const bf16* ones) {
+  constexpr int TAPS = CIN == 32 ? 3 : 1;          // tiles per wave
+  constexpr int NT = CIN == 32 ? 4 : 1;            // and wave 1's bias tile
+  const WgradGeom gm = wgrad_geom(L);
+  const int st = threadIdx.x, lane = st & 63, w = st >> 6;
+  bf16* dT = reinterpret_cast<bf16*>(smem);                 // [KP][32]
+  bf16* iT = dT + gm.KP * CH;                               // [KP + 2 MARGIN][CIN]
+
+  const int k0 = 8 * (lane >> 5) + ((lane & 15) >> 2);      // this lane's row of a k step
+  const int col = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);  // and its four columns
+  const bf16* arow = dT + k0 * CH + col;
+  const bf16* brow;
+  int bstep = CIN;
+  if (CIN == 32) {
+    brow = iT + (gm.MARGIN + k0 + (w - 1) * gm.PW) * CIN + col;
+  } else {
+    const int tap = 4 * w + col / 8;
+    if (tap < 9) {
+      brow = iT + (gm.MARGIN + k0 + tap_dy(tap) * gm.PW + tap_dx(tap)) * CIN + col % 8;
+    } else {
+      brow = ones;
+      bstep = 0;
+    }
+  }
+  const int LL = L * L;
+  const uint32_t inv_L = inverse(L);
+  f32x16 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+  bf16x8 one8;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) one8[j] = (bf16)1.0f;
+
+  SampleChunks<CIN> ch;
+  const int64_t first = row * G;
+  ch.load(dpre, in, first * LL, LL, st);
+  // the frame and the row ends stay zero for every sample
+  for (int i = st; i < gm.lds_bytes / 16; i += WG_THREADS)
+    reinterpret_cast<uint4*>(smem)[i] = make_uint4(0, 0, 0, 0);
+  const int n = (int)min((int64_t)G, B - first);
+  for (int g = 0; g < n; ++g) {
+    const int64_t smp = first + g;
+    __syncthreads();
+    ch.stage(dT, iT + gm.MARGIN * CIN, LL, inv_L, st);
+    for (int i0 = st + 4 * WG_THREADS; i0 < LL * 4; i0 += 4 * WG_THREADS) {
+      ch.load(dpre, in, smp * LL, LL, i0);
+      ch.stage(dT, iT + gm.MARGIN * CIN, LL, inv_L, i0);
+    }
+    __syncthreads();
+    if (g + 1 < n) ch.load(dpre, in, (smp + 1) * LL, LL, st);
+    // the operands of a k step are read while the step before is multiplied
+    Operands<CIN> cur;
+    cur.read(arow, brow, bstep, 0);
+    for (int k = 0; k < gm.KP; k += 16) {
+      Operands<CIN> nxt;
+      nxt.read(arow, brow, bstep, min(k + 16, gm.KP - 16));
+#pragma unroll
+      for (int t = 0; t < TAPS; ++t) acc[t] = mfma32(cur.a, cur.b[t], acc[t]);
+      if (CIN == 32 && w == 1) acc[NT - 1] = mfma32(cur.a, one8, acc[NT - 1]);
+      cur = nxt;
+    }
+  }
+  const int c = lane & 31;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int co = 8 * (i / 4) + 4 * (lane >> 5) + i % 4;
+    if (CIN == 32) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) out[co * 288 + (3 * w + t) * 32 + c] = acc[t][i];
+      if (w == 1 && c == 0) out[N_W23 + co] = acc[NT - 1][i];
+    } else {
+      const int tap = 4 * w + c / 8, ci = c % 8;
+      if (tap < 9 && ci < 3) out[co * 27 + tap * 3 + ci] = acc[0][i];
+      if (tap == 9 && ci == 0) out[N_W1 + co] = acc[0][i];
+    }
+  }
+}
+
+// grad Wh[o][f] = sum_b dz[b][o] a3[b][f]: the batch is cut into HEAD_SEGS
+// contiguous segments, each summed in batch order into hpart[seg][o][f].
+constexpr int HEAD_SEGS = 16;
+
+__device__ __forceinline__ void head_grad_body(int64_t kh, int64_t B, int64_t block,
+                                               const float* __restrict__ dz,
+                                               const bf16* __restrict__ a3,
+                                               float* __restrict__ hpart) {
+  const int64_t blocks_f = (kh / 2 + blockDim.x - 1) / blockDim.x;
+  const int seg = (int)(block / blocks_f);
+  const int64_t f = 2 * ((block - seg * blocks_f) * blockDim.x + threadIdx.x);
   if (f >= kh) return;
-  const int seg = blockIdx.y;
   const int64_t per = (B + HEAD_SEGS - 1) / HEAD_SEGS;
-  const int64_t b0 = seg * per, b1 = b0 + per < B ? b0 + per : B;
-  float s[7] = {0, 0, 0, 0, 0, 0, 0};
-  for (int64_t b = b0; b < b1; ++b) {
-    const float a = (float)a3[b * kh + f];
+  const int64_t b0 = min(seg * per, B), b1 = min(b0 + per, B);
+  float s0[7] = {0, 0, 0, 0, 0, 0, 0}, s1[7] = {0, 0, 0, 0, 0, 0, 0};
+  auto add = [&](int64_t b, uint32_t v) {
+    const float lo = __uint_as_float(v << 16), hi = __uint_as_float(v & 0xFFFF0000u);
 #pragma unroll
-    for (int o = 0; o < 7; ++o) s[o] += dz[b * 8 + o] * a;
+    for (int o = 0; o < 7; ++o) {
+      s0[o] += dz[b * 8 + o] * lo;
+      s1[o] += dz[b * 8 + o] * hi;
+    }
+  };
+  int64_t b = b0;
+  for (; b + 8 <= b1; b += 8) {
+    uint32_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const uint32_t*>(a3 + (b + j) * kh + f);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) add(b + j, v[j]);
   }
+  for (; b < b1; ++b) add(b, *reinterpret_cast<const uint32_t*>(a3 + b * kh + f));
 #pragma unroll
-  for (int o = 0; o < 7; ++o) hpart[((int64_t)seg * 7 + o) * kh + f] = s[o];
+  for (int o = 0; o < 7; ++o)
+    *reinterpret_cast<float2*>(hpart + ((int64_t)seg * 7 + o) * kh + f) = make_float2(s0[o], s1[o]);
 }
 
-__global__ void head_wgrad_reduce_kernel(int L, int64_t B, const float* __restrict__ hpart,
-                                         const float* __restrict__ dz, float* __restrict__ gWh,
-                                         float* __restrict__ gbh) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kh = (int64_t)L * L * CH;
-  if (i < 7 * kh) {
-    float t = hpart[i];
-    for (int seg = 1; seg < HEAD_SEGS; ++seg) t += hpart[(int64_t)seg * 7 * kh + i];
-    gWh[i] = t;
+// Workgroups [0, rows): conv3, [rows, 2 rows): conv2, [2 rows, 3 rows): conv1,
+// the rest the head.
+__global__ void __launch_bounds__(WG_THREADS) weight_grad_kernel(
+    int L, int64_t B, int G, int64_t rows, const bf16* __restrict__ x0,
+    const bf16* __restrict__ a1, const bf16* __restrict__ a2, const bf16* __restrict__ a3,
+    const bf16* __restrict__ dp1, const bf16* __restrict__ dp2, const bf16* __restrict__ dp3,
+    const float* __restrict__ dz, float* __restrict__ part, float* __restrict__ hpart) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ __align__(16) bf16 ones[8];
+  if (threadIdx.x < 8) ones[threadIdx.x] = (bf16)1.0f;     // read after the first barrier
+  const int64_t blk = blockIdx.x;
+  if (blk >= 3 * rows) {
+    head_grad_body((int64_t)L * L * CH, B, blk - 3 * rows, dz, a3, hpart);
+    return;
   }
-  if (i < 7) {
-    float s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int64_t b = 0;
-    for (; b + 8 <= B; b += 8)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) s[j] += dz[(b + j) * 8 + i];
-    for (int j = 0; b < B; ++b, ++j) s[j] += dz[b * 8 + i];
-    float t = s[0];
-#pragma unroll
-    for (int j = 1; j < 8; ++j) t += s[j];
-    gbh[i] = t;
-  }
+  const int layer = (int)(blk / rows);
+  const int64_t row = blk - layer * rows;
+  float* out = part + row * ROW_FLOATS;
+  if (layer == 0)
+    wgrad_body<32>(L, B, G, row, dp3, a2, out + N_W1 + CH + N_W23 + CH, smem, ones);
+  else if (layer == 1)
+    wgrad_body<32>(L, B, G, row, dp2, a1, out + N_W1 + CH, smem, ones);
+  else
+    wgrad_body<8>(L, B, G, row, dp1, x0, out, smem, ones);
 }
 
-// dpre3[b][f] = (sum_o dz[b][o] whb[o][f]) * (a3[b][f] > 0), rounded to bf16.
-__global__ void head_dgrad_kernel(int L, int64_t B, const float* __restrict__ dz,
-                                  const bf16* __restrict__ whb, const bf16* __restrict__ a3,
-                                  bf16* __restrict__ dpre) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t kh = (int64_t)L * L * CH;
-  if (i >= B * kh) return;
-  const int64_t b = i / kh, f = i - b * kh;
-  float s = 0.0f;
-  for (int o = 0; o < 7; ++o) s += dz[b * 8 + o] * (float)whb[o * kh + f];
-  dpre[i] = (bf16)((float)a3[i] > 0.0f ? s : 0.0f);
+// Samples per weight-gradient workgroup: 128 rows of partial sums at most,
+// with three workgroups (one per layer) to each.  At 512 samples of L = 13,
+// kernel and reduction: 96 rows 15.3 + 4.6 us, 128 rows 13.2 + 5.0, 192 rows
+// 13.3 + 5.3, 256 rows 13.6 + 5.7.
+inline int wgrad_group(int64_t B) {
+  const int64_t target = 128;
+  return (int)(B <= target ? 1 : (B + target - 1) / target);
+}
+inline int64_t wgrad_rows(int64_t B) {
+  const int64_t G = wgrad_group(B);
+  return (B + G - 1) / G;
+}
+
+// All gradients from the partial sums, in one launch: a workgroup takes 32
+// outputs and 8 row segments; segment g adds rows g, g+8, ... in order, and
+// the 8 segment sums are added in segment order.  Outputs: the convolutions
+// (rows of part), the head's weights (HEAD_SEGS rows of hpart), its 7 biases
+// (the B rows of dz).
+constexpr int RED_OUT = 32, RED_SEG = 8;
+
+__global__ void __launch_bounds__(RED_OUT * RED_SEG) grad_reduce_kernel(
+    int64_t rows, int64_t kh, int64_t B, const float* __restrict__ part,
+    const float* __restrict__ hpart, const float* __restrict__ dz, float* __restrict__ grads) {
+  __shared__ float seg_sum[RED_SEG][RED_OUT];
+  const int o = threadIdx.x % RED_OUT, g = threadIdx.x / RED_OUT;
+  const int64_t i = (int64_t)blockIdx.x * RED_OUT + o;
+  const int64_t n_head = 7 * kh, total = ROW_FLOATS + n_head + 7;
+  const float* src = part + i;
+  int64_t n = rows, stride = ROW_FLOATS;
+  if (i >= ROW_FLOATS) { src = hpart + (i - ROW_FLOATS); n = HEAD_SEGS; stride = n_head; }
+  if (i >= ROW_FLOATS + n_head) { src = dz + (i - ROW_FLOATS - n_head); n = B; stride = 8; }
+  if (i >= total) n = 0;
+  float acc = 0.0f;
+  int64_t k = g;
+  for (; k + 7 * RED_SEG < n; k += 8 * RED_SEG) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = src[(k + j * RED_SEG) * stride];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc += v[j];
+  }
+  for (; k < n; k += RED_SEG) acc += src[k * stride];
+  seg_sum[g][o] = acc;
+  __syncthreads();
+  if (g == 0 && i < total) {
+    float t = seg_sum[0][o];
+    for (int j = 1; j < RED_SEG; ++j) t += seg_sum[j][o];
+    grads[i] = t;
+  }
 }
 
 __global__ void adam_kernel(int64_t n, float* __restrict__ prm, const float* __restrict__ g,
@@ -808,7 +915,7 @@ CnnOffsets cnn_offsets(int L) {
 CnnWorkspace cnn_workspace(int L, int64_t B) {
   CnnWorkspace w{};
   const int64_t P = B * L * L, kh = (int64_t)L * L * CH;
-  const int64_t chunks = (B + wgrad_group(B) - 1) / wgrad_group(B);   // weight-gradient rows
+  const int64_t rows = wgrad_rows(B);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -829,8 +936,7 @@ CnnWorkspace cnn_workspace(int L, int64_t B) {
   w.dp3 = take((size_t)P * CH * 2);
   w.dp2 = take((size_t)P * CH * 2);
   w.dp1 = take((size_t)P * CH * 2);
-  w.part = take((size_t)chunks * CH * 288 * 4);
-  w.partb = take((size_t)chunks * CH * 4);
+  w.part = take((size_t)rows * ROW_FLOATS * 4);
   w.hpart = take((size_t)HEAD_SEGS * 7 * kh * 4);
   w.loss = take((size_t)B * 4);
   w.bytes = off;
@@ -862,37 +968,65 @@ int cnn_infer_group(int L) {
   if (hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) !=
       hipSuccess)
     return 0;
-  const int per = 2 * L * L * ASTR * 2;
-  const int S = (maxlds - INFER_WEIGHT_BYTES - INFER_PART_BYTES) / per;
+  const int per = L * L * FWD_PIXEL_BYTES;
+  const int S = (maxlds - FWD_WEIGHT_BYTES - FWD_PART_BYTES) / per;
   return S < 1 ? 0 : (S > 16 ? 16 : S);
 }
+
+namespace {
+
+// Workgroups of a kernel that walks groups of samples: as many as LDS lets
+// the chip hold at once, four to a CU at most.
+int64_t resident_groups(int64_t groups, size_t lds) {
+  const int per_cu = std::max<int>(1, std::min<int>(4, (int)(163840 / lds)));
+  return std::min<int64_t>(groups, (int64_t)device_cus() * per_cu);
+}
+
+// Samples per workgroup of a training pass: the batch over the CUs (the
+// registers of the layers' weights leave room for one workgroup on each),
+// up to what LDS holds.
+int train_group(int L, int64_t B) {
+  const int64_t cus = device_cus(), s = (B + cus - 1) / cus;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(s, cnn_infer_group(L)));
+}
+
+size_t forward_lds_bytes(int L, int S) {
+  return (size_t)FWD_WEIGHT_BYTES + FWD_PART_BYTES + (size_t)S * L * L * FWD_PIXEL_BYTES;
+}
+size_t backward_lds_bytes(int L, int S) {
+  return (size_t)BWD_WEIGHT_BYTES + BWD_SMALL_BYTES + (size_t)S * L * L * FWD_PIXEL_BYTES;
+}
+
+template <bool STORE>
+hipError_t launch_forward(int L, int S, int64_t B, const float* prm, const uint8_t* syn,
+                          const float* p, float* logits, bf16* wb1, bf16* wb2, bf16* wb3,
+                          bf16* wt2, bf16* wt3, bf16* whb, const CnnActs& acts, hipStream_t s) {
+  const CnnOffsets off = cnn_offsets(L);
+  const int64_t kh = (int64_t)L * L * CH;
+  // one thread per entry of the largest of the cast arrays
+  const int64_t n_cast = 16 * kh > 32 * 288 ? 16 * kh : 32 * 288;
+  hipLaunchKernelGGL(cast_kernel, dim3(blocks_for(n_cast, 256)), dim3(256), 0, s, L, prm, off, wb1,
+                     wb2, wb3, wt2, wt3, whb);
+  const size_t lds = forward_lds_bytes(L, S);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&forward_kernel<STORE>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const int64_t groups = (B + S - 1) / S;
+  hipLaunchKernelGGL((forward_kernel<STORE>), dim3((unsigned)resident_groups(groups, lds)),
+                     dim3(FWD_THREADS), lds, s, L, S, B, syn, p, wb1, wb2, wb3, whb, prm + off.b1,
+                     prm + off.b2, prm + off.b3, prm + off.bh, logits, groups, acts);
+  return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t cnn_infer(int L, int64_t B, const float* prm, const uint8_t* syn, const float* p,
                      float* logits, char* ws, hipStream_t s) {
   const CnnWeights wl = cnn_weights(L);
-  const CnnOffsets off = cnn_offsets(L);
-  const int64_t kh = (int64_t)L * L * CH;
   const int S = cnn_infer_group(L);
   if (S < 1) return hipErrorInvalidConfiguration;
-  const int64_t n_cast = 16 * kh > 32 * 288 ? 16 * kh : 32 * 288;
-  bf16* wb1 = reinterpret_cast<bf16*>(ws + wl.wb1);
-  bf16* wb2 = reinterpret_cast<bf16*>(ws + wl.wb2);
-  bf16* wb3 = reinterpret_cast<bf16*>(ws + wl.wb3);
-  bf16* whb = reinterpret_cast<bf16*>(ws + wl.whb);
-  hipLaunchKernelGGL(cast_kernel, dim3(blocks_for(n_cast, 256)), dim3(256), 0, s, L, prm, off, wb1,
-                     wb2, wb3, reinterpret_cast<bf16*>(ws + wl.wt2),
-                     reinterpret_cast<bf16*>(ws + wl.wt3), whb);
-  const size_t lds = (size_t)INFER_WEIGHT_BYTES + INFER_PART_BYTES +
-                     (size_t)2 * S * L * L * ASTR * 2;
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&infer_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  const int64_t groups = (B + S - 1) / S;
-  const int per_cu = std::max<int>(1, std::min<int>(4, (int)(163840 / lds)));
-  const int64_t wgs = std::min<int64_t>(groups, (int64_t)device_cus() * per_cu);
-  hipLaunchKernelGGL(infer_kernel, dim3((unsigned)wgs), dim3(INFER_THREADS), lds, s, L, S, B, syn,
-                     p, wb1, wb2, wb3, whb, prm + off.b1, prm + off.b2, prm + off.b3, prm + off.bh,
-                     logits, groups);
-  return hipGetLastError();
+  auto at = [&](size_t o) { return reinterpret_cast<bf16*>(ws + o); };
+  return launch_forward<false>(L, S, B, prm, syn, p, logits, at(wl.wb1), at(wl.wb2), at(wl.wb3),
+                               at(wl.wt2), at(wl.wt3), at(wl.whb), CnnActs{}, s);
 }
 
 #define WSP(T, name) reinterpret_cast<T*>(ws + wl.name)
@@ -900,79 +1034,44 @@ hipError_t cnn_infer(int L, int64_t B, const float* prm, const uint8_t* syn, con
 hipError_t cnn_forward(int L, int64_t B, const float* prm, const uint8_t* syn, const float* p,
                        float* logits, char* ws, hipStream_t s) {
   const CnnWorkspace wl = cnn_workspace(L, B);
-  const CnnOffsets off = cnn_offsets(L);
-  const int64_t P = B * L * L, kh = (int64_t)L * L * CH;
-  hipLaunchKernelGGL(encode_kernel, dim3(blocks_for(P, 256)), dim3(256), 0, s, L, B, syn, p,
-                     WSP(bf16, x0));
-  // one thread per entry of the largest of the cast arrays
-  const int64_t n_cast = 16 * kh > 32 * 288 ? 16 * kh : 32 * 288;
-  hipLaunchKernelGGL(cast_kernel, dim3(blocks_for(n_cast, 256)), dim3(256), 0, s, L, prm, off,
-                     WSP(bf16, wb1), WSP(bf16, wb2), WSP(bf16, wb3), WSP(bf16, wt2),
-                     WSP(bf16, wt3), WSP(bf16, whb));
-  const unsigned g = blocks_for((P + 15) / 16, 4);
-  hipLaunchKernelGGL((conv_kernel<8, false>), dim3(g), dim3(256), 0, s, L, P, WSP(bf16, x0),
-                     WSP(bf16, wb1), prm + off.b1, nullptr, WSP(bf16, a1));
-  hipLaunchKernelGGL((conv_kernel<32, false>), dim3(g), dim3(256), 0, s, L, P, WSP(bf16, a1),
-                     WSP(bf16, wb2), prm + off.b2, nullptr, WSP(bf16, a2));
-  hipLaunchKernelGGL((conv_kernel<32, false>), dim3(g), dim3(256), 0, s, L, P, WSP(bf16, a2),
-                     WSP(bf16, wb3), prm + off.b3, nullptr, WSP(bf16, a3));
-  hipLaunchKernelGGL(head_fwd_kernel, dim3((unsigned)((B + 15) / 16)), dim3(64 * HEAD_CHAINS), 0, s,
-                     L, B,
-                     WSP(bf16, a3), WSP(bf16, whb), prm + off.bh, logits);
-  return hipGetLastError();
+  if (cnn_infer_group(L) < 1) return hipErrorInvalidConfiguration;
+  const CnnActs acts{WSP(bf16, x0), WSP(bf16, a1), WSP(bf16, a2), WSP(bf16, a3)};
+  return launch_forward<true>(L, train_group(L, B), B, prm, syn, p, logits, WSP(bf16, wb1),
+                              WSP(bf16, wb2), WSP(bf16, wb3), WSP(bf16, wt2), WSP(bf16, wt3),
+                              WSP(bf16, whb), acts, s);
 }
 
 hipError_t cnn_backward(int L, int64_t B, const float* prm, const float* logits, const float* tgt,
                         const int32_t* budget, float wb, float* grads, float* loss, char* ws,
                         hipStream_t s) {
+  (void)prm;
   const CnnWorkspace wl = cnn_workspace(L, B);
-  const CnnOffsets off = cnn_offsets(L);
-  const int64_t P = B * L * L, kh = (int64_t)L * L * CH;
+  if (cnn_infer_group(L) < 1) return hipErrorInvalidConfiguration;
+  const int64_t kh = (int64_t)L * L * CH;
+  const int S = train_group(L, B);
+  const int64_t groups = (B + S - 1) / S;
+  const size_t lds_b = backward_lds_bytes(L, S);
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&backward_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_b);
+  hipLaunchKernelGGL(backward_kernel, dim3((unsigned)resident_groups(groups, lds_b)),
+                     dim3(FWD_THREADS), lds_b, s, L, S, B, logits, tgt, budget, wb,
+                     WSP(bf16, wt2), WSP(bf16, wt3), WSP(bf16, whb), WSP(bf16, a1), WSP(bf16, a2),
+                     WSP(bf16, a3), WSP(float, dz), loss ? loss : WSP(float, loss), WSP(bf16, dp1),
+                     WSP(bf16, dp2), WSP(bf16, dp3), groups);
+
   const int G = wgrad_group(B);
-  const int64_t chunks = (B + G - 1) / G;
-  const size_t lds32 = wgrad_lds_bytes<32>(L), lds8 = wgrad_lds_bytes<8>(L);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_kernel<32>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds32);
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wgrad_kernel<8>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds8);
-  float* lossv = loss ? loss : WSP(float, loss);
-  hipLaunchKernelGGL(loss_kernel, dim3(blocks_for(B, 256)), dim3(256), 0, s, B, logits, tgt,
-                     budget, wb, WSP(float, dz), lossv);
-  hipLaunchKernelGGL(head_wgrad_kernel, dim3(blocks_for(kh, 256), HEAD_SEGS), dim3(256), 0, s, L,
-                     B, WSP(float, dz), WSP(bf16, a3), WSP(float, hpart));
-  hipLaunchKernelGGL(head_wgrad_reduce_kernel, dim3(blocks_for(7 * kh, 256)), dim3(256), 0, s, L,
-                     B, WSP(float, hpart), WSP(float, dz), grads + off.Wh, grads + off.bh);
-  hipLaunchKernelGGL(head_dgrad_kernel, dim3(blocks_for(B * kh, 256)), dim3(256), 0, s, L, B,
-                     WSP(float, dz), WSP(bf16, whb), WSP(bf16, a3), WSP(bf16, dp3));
-  const unsigned g = blocks_for((P + 15) / 16, 4);
-  // conv3: weights, then data back into a2's gradient
-  hipLaunchKernelGGL((conv_wgrad_kernel<32>), dim3((unsigned)chunks), dim3(WG_THREADS), lds32, s,
-                     L, B, G,
-                     WSP(bf16, dp3), WSP(bf16, a2), WSP(float, part), WSP(float, partb));
-  hipLaunchKernelGGL((wgrad_reduce_kernel<32>), dim3(blocks_for(CH * 9 * CH + CH, RED_OUT)),
-                     dim3(RED_OUT * RED_SEG), 0,
-                     s, chunks, CH, WSP(float, part), WSP(float, partb), grads + off.W3,
-                     grads + off.b3);
-  hipLaunchKernelGGL((conv_kernel<32, true>), dim3(g), dim3(256), 0, s, L, P, WSP(bf16, dp3),
-                     WSP(bf16, wt3), nullptr, WSP(bf16, a2), WSP(bf16, dp2));
-  // conv2
-  hipLaunchKernelGGL((conv_wgrad_kernel<32>), dim3((unsigned)chunks), dim3(WG_THREADS), lds32, s,
-                     L, B, G,
-                     WSP(bf16, dp2), WSP(bf16, a1), WSP(float, part), WSP(float, partb));
-  hipLaunchKernelGGL((wgrad_reduce_kernel<32>), dim3(blocks_for(CH * 9 * CH + CH, RED_OUT)),
-                     dim3(RED_OUT * RED_SEG), 0,
-                     s, chunks, CH, WSP(float, part), WSP(float, partb), grads + off.W2,
-                     grads + off.b2);
-  hipLaunchKernelGGL((conv_kernel<32, true>), dim3(g), dim3(256), 0, s, L, P, WSP(bf16, dp2),
-                     WSP(bf16, wt2), nullptr, WSP(bf16, a1), WSP(bf16, dp1));
-  // conv1: weights only
-  hipLaunchKernelGGL((conv_wgrad_kernel<8>), dim3((unsigned)chunks), dim3(WG_THREADS), lds8, s,
-                     L, B, G,
-                     WSP(bf16, dp1), WSP(bf16, x0), WSP(float, part), WSP(float, partb));
-  hipLaunchKernelGGL((wgrad_reduce_kernel<8>), dim3(blocks_for(CH * 9 * 3 + CH, RED_OUT)),
-                     dim3(RED_OUT * RED_SEG), 0, s,
-                     chunks, 3, WSP(float, part), WSP(float, partb), grads + off.W1,
-                     grads + off.b1);
+  const int64_t rows = wgrad_rows(B);
+  const int64_t head = (int64_t)blocks_for(kh / 2, WG_THREADS) * HEAD_SEGS;
+  const int lds_w = wgrad_geom(L).lds_bytes;
+  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&weight_grad_kernel),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_w);
+  hipLaunchKernelGGL(weight_grad_kernel, dim3((unsigned)(3 * rows + head)), dim3(WG_THREADS),
+                     lds_w, s, L, B, G, rows, WSP(bf16, x0), WSP(bf16, a1), WSP(bf16, a2),
+                     WSP(bf16, a3), WSP(bf16, dp1), WSP(bf16, dp2), WSP(bf16, dp3), WSP(float, dz),
+                     WSP(float, part), WSP(float, hpart));
+  hipLaunchKernelGGL(grad_reduce_kernel, dim3(blocks_for(ROW_FLOATS + 7 * kh + 7, RED_OUT)),
+                     dim3(RED_OUT * RED_SEG), 0, s, rows, kh, B, WSP(float, part),
+                     WSP(float, hpart), WSP(float, dz), grads);
   return hipGetLastError();
 }
 
