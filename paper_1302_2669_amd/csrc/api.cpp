@@ -240,8 +240,29 @@ int mcmc_chain_state_size(const mcmc_params* prm, int64_t n, size_t* bytes) {
   return MCMC_OK;
 }
 
-// mcmc_decode_batch; may_create: the matching starts may create their side
-// stream (not for the entry point that allocates nothing)
+// The chains of a uniform batch under two mappings: the first h waves of every
+// SIMD one chain per lane, the others split on the side stream.
+static hipError_t launch_both(const RunArgs& a, int h, SideStream& side, hipStream_t s) {
+  const int L = a.g0.L, range = range_of(L), cus = device_cus();
+  RunArgs lanes = a, rest = a;
+  lanes.n_tiles = (int64_t)h * 4 * cus;
+  rest.split_from = lanes.n_tiles * TILE;
+  rest.n_tiles = (a.g0.n_tasks - rest.split_from + split_tile(L) - 1) / split_tile(L);
+  rest.queue = a.queue + 1;
+  const int64_t waves = std::min<int64_t>(lanes.n_tiles, default_waves(range, cus));
+  const int64_t split_waves = std::min<int64_t>(rest.n_tiles, (int64_t)cus * 4 * SPLIT_WAVES);
+  hipError_t e = side.fork();
+  if (e != hipSuccess) return e;
+  e = launch_chains(range, lanes, (int)waves, 256, s);
+  if (e == hipSuccess)
+    e = launch_chains_split(rest, range_is_wide(range), (int)split_waves, side.stream());
+  const hipError_t joined = side.join();
+  return e != hipSuccess ? e : joined;
+}
+
+// mcmc_decode_batch; may_create: the side stream of the matching starts and of
+// batches under two mappings may be created (not for the entry point that
+// allocates nothing)
 static int decode_batch(const uint8_t* syndromes, const uint32_t* syndrome_ids, int64_t n,
                         const mcmc_params* prm, double* class_prob, double* mean_n,
                         int64_t* sum_n, int64_t* accepts, uint8_t* chosen, uint8_t* correction,
@@ -332,8 +353,19 @@ static int decode_batch(const uint8_t* syndromes, const uint32_t* syndrome_ids, 
   } else {
     const int range = range_of(L), cus = device_cus();
     const int64_t total = a.g0.sweep_end - a.g0.sweep_begin;
+    const int both = a.trace ? 0 : both_waves(L, T, total, 4 * cus);
+    bool launched = false;
+    if (both > 0) {
+      SideStream side(s, may_create, false);
+      if (side.stream()) {
+        st = hip_status(launch_both(a, both, side, s));
+        launched = true;
+      }
+    }
     // traces come from the one-lane kernels alone
-    if (!a.trace && lone_pays(L, T, total, 4 * cus)) {
+    if (launched) {
+      // done
+    } else if (!a.trace && lone_pays(L, T, total, 4 * cus)) {
       st = hip_status(launch_chains_lone(a, s));
     } else if (!a.trace && split_pays(L, T, total, 4 * cus)) {
       a.n_tiles = (T + split_tile(L) - 1) / split_tile(L);

@@ -1,5 +1,6 @@
 // Choice between the chain mappings: one chain per lane (chain_body.h), split
-// over L lanes (chain_split.h), one chain per wave (chain_lone.hip).
+// over L lanes (chain_split.h), one chain per wave (chain_lone.hip), or the
+// first two side by side.
 //
 // The unit is SIMD cycles per update of 64 chains, measured on full and partly
 // filled chips (canonical starts, p = 0.1, L from 3 to 25).
@@ -41,6 +42,37 @@ inline bool split_pays(int L, int64_t chains, int64_t sweeps, int simds) {
   const double W = (double)chains / ((double)TILE * simds);
   const double gain = one_lane_cycles(L, ceil(W)) - (split_cycles(L) * W + 20.0);
   return gain * (double)sweeps * 2.0 * L * (L - 1) > 40000.0;
+}
+
+// Both mappings side by side: whole one-lane waves per SIMD, the chains beyond
+// them split, running in what the waves leave of the SIMD.  Bound by the
+// one-lane waves' own time or by the issue of both.  W = 2.44, L = 25: 7133 us
+// one-lane, 5728 with two waves; W = 3.3, L = 9: 8374, 6908 (two waves), 7202
+// (three); W = 6.2, L = 13: 8587, 7641.
+inline double both_cycles(int L, int h, double rest) {
+  return fmax(one_lane_cycles(L, h), one_lane_issue(L) * h + split_cycles(L) * rest + 20.0);
+}
+
+// The one-lane waves per SIMD of a batch that runs side by side, 0 if one
+// mapping alone is as good: the estimate has to win 7%, its own error (W = 3.9:
+// L = 17 loses 1% at an estimate of 0.94; W = 12.7 and above gain 0 to 4%).
+inline int both_waves(int L, int64_t chains, int64_t sweeps, int simds) {
+  const double W = (double)chains / ((double)TILE * simds);
+  const double alone =
+      fmin(one_lane_cycles(L, ceil(W)),
+           split_pays(L, chains, sweeps, simds) ? split_cycles(L) * W + 20.0 : INFINITY);
+  const int top = (int)fmin(floor(W), 1e6);
+  int best = 0;
+  double cycles = 0.93 * alone;
+  for (int h = top; h >= 1 && h >= top - 1; --h) {
+    const double c = both_cycles(L, h, W - h);
+    if (W > h && c < cycles) {
+      cycles = c;
+      best = h;
+    }
+  }
+  const double gain = (alone - cycles) * (double)sweeps * 2.0 * L * (L - 1);
+  return gain > 40000.0 ? best : 0;
 }
 
 // One chain per wave (codes whose draws fill the lanes, LONE_L_MIN) pays up to

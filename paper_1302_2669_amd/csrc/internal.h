@@ -165,9 +165,27 @@ hipError_t launch_init_matching(const StartArgs& a, hipStream_t s);
 // (callers that must not create runtime objects pass false: then, as under a
 // capture before the stream exists, every launch goes to s in order).
 hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create = true);
-// Creates the current device's side stream of launch_init_mwpm now (for
-// callers that capture the starts into a graph later).
-hipError_t mwpm_prepare_overlap();
+// Creates the current device's side stream now (for callers that may only
+// launch inside a capture).
+hipError_t prepare_side_stream();
+// The current device's side stream, held by one caller at a time: fork() makes
+// it follow what s holds, join() makes s follow it.  stream() is null where
+// there is none: not creatable, another caller's capture holds it, or s is
+// being captured and in_capture is false.
+class SideStream {
+ public:
+  SideStream(hipStream_t s, bool may_create, bool in_capture);
+  ~SideStream();
+  SideStream(const SideStream&) = delete;
+  SideStream& operator=(const SideStream&) = delete;
+  hipStream_t stream() const { return side_; }
+  hipError_t fork();
+  hipError_t join();
+
+ private:
+  hipStream_t s_, side_ = nullptr;
+  hipEvent_t fork_ = nullptr, join_ = nullptr;
+};
 // The start kernel of an MCMC_INIT_* mode.
 hipError_t launch_init_mode(uint32_t init, const StartArgs& a, hipStream_t s,
                             bool may_create = true);

@@ -23,7 +23,6 @@
 // bit planes, and the workgroup packs the four class starts.  Up to three
 // launches by problem size (capacity tiers); the larger two, which hold few
 // syndromes but long solves, run on a side stream beside the first.
-#include <mutex>
 
 #include "device_common.h"
 #include "internal.h"
@@ -258,37 +257,6 @@ init_mwpm_kernel(const StartArgs a, int cap_arg, int waves, int lo, int hi) {
 
 namespace {
 
-// Per device: the side stream of the larger tiers and the events that fork
-// it from and join it to the caller's stream.  Created on first use outside
-// a stream capture (or by mwpm_prepare_overlap) and kept until the process
-// ends; the mutex orders concurrent callers' fork-launch-join sequences.
-struct Overlap {
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
-};
-constexpr int kOverlapDevices = 64;
-std::mutex g_overlap_mu;
-Overlap g_overlap[kOverlapDevices];
-
-// the current device's entry, created if `create`; null if it does not exist
-// (or cannot be made)
-Overlap* overlap_entry(bool create) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kOverlapDevices) return nullptr;
-  Overlap& o = g_overlap[dev];
-  if (o.side || !create) return o.side ? &o : nullptr;
-  Overlap n;
-  if (hipStreamCreateWithFlags(&n.side, hipStreamNonBlocking) != hipSuccess) return nullptr;
-  if (hipEventCreateWithFlags(&n.fork, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&n.join, hipEventDisableTiming) != hipSuccess) {
-    if (n.fork) (void)hipEventDestroy(n.fork);
-    (void)hipStreamDestroy(n.side);
-    return nullptr;
-  }
-  o = n;
-  return &o;
-}
-
 constexpr int kMaxTiers = 5;
 
 hipError_t launch_tier(const StartArgs& a, int cap, int lo, int hi, hipStream_t s) {
@@ -309,11 +277,6 @@ hipError_t launch_tier(const StartArgs& a, int cap, int lo, int hi, hipStream_t 
 }
 
 }  // namespace
-
-hipError_t mwpm_prepare_overlap() {
-  std::lock_guard<std::mutex> lock(g_overlap_mu);
-  return overlap_entry(true) ? hipSuccess : hipErrorOutOfMemory;
-}
 
 hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create) {
   if (a.n == 0) return hipSuccess;
@@ -344,21 +307,16 @@ hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create) 
   // workgroups' look at every syndrome holds the most LDS; first it made 8000
   // syndromes at L = 15 take 1.16 ms instead of 0.92); the smaller ones, largest
   // first, on s; without a side stream, in order on s
-  std::lock_guard<std::mutex> lock(g_overlap_mu);
-  hipStreamCaptureStatus cap_status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap_status) != hipSuccess) cap_status = hipStreamCaptureStatusNone;
-  const Overlap* o = overlap_entry(may_create && cap_status == hipStreamCaptureStatusNone);
   hipError_t e = hipSuccess;
-  if (o) {
-    if ((e = hipEventRecord(o->fork, s)) != hipSuccess) return e;
-    if ((e = hipStreamWaitEvent(o->side, o->fork, 0)) != hipSuccess) return e;
+  SideStream side(s, may_create, true);
+  if (side.stream()) {
+    if ((e = side.fork()) != hipSuccess) return e;
     const int first_aside = full > mid ? nt - 2 : nt - 1;
     for (int t = first_aside; t < nt; ++t)
-      if ((e = launch_tier(a, caps[t], lo[t], hi[t], o->side)) != hipSuccess) return e;
+      if ((e = launch_tier(a, caps[t], lo[t], hi[t], side.stream())) != hipSuccess) return e;
     for (int t = first_aside - 1; t >= 0; --t)
       if ((e = launch_tier(a, caps[t], lo[t], hi[t], s)) != hipSuccess) return e;
-    if ((e = hipEventRecord(o->join, o->side)) != hipSuccess) return e;
-    return hipStreamWaitEvent(s, o->join, 0);
+    return side.join();
   }
   for (int t = 0; t < nt; ++t)
     if ((e = launch_tier(a, caps[t], lo[t], hi[t], s)) != hipSuccess) return e;

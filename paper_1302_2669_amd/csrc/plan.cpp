@@ -695,7 +695,7 @@ int mcmc_plan_create(const mcmc_item* items, int64_t n, uint64_t seed, uint32_t 
   p->tuning.concurrent = 2;
   // the matching starts' side stream exists before any capture of the plan
   // (without it the starts run their launches in order)
-  if (init == MCMC_INIT_MWPM) (void)mwpm_prepare_overlap();
+  if (init == MCMC_INIT_MWPM) (void)prepare_side_stream();
   *out = p;
   return MCMC_OK;
 }

@@ -96,6 +96,16 @@ def test_one_lane_waves_with_a_split_rest(L, noise, chains):
     decode_pair(L, 513, chains, 1, noise, 1)        # 2.0 to 3.1 one-lane waves per SIMD
 
 
+# one-lane waves and a split rest side by side, long enough to be chosen: one to
+# six waves per SIMD, the rest under and over one more wave's worth, ragged
+@pytest.mark.parametrize("L,noise,chains,sweeps", [(2, 0, 83, 90), (5, 1, 78, 60), (9, 0, 105, 12),
+                                                   (12, 0, 201, 8), (13, 1, 78, 8), (16, 0, 80, 6),
+                                                   (17, 0, 71, 6), (25, 1, 57, 4), (25, 0, 78, 4)])
+def test_both_mappings_side_by_side(L, noise, chains, sweeps):
+    decode_pair(L, 513, chains, 1, noise, sweeps)
+    decode_pair(L, 513, chains, 1, noise, sweeps + 1, burn=2, resume=True)
+
+
 @pytest.mark.parametrize("L,chains,K", [(4, 17, 1), (9, 33, 2), (3, 1, 4)])
 def test_estimator_lane_sums(L, chains, K):
     # replica counts around the 16 lanes a class's sums are spread over
