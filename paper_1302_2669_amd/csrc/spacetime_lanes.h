@@ -29,6 +29,14 @@
 // table by q.  A move's threshold is one table read by its gathered codes and
 // set outcomes, "always" being 2^32 - 1 against min(u, 2^32 - 2).  n and m are
 // popcounts of the words after each half.
+//
+// What bounds it: vector issue, once the code fits the instruction cache.  The
+// spatial half is unrolled over its n_stab moves; the time half is unrolled up
+// to L = 7 and else a loop over groups of 32 steps, the words turning by 32
+// positions between groups so that the bit indices stay constants.  L = 7, 2048
+// histories of 7 rounds, 4 chains, 784 sweeps: 204 ms one lane per chain, 43.4
+// ms here (63 of 64 lanes, 3.56 waves per SIMD).  Unrolled, 300 histories of 12
+// rounds at L = 12 take 6.7 ms, rolled 4.7; 1000 of 9 rounds at L = 9 5.7, 5.5.
 #pragma once
 
 #include "spacetime_common.h"
@@ -67,8 +75,16 @@ struct StLanes {
   static constexpr int NQ = G::NQ, SIDE = G::SIDE;
   static constexpr int SKEW = 2 * (ST_LANES_T_MAX - 1);          // positions, last lane
   static constexpr int STEPS = NQ + 2 * (ST_LANES_T_MAX - 2);    // of the time half, at most
-  static constexpr int WE = (NQ + SKEW + 15) / 16;               // skewed data words
-  static constexpr int WO = (G::NSTAB + SKEW + 31) / 32;         // skewed outcome words
+  // The time half rolled into groups of 32 steps, from the size on at which its
+  // code does not fit the instruction cache beside the spatial half's (8192
+  // histories of 3 rounds at L = 3: 27.1 ms unrolled, 28.1 rolled; L = 7: 8.49,
+  // 8.57; 1000 of 8 rounds at L = 8: 4.47, 4.40).  Outcome bits then lie one word
+  // up, and both kinds of words are rings.
+  static constexpr bool ROLLED = L >= 8;
+  static constexpr int OFF = ROLLED ? 32 : 0;
+  static constexpr int WO = (G::NSTAB + SKEW + OFF + 31) / 32;              // skewed outcome words
+  static constexpr int WE = ROLLED ? 2 * WO : (NQ + SKEW + 15) / 16;        // skewed data words
+  static_assert(!ROLLED || (16 * WE >= NQ + SKEW + 2 && 32 * WO >= STEPS), "room for every step");
   static constexpr int PAD = SKEW + 2;                           // table entries below qubit 0
   static constexpr int NTAB = PAD + STEPS + 2;
   // stabilizer on cell (r, c)
@@ -156,11 +172,11 @@ st_chain_lanes_kernel(const SpaceTimeArgs a) {
     });
   } else if (c < per_wave) {
     const uint8_t* o = a.obs + (tk.item * T + t) * NSTAB;
-    uint32_t raw[WO + 1];
+    uint32_t raw[WO + 1];   // a word up, for the shift; two if rolled
     static_for<WO + 1>([&](auto WW) { raw[decltype(WW)::value] = 0u; });
     static_for<NSTAB>([&](auto HH) {
       constexpr int h = decltype(HH)::value;
-      if (o[S::stab_of_bit(h)] != 0) raw[(h >> 5) + 1] |= 1u << (h & 31);
+      if (o[S::stab_of_bit(h)] != 0) raw[(h >> 5) + 1 + S::OFF / 32] |= 1u << (h & 31);
     });
     // skewed for good: the spatial half does not use them
     static_for<WO>([&](auto WW) {
@@ -294,71 +310,98 @@ st_chain_lanes_kernel(const SpaceTimeArgs a) {
         nb[w] = __builtin_amdgcn_alignbit(hi, lo, 4u);
       });
       uint4 tnext = block(time_block);
-      static_for<(S::STEPS + 1) / 2>([&](auto PP) {
-        constexpr int s0 = 2 * decltype(PP)::value;
-        if (s0 < NQ || s0 < steps) {   // uniform; always for the first n_q steps
-          const uint4 blk = tnext;
-          tnext = block(st_opaque(time_block + (uint32_t)(s0 / 2 + 1)));
-          static_for<2>([&](auto HH) {
-            constexpr int s = s0 + decltype(HH)::value;
-            const uint32_t en = entry[s];
-            // outcomes west, east, north, south of the qubit at bits 0..3
-            auto bit_at = [&](auto KK) -> uint32_t {
-              constexpr int p = decltype(KK)::value;
-              if constexpr (p < 0 || (p >> 5) >= WO) return 0u;
-              else return (out[p >> 5] >> (p & 31)) & 1u;
-            };
-            uint32_t around;
-            if constexpr (s > 0 && ((s - 1) >> 5) == (s >> 5) && (s >> 5) < WO)
-              around = (out[s >> 5] >> ((s - 1) & 31)) & 3u;
-            else
-              around = bit_at(std::integral_constant<int, s - 1>{}) |
-                       (bit_at(std::integral_constant<int, s>{}) << 1);
-            around |= bit_at(std::integral_constant<int, s - L>{}) << 2;
-            around |= bit_at(std::integral_constant<int, s + L - 1>{}) << 3;
-            // the qubit's codes in intervals t and t + 1, times 4
-            constexpr int w = s >> 4, sh = 2 * (s & 15);
-            uint32_t codes = 0;
-            if constexpr (w < WE)
-              codes = (((es[w] >> sh) & 3u) << 2) | (((nb[w] >> sh) & 3u) << 4);
-            // X: row 3 x neighbours + set ones of its table
-            const uint32_t row_x = (uint32_t)__builtin_popcount(around & en & 15u) + ((en >> 8) & 15u);
-            const uint32_t thr_x = threshold(thr_time, (row_x << 6) + codes);
-            const uint32_t ax = word_of(blk, (2 * s) & 3) < thr_x ? 0xFFFFFFFFu : 0u;
-            codes = bitop3<0x78>(codes, ax, 0x14u);
-            const uint32_t en_z = en >> 4;
-            const uint32_t row_z = (uint32_t)__builtin_popcount(around & en_z & 15u) + (en >> 12);
-            const uint32_t thr_z = threshold(thr_time + 576, (row_z << 6) + codes);
-            const uint32_t az = word_of(blk, (2 * s + 1) & 3) < thr_z ? 0xFFFFFFFFu : 0u;
-            moves -= ax;
-            moves -= az;
-            // flips: the qubit here and, two positions on, one lane up ...
-            const uint32_t flip = (ax & 1u) | (az & 2u);
-            if constexpr (w < WE) es[w] ^= flip << sh;
-            constexpr int wu = (s + 2) >> 4, shu = 2 * ((s + 2) & 15);
-            if constexpr (wu < WE) es[wu] ^= st_prev_lane(flip << shu);
-            // ... and the outcomes around it
-            const uint32_t turn = (ax & en & 15u) ^ (az & en_z & 15u);
-            if constexpr (s > 0 && ((s - 1) >> 5) == (s >> 5) && (s >> 5) < WO) {
-              out[s >> 5] = bitop3<0x78>(out[s >> 5], turn << ((s - 1) & 31), 3u << ((s - 1) & 31));
-            } else {
-              if constexpr (s > 0 && ((s - 1) >> 5) < WO)
-                out[(s - 1) >> 5] = bitop3<0x78>(out[(s - 1) >> 5], turn << ((s - 1) & 31),
-                                                 1u << ((s - 1) & 31));
-              if constexpr ((s >> 5) < WO)
-                out[s >> 5] = bitop3<0x78>(out[s >> 5], st_shift<(s & 31) - 1>(turn), 1u << (s & 31));
-            }
-            constexpr int pn = s - L, ps = s + L - 1;
-            if constexpr (pn >= 0 && (pn >> 5) < WO)
-              out[pn >> 5] = bitop3<0x78>(out[pn >> 5], st_shift<(pn & 31) - 2>(turn), 1u << (pn & 31));
-            if constexpr ((ps >> 5) < WO)
-              out[ps >> 5] = bitop3<0x78>(out[ps >> 5], st_shift<(ps & 31) - 3>(turn), 1u << (ps & 31));
-            st_fence(es);
-            st_fence(out);
-            st_fence1(moves);
+#pragma unroll 1
+      for (int group = 0; group < (S::ROLLED ? WO : 1); ++group) {
+        const int left = steps - 32 * group;
+        const uint32_t* group_entry = entry + 32 * group;
+        const uint32_t group_block = time_block + 16u * (uint32_t)group;
+        static_for<S::ROLLED ? 16 : (S::STEPS + 1) / 2>([&](auto PP) {
+          constexpr int i0 = 2 * decltype(PP)::value;
+          // uniform; always for the first n_q steps
+          if ((!S::ROLLED && i0 < NQ) || i0 < left) {
+            const uint4 blk = tnext;
+            tnext = block(st_opaque(group_block + (uint32_t)(i0 / 2 + 1)));
+            static_for<2>([&](auto HH) {
+              constexpr int i = i0 + decltype(HH)::value;   // step 32 group + i
+              const uint32_t en = group_entry[i];
+              // outcomes west, east, north, south of the qubit at bits 0..3
+              constexpr int pe = i + S::OFF, pw = pe - 1, pn = pe - L, ps = pe + L - 1;
+              constexpr bool pair = pw >= 0 && (pw >> 5) == (pe >> 5) && (pe >> 5) < WO;
+              auto bit_at = [&](auto KK) -> uint32_t {
+                constexpr int p = decltype(KK)::value;
+                if constexpr (p < 0 || (p >> 5) >= WO) return 0u;
+                else return (out[p >> 5] >> (p & 31)) & 1u;
+              };
+              uint32_t around;
+              if constexpr (pair)
+                around = (out[pe >> 5] >> (pw & 31)) & 3u;
+              else
+                around = bit_at(std::integral_constant<int, pw>{}) |
+                         (bit_at(std::integral_constant<int, pe>{}) << 1);
+              around |= bit_at(std::integral_constant<int, pn>{}) << 2;
+              around |= bit_at(std::integral_constant<int, ps>{}) << 3;
+              // the qubit's codes in intervals t and t + 1, times 4
+              constexpr int w = i >> 4, sh = 2 * (i & 15);
+              uint32_t codes = 0;
+              if constexpr (w < WE)
+                codes = (((es[w] >> sh) & 3u) << 2) | (((nb[w] >> sh) & 3u) << 4);
+              // X: row 3 x neighbours + set ones of its table
+              const uint32_t row_x =
+                  (uint32_t)__builtin_popcount(around & en & 15u) + ((en >> 8) & 15u);
+              const uint32_t thr_x = threshold(thr_time, (row_x << 6) + codes);
+              const uint32_t ax = word_of(blk, (2 * i) & 3) < thr_x ? 0xFFFFFFFFu : 0u;
+              codes = bitop3<0x78>(codes, ax, 0x14u);
+              const uint32_t en_z = en >> 4;
+              const uint32_t row_z = (uint32_t)__builtin_popcount(around & en_z & 15u) + (en >> 12);
+              const uint32_t thr_z = threshold(thr_time + 576, (row_z << 6) + codes);
+              const uint32_t az = word_of(blk, (2 * i + 1) & 3) < thr_z ? 0xFFFFFFFFu : 0u;
+              moves -= ax;
+              moves -= az;
+              // flips: the qubit here and, two positions on, one lane up ...
+              const uint32_t flip = (ax & 1u) | (az & 2u);
+              if constexpr (w < WE) es[w] ^= flip << sh;
+              constexpr int wu = (i + 2) >> 4, shu = 2 * ((i + 2) & 15);
+              if constexpr (wu < WE) es[wu] ^= st_prev_lane(flip << shu);
+              // ... and the outcomes around it
+              const uint32_t turn = (ax & en & 15u) ^ (az & en_z & 15u);
+              if constexpr (pair) {
+                out[pe >> 5] =
+                    bitop3<0x78>(out[pe >> 5], turn << (pw & 31), 3u << (pw & 31));
+              } else {
+                if constexpr (pw >= 0 && (pw >> 5) < WO)
+                  out[pw >> 5] = bitop3<0x78>(out[pw >> 5], turn << (pw & 31), 1u << (pw & 31));
+                if constexpr ((pe >> 5) < WO)
+                  out[pe >> 5] =
+                      bitop3<0x78>(out[pe >> 5], st_shift<(pe & 31) - 1>(turn), 1u << (pe & 31));
+              }
+              if constexpr (pn >= 0 && (pn >> 5) < WO)
+                out[pn >> 5] =
+                    bitop3<0x78>(out[pn >> 5], st_shift<(pn & 31) - 2>(turn), 1u << (pn & 31));
+              if constexpr ((ps >> 5) < WO)
+                out[ps >> 5] =
+                    bitop3<0x78>(out[ps >> 5], st_shift<(ps & 31) - 3>(turn), 1u << (ps & 31));
+              st_fence(es);
+              st_fence(out);
+              st_fence1(moves);
+            });
+          }
+        });
+        if constexpr (S::ROLLED) {
+          // turn the rings; interval t + 1's words are used up
+          const uint32_t es0 = es[0], es1 = es[1], out0 = out[0];
+          static_for<WE - 2>([&](auto WW) {
+            constexpr int w = decltype(WW)::value;
+            es[w] = es[w + 2];
+            nb[w] = nb[w + 2];
           });
+          es[WE - 2] = es0;
+          es[WE - 1] = es1;
+          static_for<WO - 1>([&](auto WW) {
+            out[decltype(WW)::value] = out[decltype(WW)::value + 1];
+          });
+          out[WO - 1] = out0;
         }
-      });
+      }
       // back to plain positions
       static_for<WQ>([&](auto WW) {
         constexpr int w = decltype(WW)::value;
