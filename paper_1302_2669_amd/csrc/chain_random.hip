@@ -21,9 +21,12 @@
 // everything before it, the draws, the site's table entry and the number of
 // acceptance thresholds the draw reaches, depends on no state.  So a lane
 // takes its steps in batches of four: while the reads of a step are in
-// flight it works on the draws of the next batch (half a Philox block per
-// step).  4096 syndromes x 16 chains x 169 sweeps at L = 13, one wave per SIMD:
-// 25.8 -> 9.8 ms, 1175 -> 445 cycles per step.
+// flight it works on the draws of the next batch, half a Philox block and the
+// entry of the slot freed by the step before.
+// A lone wave issues an instruction in about 4.7 cycles whatever it waits for,
+// so the count of them is the time: 90 a step with the batch copied and 77 now.
+// 4096 syndromes x 16 chains x 169 sweeps at L = 13, one wave per SIMD: 25.8 ->
+// 8.6 ms, 1175 -> 391 cycles per step.
 //
 // Randomness: step t of a sweep uses block t >> 1 of Philox4x32-10 at counter
 // (t >> 1, sweep, syndrome_id, 2<<30 | cls<<28 | temp<<20 | chain): word
@@ -57,7 +60,7 @@ struct RowWord<true> {
 //      offset in LDS (r 256 or r 512 bytes, the row above), 16-21 shift of
 //      the fields above and below;
 //   y: bits 0-5 and 8-13 the same shifts plus the flipped part's bit t (0:
-//      x, star; 1: z, plaquette), 16-17 2 - 2t, 24-31 the flipped part's bits
+//      x, star; 1: z, plaquette), 16-20 2 - 2t, 24-31 the flipped part's bits
 //      of the four gathered codes (missing neighbours left out under
 //      bit/phase flips, where their padding would count).
 template <int NOISE, bool WIDE>
@@ -83,21 +86,34 @@ __device__ uint2 site_entry(int L, int s) {
   return e;
 }
 
-// acc + (u >= thr).
-__device__ __forceinline__ uint32_t count_reached(uint32_t acc, uint32_t u, uint32_t thr) {
-  asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
-      : "+v"(acc)
-      : "v"(u), "v"(thr)
-      : "vcc");
-  return acc;
+// philox_round with the compiler's own three-input operation: behind one in
+// inline asm it leaves a wait state, which a lone wave feels (8.70 and 8.60 ms
+// on the launch above).
+__device__ __forceinline__ uint4 keyed_round(uint4 c, uint32_t k0, uint32_t k1) {
+  uint32_t h0, l0, h1, l1;
+  mulhilo(PHILOX_M0, c.x, h0, l0);
+  mulhilo(PHILOX_M1, c.z, h1, l1);
+  return make_uint4(bitop3<0x96>(h1, c.y, k0), l1, bitop3<0x96>(h0, c.w, k1), l0);
 }
 
-// One step ahead of its turn: its site's entry and, as a negative number, how
-// many of the four thresholds its draw stays below (Delta n is accepted iff
-// it is at most that).
+// How many of the four thresholds u stays below.
+__device__ __forceinline__ int32_t count_below(uint32_t u, const uint32_t thr[4]) {
+  int32_t q;
+  asm("v_cmp_lt_u32 vcc, %1, %2\n\tv_cndmask_b32 %0, 0, 1, vcc\n\t"
+      "v_cmp_lt_u32 vcc, %1, %3\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+      "v_cmp_lt_u32 vcc, %1, %4\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+      "v_cmp_lt_u32 vcc, %1, %5\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
+      : "=&v"(q)
+      : "v"(u), "v"(thr[0]), "v"(thr[1]), "v"(thr[2]), "v"(thr[3])
+      : "vcc");
+  return q;
+}
+
+// One step ahead of its turn: its site's entry and how many of the four
+// thresholds its draw stays below (Delta n is accepted iff it is at most that).
 struct Step {
   uint2 site;
-  uint32_t minus_q;
+  int32_t q;
 };
 
 template <int NOISE, bool WIDE>
@@ -112,8 +128,8 @@ chains_random_kernel(const RunArgs a) {
   const int RW = R * W;
   const int nstab = 2 * L * (L - 1);
   const int lane = threadIdx.x;
-  uint2* sites = reinterpret_cast<uint2*>(rs_lds);
-  Row* rows = reinterpret_cast<Row*>(rs_lds + 2 * nstab);   // [R + 2][RS_LANES]
+  Row* rows = reinterpret_cast<Row*>(rs_lds);   // [R + 2][RS_LANES], aligned as a row offset
+  uint2* sites = reinterpret_cast<uint2*>(rows + (R + 2) * RS_LANES);
   for (int s = lane; s < nstab; s += RS_LANES) sites[s] = site_entry<NOISE, WIDE>(L, s);
   __syncthreads();
 
@@ -153,84 +169,103 @@ chains_random_kernel(const RunArgs a) {
   ChainRng rng;
   rng.init(a.k0, a.k1, sid, (2u << 30) | ((uint32_t)cls << 28) | ((uint32_t)(kt + 1) << 20) |
                                 (uint32_t)chain);
-  // block b of the sweep begun last (b the same in every lane)
+  // the first five rounds of block b of the sweep begun last (b the same in
+  // every lane), and the others
   auto block = [&](uint32_t b) -> uint4 {
     uint32_t hi0, lo0, qh, ql;
     mulhilo(PHILOX_M0, b, hi0, lo0);
     mulhilo(PHILOX_M1, hi0 ^ rng.ctr3, qh, ql);
     uint4 v = make_uint4(qh ^ rng.sid_x, ql, rng.sw_x ^ lo0, rng.sw_lo);
 #pragma unroll
-    for (uint32_t r = 2; r < 10; ++r) v = philox_round(v, a.k0 + r * PHILOX_W0, a.k1 + r * PHILOX_W1);
+    for (uint32_t r = 2; r < 5; ++r) v = keyed_round(v, a.k0 + r * PHILOX_W0, a.k1 + r * PHILOX_W1);
+    return v;
+  };
+  auto finish = [&](uint4 v) -> uint4 {
+#pragma unroll
+    for (uint32_t r = 5; r < 10; ++r) v = keyed_round(v, a.k0 + r * PHILOX_W0, a.k1 + r * PHILOX_W1);
     return v;
   };
   auto step_of = [&](uint32_t u_site, uint32_t u_acc) -> Step {
     Step s;
     s.site = sites[__umulhi(u_site, (uint32_t)nstab)];
-    s.minus_q = (uint32_t)-4;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) s.minus_q = count_reached(s.minus_q, u_acc, thr[k]);
+    s.q = count_below(u_acc, thr);
     return s;
   };
 
-  char* const at0 = reinterpret_cast<char*>(rows) + lane * sizeof(Row);
+  // this lane's column; the kernel's only shared memory begins at LDS address 0
+  typedef Row __attribute__((address_space(3))) * LdsRow;
+  const uint32_t column = (uint32_t)(uintptr_t)(LdsRow)(rows + lane);
   constexpr uint32_t kShift = WIDE ? 63u : 31u;
-  Step cur[RS_BATCH], next[RS_BATCH];
+  // the steps to come: slot k holds the next step at position k of a batch; va
+  // and vb are the blocks of slots 0, 1 and 2, 3
+  Step slot[RS_BATCH];
+  uint4 va = make_uint4(0, 0, 0, 0), vb = va;
   if (g.sweep_begin < g.sweep_end) {
     rng.begin_sweep((uint32_t)g.sweep_begin);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint4 v = block((uint32_t)h);
-      next[2 * h] = step_of(v.x, v.y);
-      next[2 * h + 1] = step_of(v.z, v.w);
-    }
+    va = finish(block(0u));
+    vb = finish(block(1u));
+    slot[0] = step_of(va.x, va.y);
+    slot[1] = step_of(va.z, va.w);
+    slot[2] = step_of(vb.x, vb.y);
   }
   for (int sweep = g.sweep_begin; sweep < g.sweep_end; ++sweep) {
     int32_t moves = 0;
     int64_t sum = 0;
     for (int first = 0; first < nstab; first += RS_BATCH) {
-#pragma unroll
-      for (int k = 0; k < RS_BATCH; ++k) cur[k] = next[k];
       // the batch after this one: of this sweep or the first of the next
       uint32_t b = (uint32_t)(first + RS_BATCH) >> 1;
       if (first + RS_BATCH == nstab) {
         rng.begin_sweep((uint32_t)sweep + 1);
         b = 0;
       }
-      uint4 v;
       int32_t batch_sum = 0;
 #pragma unroll
       for (int k = 0; k < RS_BATCH; ++k) {
-        const uint2 e = cur[k].site;
-        Row* p = reinterpret_cast<Row*>(at0 + (e.x & (WIDE ? 0x7E00u : 0x7F00u)));
+        const uint2 e = slot[k].site;
+        const LdsRow p = (LdsRow)(uintptr_t)((e.x & (WIDE ? 0x7E00u : 0x7F00u)) | column);
         const Row up = p[0], mid = p[RS_LANES], down = p[2 * RS_LANES];
         __builtin_amdgcn_sched_barrier(0);
-        // while they arrive: a block of the next batch, or its two steps
-        if (k % 2 == 0) {
-          v = block(b + k / 2);
+        // while they arrive: half a block, and the slot that is free again
+        if (k == 0) {
+          slot[3] = step_of(vb.z, vb.w);
+          va = block(b);
+        } else if (k == 1) {
+          va = finish(va);
+          slot[0] = step_of(va.x, va.y);
+        } else if (k == 2) {
+          slot[1] = step_of(va.z, va.w);
+          vb = block(b + 1);
         } else {
-          next[k - 1] = step_of(v.x, v.y);
-          next[k] = step_of(v.z, v.w);
+          vb = finish(vb);
+          slot[2] = step_of(vb.x, vb.y);
         }
         __builtin_amdgcn_sched_barrier(0);
         // the four codes: above, below, the pair
-        const uint32_t single = e.x >> 16;
-        uint32_t code = ((uint32_t)(up >> (single & kShift)) & 3u) |
-                        (((uint32_t)(down >> (single & kShift)) & 3u) << 2);
-        code |= ((uint32_t)(mid >> (e.x & kShift)) & 15u) << 4;
-        // Delta n = (qubits whose weight the move changes) - 2 (those of them
-        // with the flipped part set): every valid qubit under bit/phase
-        // flips, else those without the other part
+        uint32_t code;
+        if constexpr (WIDE) {
+          const uint32_t single = e.x >> 16;
+          code = (((uint32_t)(mid >> (e.x & kShift)) & 15u) << 2) |
+                 ((uint32_t)(down >> (single & kShift)) & 3u);
+          code = (code << 2) | ((uint32_t)(up >> (single & kShift)) & 3u);
+        } else {
+          const uint32_t single = e.x >> 16;
+          code = (__builtin_amdgcn_ubfe(mid, e.x, 4) << 2) | __builtin_amdgcn_ubfe(down, single, 2);
+          code = (code << 2) | __builtin_amdgcn_ubfe(up, single, 2);
+        }
+        // Delta n = the qubits that the move makes wrong minus those that it
+        // mends: the valid ones without and with the flipped part set, under
+        // depolarizing noise only those without the other part
         const uint32_t own = e.y >> 24;
-        uint32_t live = own;
-        if constexpr (NOISE == 0) live = own & ~((code << 1) >> ((e.y >> 16) & 3u));
-        const int32_t over = (int32_t)__builtin_popcount(live) + (int32_t)cur[k].minus_q -
-                             2 * (int32_t)__builtin_popcount(code & live);
-        if (over <= 0) {
-          const Row ms = (Row)1 << ((e.y >> 8) & kShift), mp = (Row)5 << (e.y & kShift);
+        uint32_t other = 0;
+        if constexpr (NOISE == 0) other = (code << 1) >> ((e.y >> 16) & 31u);
+        const int32_t delta = (int32_t)__builtin_popcount(bitop3<0x10>(own, code, other)) -
+                              (int32_t)__builtin_popcount(bitop3<0x40>(own, code, other));
+        if (delta <= slot[k].q) {
+          const Row ms = (Row)1 << ((e.y >> 8) & 0xFFu), mp = (Row)5 << (e.y & kShift);
           p[0] = up ^ ms;
           p[RS_LANES] = mid ^ mp;
           p[2 * RS_LANES] = down ^ ms;
-          n += over - (int32_t)cur[k].minus_q;
+          n += delta;
           ++moves;
         }
         batch_sum += n;
