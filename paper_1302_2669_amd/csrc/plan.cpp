@@ -395,8 +395,14 @@ int build_plan(mcmc_plan* p, const mcmc_item* items, int64_t n) {
 
 // Which groups run split over lanes.  A plan of one group decides as a uniform
 // batch.  With several the longest ones are split, as many as give the
-// shortest estimated execution: the larger of the work over all SIMDs and the
-// longest one-lane tile, which shares its SIMD with other waves.
+// shortest estimated execution.  The work spreads over all SIMDs; beside it run
+// the one-lane tiles of the two-word-row ranges and of the first launch on the
+// caller's stream, the longest of which shares its SIMD with other waves.  The
+// launches behind that one find the split waves resident and their registers
+// taken: where there are split chains their longest tiles come on top, alone on
+// their SIMDs.  (4096 syndromes of 11 sizes, 4 chains, L^2 sweeps: with L >= 17
+// split and the launches of L <= 15 in a row 16.2 ms, with L >= 9 split 12.5;
+// 16384 of 7 sizes up to 15: 8.3, 6.1.)
 void choose_split(mcmc_plan* p) {
   const size_t n = p->groups.size();
   const int simds = 4 * device_cus();
@@ -412,13 +418,38 @@ void choose_split(mcmc_plan* p) {
   double work = 0.0;
   for (size_t gi = 0; gi < n; ++gi)
     work += (double)p->groups[gi].n_tasks / TILE * updates(gi) * one_lane_issue(p->groups[gi].L);
+  // the estimate with groups 0 .. k - 1 split
+  auto estimate = [&](size_t k) {
+    bool split_narrow = false;
+    for (size_t gi = 0; gi < k; ++gi) split_narrow |= p->groups[gi].L <= 16;
+    // longest tiles: the two-word-row ranges, then the launches of the caller's
+    // stream but for the split one, which comes second
+    double wide = 0.0, range1 = 0.0, pair = 0.0, range0 = 0.0;
+    for (size_t gi = k; gi < n; ++gi) {
+      const int L = p->groups[gi].L;
+      double& longest = L > 16             ? wide
+                        : L <= PAIR_L_MAX  ? pair
+                        : range_of(L) == 1 ? range1
+                                           : range0;
+      longest = std::max(longest, updates(gi) * one_lane_cycles(L, 2.0));
+    }
+    double beside = wide, behind = 0.0;
+    bool first = true;
+    for (double tile : {range1, split_narrow ? -1.0 : 0.0, pair, range0}) {
+      if (tile == 0.0) continue;
+      if (tile > 0.0 && first) beside = std::max(beside, tile);
+      if (tile > 0.0 && !first) behind += tile;
+      first = false;
+    }
+    const double t = std::max(work / simds, beside);
+    return k == 0 ? std::max(t, behind) : t + behind;
+  };
   // groups are in descending cost: the longest one-lane tile is the first
   // group's that is not split
   double best = 0.0;
   size_t best_count = 0;
-  for (size_t k = 0; k <= n; ++k) {   // groups 0 .. k - 1 split
-    const double tile = k < n ? updates(k) * one_lane_cycles(p->groups[k].L, 2.0) : 0.0;
-    const double t = std::max(work / simds, tile);
+  for (size_t k = 0; k <= n; ++k) {
+    const double t = estimate(k);
     if (k == 0 || t < best) {
       best = t;
       best_count = k;

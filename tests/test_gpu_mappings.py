@@ -106,6 +106,28 @@ def test_both_mappings_side_by_side(L, noise, chains, sweeps):
     decode_pair(L, 513, chains, 1, noise, sweeps + 1, burn=2, resume=True)
 
 
+# plans whose longest groups are split and whose launches on the caller's stream
+# follow each other: all groups split, a pair launch left, one-lane ranges left
+@pytest.mark.parametrize("Ls,per", [((3, 5, 7, 9, 11, 13, 15), 80), ((5, 9, 13, 15, 17, 25), 120),
+                                    ((8, 16, 17), 200), ((9, 11, 13, 15), 900)])
+def test_plan_with_split_groups(Ls, per):
+    syns = [mc.sample_errors(L, 0.1, 5, per)[0] for L in Ls]
+    items = [dict(L=L, p=0.1, sweeps=L * L // 4, burn=0, chains=3, n_temps=1, syndrome_id=i)
+             for L in Ls for i in range(per)]
+    plan = mc.MixedPlan(items, seed=9)
+    out = plan.execute(torch.cat([s.reshape(-1) for s in syns]), want_sums=True)
+    g = to_np(out)
+    for j, L in enumerate(Ls):
+        u = to_np(mc.decode_batch(syns[j], L, 0.1, L * L // 4, 9, chains=3, want_sums=True,
+                                  init=mc.MCMC_INIT_MATCHING))
+        lo, hi = j * per, (j + 1) * per
+        a, b = plan.chain_offsets[lo], plan.chain_offsets[hi]
+        for k in ("sum_n", "accepts"):
+            assert np.array_equal(g[k][a:b], u[k].reshape(-1)), (L, k)
+        assert np.array_equal(g["chosen"][lo:hi], u["chosen"]), L
+    plan.close()
+
+
 @pytest.mark.parametrize("L,chains,K", [(4, 17, 1), (9, 33, 2), (3, 1, 4)])
 def test_estimator_lane_sums(L, chains, K):
     # replica counts around the 16 lanes a class's sums are spread over
