@@ -1,12 +1,14 @@
 // Device-built plan for a batch of one code size whose syndromes each carry a
 // sweep budget (route 0: no counted sweep, 1: short, 2: full), as set by the
-// gate.  Three groups in descending cost (full, short, none); the items of a
-// group are written in whatever order the atomics give, which changes no
+// gate.  Three groups in descending cost (full, short, none), the full one's
+// chains under the mappings that a uniform batch of as many would take; the
+// items of a group are written in whatever order the atomics give, which changes no
 // result: every chain is keyed by its syndrome id, class, temperature and
 // replica, and every output goes to the syndrome's own slots.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "chain_choice.h"
 #include "device_common.h"
 #include "internal.h"
 
@@ -59,9 +61,27 @@ __global__ void budget_finalize_kernel(const BudgetArgs a) {
     d.first_item = (int32_t)first;
     d.n_items = (int32_t)ng;
     d.n_tasks = (int64_t)ng * 4 * a.K * a.C;
-    a.groups[g] = d;
     a.counts[4 + g] = first;        // cursor of the group's items
     first += ng;
+    if (g == 0) {
+      // the full budget under the mapping of a uniform batch: its first items
+      // one chain per lane, the others split
+      const int64_t per_item = 4 * (int64_t)a.K * a.C;
+      const int64_t tasks = d.n_tasks, sweeps = d.sweep_end;
+      const int h = both_waves(a.L, tasks, sweeps, a.simds);
+      int64_t keep = ng;
+      if (h > 0) keep = (int64_t)h * a.simds * TILE / per_item;
+      else if (split_pays(a.L, tasks, sweeps, a.simds)) keep = 0;
+      GroupDesc rest = d;
+      rest.first_item = (int32_t)(d.first_item + keep);
+      rest.n_items = (int32_t)(ng - keep);
+      rest.n_tasks = (ng - keep) * per_item;
+      a.groups[3] = rest;
+      a.tile_cum[3] = (uint32_t)((rest.n_tasks + split_tile(a.L) - 1) / split_tile(a.L));
+      d.n_items = (int32_t)keep;
+      d.n_tasks = keep * per_item;
+    }
+    a.groups[g] = d;
     cum += (uint32_t)((d.n_tasks + TILE - 1) / TILE);
     a.tile_cum[g] = cum;
   }

@@ -17,10 +17,10 @@ namespace mcmc {
 // less to amortise a row's fixed work over.  L = 13, measured and estimated: 1
 // wave 186 / 181, 2 217 / 208, 3 272 / 275, 5 406 / 408; L = 5: 187 / 227, 249 /
 // 260, 337 / 344, 521 / 512.
-inline double one_lane_issue(int L) {
+__host__ __device__ inline double one_lane_issue(int L) {
   return (64.0 + 500.0 / (L * L)) * (L > 16 ? 1.07 : 1.0);
 }
-inline double one_lane_cycles(int L, double w) {
+__host__ __device__ inline double one_lane_cycles(int L, double w) {
   return one_lane_issue(L) * (w <= 1.0 ? 2.7 : w + 1.1);
 }
 
@@ -28,7 +28,7 @@ inline double one_lane_cycles(int L, double w) {
 // counts (250 cycles a block) and four phases of one or two row words.
 // Measured and estimated: L = 3 203 / 204, 5 139 / 140, 9 97 / 99, 13 106 / 106,
 // 16 86 / 86, 17 116 / 118, 21 93 / 89, 25 112 / 107.
-inline double split_cycles(int L) {
+__host__ __device__ inline double split_cycles(int L) {
   const int blocks = L / 2, words = (L + 15) / 16;
   const double sweep = 250.0 * blocks + 4.0 * (110.0 * words + 26.0);
   return sweep * 64.0 / (split_tile(L) * 2.0 * L * (L - 1));
@@ -38,7 +38,7 @@ inline double split_cycles(int L) {
 // split: one-lane waves come whole to a SIMD, the split work spreads evenly,
 // but its waves take some 40000 cycles longer to set up (3000 syndromes at L = 6
 // without a sweep: 171 us one-lane, 193 split).
-inline bool split_pays(int L, int64_t chains, int64_t sweeps, int simds) {
+__host__ __device__ inline bool split_pays(int L, int64_t chains, int64_t sweeps, int simds) {
   const double W = (double)chains / ((double)TILE * simds);
   const double gain = one_lane_cycles(L, ceil(W)) - (split_cycles(L) * W + 20.0);
   return gain * (double)sweeps * 2.0 * L * (L - 1) > 40000.0;
@@ -49,14 +49,14 @@ inline bool split_pays(int L, int64_t chains, int64_t sweeps, int simds) {
 // one-lane waves' own time or by the issue of both.  W = 2.44, L = 25: 7133 us
 // one-lane, 5728 with two waves; W = 3.3, L = 9: 8374, 6908 (two waves), 7202
 // (three); W = 6.2, L = 13: 8587, 7641.
-inline double both_cycles(int L, int h, double rest) {
+__host__ __device__ inline double both_cycles(int L, int h, double rest) {
   return fmax(one_lane_cycles(L, h), one_lane_issue(L) * h + split_cycles(L) * rest + 20.0);
 }
 
 // The one-lane waves per SIMD of a batch that runs side by side, 0 if one
 // mapping alone is as good: the estimate has to win 7%, its own error (W = 3.9:
 // L = 17 loses 1% at an estimate of 0.94; W = 12.7 and above gain 0 to 4%).
-inline int both_waves(int L, int64_t chains, int64_t sweeps, int simds) {
+__host__ __device__ inline int both_waves(int L, int64_t chains, int64_t sweeps, int simds) {
   const double W = (double)chains / ((double)TILE * simds);
   const double alone =
       fmin(one_lane_cycles(L, ceil(W)),

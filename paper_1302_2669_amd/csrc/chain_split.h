@@ -356,20 +356,25 @@ __device__ __forceinline__ void dispatch_split(const RunArgs& a, const GroupDesc
 
 // Persistent tile loop, one wave per workgroup, as in chains_persistent.  A
 // plan's entry is a whole group: its first_task field holds the number of tiles
-// before it.
+// before it.  A device-built plan has one group to split, its last.
 template <int LMIN, int LMAX, int NOISE>
 __device__ __forceinline__ void split_persistent(const RunArgs& a) {
   __shared__ __align__(16) uint32_t lds[split_words<LMIN, LMAX>()];
   const int lane = threadIdx.x & 63;
+  const int64_t n_tiles = a.tile_cum ? (int64_t)a.tile_cum[3] : a.n_tiles;
   while (true) {
     uint32_t tile = 0;
     if (lane == 0) tile = atomicAdd(a.queue, 1u);
     tile = __builtin_amdgcn_readfirstlane(tile);
-    if ((int64_t)tile >= a.n_tiles) break;
+    if ((int64_t)tile >= n_tiles) break;
     GroupDesc g;
     int L;
     int64_t first;
-    if (a.tiles) {
+    if (a.tile_cum) {
+      g = a.groups[3];
+      L = g.L;
+      first = (int64_t)tile * split_tile(L);
+    } else if (a.tiles) {
       int lo = 0, hi = a.n_split - 1;   // the last entry that starts at or before the tile
       while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;

@@ -15,7 +15,7 @@ chains_split_wide_kernel(const RunArgs a) {
 
 hipError_t launch_chains_split(const RunArgs& a, bool wide, int waves, hipStream_t s) {
   if (a.n_tiles == 0) return hipSuccess;
-  if (a.trace || a.tile_cum || waves < 1) return hipErrorInvalidValue;
+  if (a.trace || waves < 1) return hipErrorInvalidValue;
   if (a.noise == MCMC_NOISE_BITPHASE) return launch_chains_split_flip(a, wide, waves, s);
   if (a.noise != MCMC_NOISE_DEPOLARIZING) return hipErrorInvalidValue;
   if (wide)

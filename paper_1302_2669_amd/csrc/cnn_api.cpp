@@ -277,7 +277,7 @@ struct mcmc_gated {
   int32_t* h_idx = nullptr;   // escalated batch indices
   float* h_pf = nullptr;
   std::vector<mcmc_item> items;
-  // device-built budget plan (the path without escalation): groups [3],
+  // device-built budget plan (the path without escalation): groups [4],
   // items [N], tables [N][K][4], beta_bar [N], ids [N], counters [8],
   // cumulative tiles [4]; pinned staging of ids, tables, beta and counts
   void* dblock = nullptr;
@@ -421,7 +421,7 @@ int mcmc_gated_create(const mcmc_gate_config* h_cfg, mcmc_gated** out) {
   ok = ok && hipHostMalloc((void**)&g->h_pf, n * 4, hipHostMallocDefault) == hipSuccess;
   // device-built budget plan storage
   const size_t K4 = 4 * (size_t)c.n_temps;
-  const size_t sz_g = align_up(3 * sizeof(GroupDesc)), sz_i = align_up(n * sizeof(ItemDesc));
+  const size_t sz_g = align_up(4 * sizeof(GroupDesc)), sz_i = align_up(n * sizeof(ItemDesc));
   // tables: one per syndrome, then the configured rate's at slot N
   const size_t sz_t = align_up((n + 1) * K4 * 4), sz_b = align_up(n * 8), sz_id = align_up(n * 4);
   const size_t sz_c = align_up(8 * 4), sz_tc = align_up(4 * 4), sz_gap = align_up(MCMC_GAP_BINS);
@@ -611,6 +611,7 @@ int gated_decode_device(mcmc_gated* g, const float* d_params, const uint8_t* d_s
   ba.sweeps[0] = c.sweeps_full;
   ba.sweeps[1] = c.sweeps_short;
   ba.sweeps[2] = 0;
+  ba.simds = 4 * device_cus();
   ba.counts = g->d_counts;
   ba.groups = g->d_groups;
   ba.items = g->d_items;
@@ -646,8 +647,24 @@ int gated_decode_device(mcmc_gated* g, const float* d_params, const uint8_t* d_s
   a.final_rows = frows;
   a.total_chains = n * per_item;
   const int64_t waves = std::min<int64_t>(max_tiles, (int64_t)device_cus() * 4 * RANGE_WAVES[r]);
-  st = hip_status(launch_chains(r, a, (int)waves, 256, s));
-  if (st != MCMC_OK) return st;
+  // the chains that the plan splits run beside the others
+  RunArgs rest = a;
+  rest.queue = queue + N_RANGES;
+  rest.n_tiles = (n * per_item + split_tile(c.L) - 1) / split_tile(c.L);   // at most
+  const int split_waves =
+      (int)std::min<int64_t>(rest.n_tiles, (int64_t)device_cus() * 4 * SPLIT_WAVES);
+  {
+    SideStream side(s, true, false);
+    const bool beside = side.stream() != nullptr;
+    if (beside) st = hip_status(side.fork());
+    if (st != MCMC_OK) return st;
+    st = hip_status(launch_chains(r, a, (int)waves, 256, s));
+    const int st2 = hip_status(launch_chains_split(rest, range_is_wide(r), split_waves,
+                                                   beside ? side.stream() : s));
+    const int st3 = beside ? hip_status(side.join()) : MCMC_OK;
+    if (st == MCMC_OK) st = st2 != MCMC_OK ? st2 : st3;
+    if (st != MCMC_OK) return st;
+  }
 
   DecideArgs d{};
   d.items = g->d_items;

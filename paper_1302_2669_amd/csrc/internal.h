@@ -70,8 +70,8 @@ struct RunArgs {
   uint32_t table0[MCMC_TEMPS_MAX][4];
   int64_t n_tiles;
   // device-built plan: cumulative tile counts of groups 0, 1, 2 (tile t of
-  // group g covers tasks (t - tiles before g) * TILE ...); when set, tiles and
-  // n_tiles are not used by the kernel
+  // group g covers tasks (t - tiles before g) * TILE ...), then the split tiles
+  // of group 3; when set, tiles and n_tiles are not used by the kernels
   const uint32_t* tile_cum;
   uint32_t* queue;               // tile counter of this launch, zero at start
   int32_t lmin, lmax;            // L range compiled into the launched kernel
@@ -320,9 +320,10 @@ struct BudgetArgs {
   int32_t L, K, C, burn;
   int32_t sweeps[3];
   uint32_t* counts;             // [8] scratch, cleared here
-  GroupDesc* groups;            // [3] out
+  int32_t simds;
+  GroupDesc* groups;            // [4] out: the last is the part of the first that runs split
   ItemDesc* items;              // [n] out
-  uint32_t* tile_cum;           // [3] out: cumulative tiles of groups 0..2
+  uint32_t* tile_cum;           // [4] out: cumulative tiles of groups 0..2, split tiles of group 3
 };
 hipError_t launch_budget_plan(const BudgetArgs& a, hipStream_t s);
 

@@ -10,9 +10,11 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import paper_1302_2669_amd as mc  # noqa: E402
+import test_gpu_gated  # noqa: E402
 from oracle import decoder, geometry, sampler  # noqa: E402
 from oracle import spacetime as stm  # noqa: E402
 
+from paper_1302_2669_amd import gate  # noqa: E402
 from paper_1302_2669_amd.inputs import SEED_L9  # noqa: E402
 
 DEV = "cuda"
@@ -126,6 +128,22 @@ def test_plan_with_split_groups(Ls, per):
             assert np.array_equal(g[k][a:b], u[k].reshape(-1)), (L, k)
         assert np.array_equal(g["chosen"][lo:hi], u["chosen"]), L
     plan.close()
+
+
+# the gate's device-built plan: its full-budget chains all split, in whole waves
+# with a split rest (ragged on both sides), and one chain per lane
+@pytest.mark.parametrize("L,n,chains,full,threshold", [(5, 700, 3, 40, 0.5), (5, 9001, 4, 60, 1.0),
+                                                       (13, 9001, 6, 10, 0.5), (17, 2500, 11, 5, 1.0),
+                                                       (9, 8192, 2, 7, 1.0)])
+def test_gated_mappings(L, n, chains, full, threshold):
+    syn = mc.sample_errors(L, 0.1, 3, n)[0]
+    prm = torch.from_numpy(test_gpu_gated.spread_params(L, 17)).to(DEV)
+    g = gate.GatedDecoder(L, 0.1, 21, max_batch=n, sweeps_short=2, sweeps_full=full, chains=chains,
+                          threshold=threshold)
+    out = g.decode(prm, syn, want_correction=True)
+    test_gpu_gated.check_routes(L, syn, np.full(n, 0.1), np.arange(n, dtype=np.int64), out, chains,
+                                2, full, 21)
+    g.close()
 
 
 @pytest.mark.parametrize("L,chains,K", [(4, 17, 1), (9, 33, 2), (3, 1, 4)])
