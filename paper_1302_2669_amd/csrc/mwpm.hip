@@ -19,12 +19,14 @@
 //
 // One workgroup per syndrome.  Its two waves each solve one anyon type (both
 // parities, the second from the first's solution) with the whole solver state
-// in LDS (at large L one wave takes both types in turn), XOR their parts into
-// bit planes, and the workgroup packs the four class starts.  Up to three
-// launches by problem size (capacity tiers); the larger two, which hold few
-// syndromes but long solves, run on a side stream beside the first.
+// in LDS (at large L one wave takes both types in turn, in small batches four
+// waves take one problem each), XOR their parts into
+// bit planes, and the workgroup packs the four class starts.  Up to five
+// launches by problem size (capacity tiers); the largest two, which hold few
+// syndromes but long solves, run on a side stream beside the others.
 
 #include "device_common.h"
+#include "host_common.h"
 #include "internal.h"
 
 #define MW_FN __device__ __forceinline__
@@ -125,12 +127,24 @@ struct Wave64 {
   MW_FN void xor_word(uint32_t* p, uint32_t v) const { atomicXor(p, v); }
 };
 
-// waves per workgroup: one per anyon type when both states fit in 64 KB,
-// else one wave taking the types in turn
-int mwpm_waves(int cap) { return 2 * mw::region_bytes(cap) <= 64 * 1024 ? 2 : 1; }
+size_t mwpm_lds(int cap, int waves) {
+  return waves * mw::region_bytes(cap) + (4 * mw::ROWS + 4) * sizeof(uint32_t);
+}
 
-size_t mwpm_lds(int cap) {
-  return mwpm_waves(cap) * mw::region_bytes(cap) + (4 * mw::ROWS + 4) * sizeof(uint32_t);
+// Up to this many syndromes a wave takes one of the four problems: the batch
+// leaves the chip idle, and its time is that of a wave's problems in a row.
+// Types in turn and alone, us: L = 13, p = 0.15 170, 146 (1 syndrome), 319, 265
+// (256), 355, 294 (512); L = 25, p = 0.1 772, 671 (1), 1215, 1087 (256), but 1218,
+// 1684 (400), where the four states leave a compute unit one workgroup at a time.
+constexpr int64_t MWPM_ALONE_MAX = 512;
+
+// waves per workgroup: one per problem in small batches whose workgroups' four
+// states fit in the chip's LDS at once, else one per anyon type when both states
+// fit in 64 KB, else one wave taking the types in turn
+int mwpm_waves(int cap, int64_t n) {
+  const int64_t at_once = (int64_t)(160 * 1024 / (mwpm_lds(cap, 4) + 64)) * device_cus();
+  if (n <= MWPM_ALONE_MAX && n <= at_once) return 4;
+  return 2 * mw::region_bytes(cap) <= 64 * 1024 ? 2 : 1;
 }
 
 // Capacity of the first launch: two 64-vertex states and the planes take
@@ -162,7 +176,8 @@ __device__ __forceinline__ int max_vertices(int k) { return (k & 1) ? k + 3 : k 
 
 // Wave w solves anyon types w, w + waves (0 plaquettes / x parts, 1 stars /
 // z parts): parity 0 from the start, then parity 1 from parity 0's solution;
-// problem p = 2 type + parity paints plane p.  A launch takes the syndromes
+// ALONE: wave w solves type w / 2, parity w % 2 from the start (the optimum is
+// unique, so it is the same).  Problem p = 2 type + parity paints plane p.  A launch takes the syndromes
 // whose larger problem needs more than `lo` and at most `hi` vertices, in a
 // state sized for `cap`.  WPE is the register budget in waves per SIMD, U the
 // vertices a lane takes at once:
@@ -173,8 +188,8 @@ __device__ __forceinline__ int max_vertices(int k) { return (k & 1) ? k + 3 : k 
 //     U = 1, 3.2 with 2, 3.7 with 3);
 //   3, 3 (168 VGPRs) from MWPM_WIDE_CAP, whose LDS holds no more waves (4096 at
 //     L = 25, p = 0.1: 6.1, 5.9 and 5.5 ms).
-template <int WPE, int CAP, int U>
-__global__ void __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(WPE)))
+template <int WPE, int CAP, int U, bool ALONE>
+__global__ void __launch_bounds__(ALONE ? 256 : 128) __attribute__((amdgpu_waves_per_eu(WPE)))
 init_mwpm_kernel(const StartArgs a, int cap_arg, int waves, int lo, int hi) {
   // CAP != 0: the capacity as a compile-time constant, so that every solver
   // array sits at a constant offset from the wave's region
@@ -209,7 +224,12 @@ init_mwpm_kernel(const StartArgs a, int cap_arg, int waves, int lo, int hi) {
     mw::Solver<Wave64, U> m;
     m.wv.lane = threadIdx.x & 63;
     m.carve(mw_lds + wave * region, cap);
-    for (int t = wave; t < 2; t += waves) {
+    if constexpr (ALONE) {
+      m.load(si.sy, L, wave >= 2, wave & 1);
+      m.solve();
+      m.wv.sync();
+      m.paint(planes + wave * mw::ROWS, wave & 1);
+    } else for (int t = wave; t < 2; t += waves) {
       m.load(si.sy, L, t != 0, 0);
       m.solve();
       m.wv.sync();
@@ -259,20 +279,27 @@ namespace {
 
 constexpr int kMaxTiers = 5;
 
+// the capacity compiled in only where the launch's is exactly that one
+// (smaller codes have smaller single-tier capacities)
+template <bool ALONE>
+auto mwpm_kernel(int cap) {
+  return cap == MWPM_FAST_CAP  ? init_mwpm_kernel<7, MWPM_FAST_CAP, 1, ALONE>
+         : cap < MWPM_FAST_CAP ? init_mwpm_kernel<7, 0, 1, ALONE>
+         : cap < MWPM_WIDE_CAP ? init_mwpm_kernel<5, 0, 2, ALONE>
+                               : init_mwpm_kernel<3, 0, 3, ALONE>;
+}
+
 hipError_t launch_tier(const StartArgs& a, int cap, int lo, int hi, hipStream_t s) {
-  const size_t lds = mwpm_lds(cap);
-  // the capacity compiled in only where the launch's is exactly that one
-  // (smaller codes have smaller single-tier capacities)
-  auto* fn = cap == MWPM_FAST_CAP  ? init_mwpm_kernel<7, MWPM_FAST_CAP, 1>
-             : cap < MWPM_FAST_CAP ? init_mwpm_kernel<7, 0, 1>
-             : cap < MWPM_WIDE_CAP ? init_mwpm_kernel<5, 0, 2>
-                                   : init_mwpm_kernel<3, 0, 3>;
+  const int waves = mwpm_waves(cap, a.n);
+  const size_t lds = mwpm_lds(cap, waves);
+  auto* fn = waves == 4 ? mwpm_kernel<true>(cap) : mwpm_kernel<false>(cap);
   if (lds > 64 * 1024) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(fn, dim3((unsigned)a.n), dim3(128), lds, s, a, cap, mwpm_waves(cap), lo, hi);
+  hipLaunchKernelGGL(fn, dim3((unsigned)a.n), dim3(waves == 4 ? 256 : 128), lds, s, a, cap, waves,
+                     lo, hi);
   return hipGetLastError();
 }
 

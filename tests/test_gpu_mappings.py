@@ -203,3 +203,19 @@ def test_matching_tiers_of_large_batches():
             small = mc.init_representatives(syn[lo:lo + 512], L, mc.MCMC_INIT_MWPM)
             torch.cuda.synchronize()
             assert torch.equal(reps[lo:lo + 512], small), (L, lo)
+
+
+@pytest.mark.parametrize("L", [2, 5, 9, 13, 17, 21, 25])
+def test_matching_problems_alone(L):
+    # up to 512 syndromes (as many as the chip's LDS holds at once) every problem
+    # has its own wave: the same starts as in a larger batch, lit from none to all
+    n = 513
+    syn = torch.cat([mc.sample_errors(L, p, 8, 128)[0] for p in (0.02, 0.08, 0.16, 0.4)])
+    syn = torch.cat([syn, torch.ones_like(syn[:1])])
+    syn[0] = 0
+    reps = mc.init_representatives(syn, L, mc.MCMC_INIT_MWPM)
+    for lo, hi in ((0, 1), (0, 256), (256, 512), (512, 513), (1, 513)):
+        small = mc.init_representatives(syn[lo:hi].contiguous(), L, mc.MCMC_INIT_MWPM)
+        torch.cuda.synchronize()
+        assert torch.equal(reps[lo:hi], small), (lo, hi)
+    assert n == len(syn)
