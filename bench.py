@@ -516,7 +516,7 @@ def bench_gated(args, mc, torch, dev):
                            "plain_right_gated_wrong": b_dis, "plain_wrong_gated_right": c_dis,
                            "mcnemar_p": mcnemar, "routes": c})
         # the network alone over the evaluation batch: the fused inference
-        # kernel the gated decoder runs, and the layered training forward
+        # kernel the gated decoder runs, and the training forward, which stores its activations
         pe = torch.from_numpy(p_ev.astype(np.float32)).to(dev)
         stream = torch.cuda.current_stream(dev)
 
@@ -582,7 +582,7 @@ def bench_gated(args, mc, torch, dev):
                             "rule": "fastest decoder (plain included) within 2% relative "
                                     "logical error of plain"},
         "results": [uni, fix],
-        "roofline": {"bound": "mfma", "kernel": "infer_kernel (fused gate network inference)",
+        "roofline": {"bound": "mfma", "kernel": "forward_kernel (fused gate network inference)",
                      "achieved": flops_fwd / (uni["cnn_infer_ms"] * 1e-3) / 1e12,
                      "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": flops_fwd / (uni["cnn_infer_ms"] * 1e-3) / 1e12 / 2500.0,
@@ -759,7 +759,7 @@ def bench_spacetime(args, mc, torch, dev):
         "logical_error": {"rate": fails / total, "samples": total,
                           "last_round_only": last_fail / total},
         "roofline": {"bound": "alu",
-                     "kernel": (f"st_chain_fast_kernel<{Ls}>" if Ls <= 12 else
+                     "kernel": (f"st_chain_lanes_kernel<{Ls}>" if Ls <= 12 else
                                 f"st_chain_win_kernel<{Ls}>") + " (space-time chains)",
                      "achieved": achieved, "peak": PEAK_INT_OPS / 1e12, "unit": "Tops/s",
                      "frac": achieved / (PEAK_INT_OPS / 1e12), "traffic": None,
