@@ -8,7 +8,7 @@
 // Mapping.  One lane per chain as in the colour-phased kernels, but a random
 // site needs its rows by a runtime index, so each lane's configuration lives
 // in LDS, one word (L <= 15) or one 64-bit word per grid row, row-major with
-// the wave's 64 lanes side by side (no bank conflicts).  A site touches one
+// the lanes side by side (no bank conflicts).  A site touches one
 // qubit of the row above, two neighbouring ones of its own row and one of the
 // row below: three reads at one address with fixed offsets.  To make that hold
 // at the boundaries there is a padding row above and below, and odd rows are
@@ -34,13 +34,24 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "device_common.h"
+#include "host_common.h"
 #include "internal.h"
 
 namespace mcmc {
 namespace {
 
-constexpr int RS_LANES = 64;
+// Four waves share a site table, their lanes side by side in the rows: a wave on
+// every SIMD of a compute unit.  Smaller workgroups are not spread evenly over the
+// SIMDs: with one wave each the first launch above took 11.6 ms and the others
+// 8.06, with two each all of them 11.6; 40000 x 16 chains x 10 sweeps 4.08 ms with
+// one, 2.93 with four.  Where four waves' rows leave a compute unit fewer waves
+// than single ones do (L = 19 to 22), full batches take those, and so do batches
+// of at most one wave per compute unit, whose LDS each then has to itself (16000
+// chains at L = 17: 1.99 ms, 2.05 with four).
+constexpr int RS_WAVES = 4;
 // steps per batch: two Philox blocks; n_stab = 2 L (L - 1) is a multiple of 4
 constexpr int RS_BATCH = 4;
 // codes with one 32-bit word per row, the field past an odd row's end included
@@ -56,14 +67,14 @@ struct RowWord<true> {
 };
 
 // Table entry of a site (center row r, first field j of the row's pair):
-//   x: bits 0-5 shift of the pair (2 j), 8-14 (narrow) or 9-14 (wide) row
-//      offset in LDS (r 256 or r 512 bytes, the row above), 16-21 shift of
-//      the fields above and below;
+//   x: bits 0-5 shift of the pair (2 j), then the row's offset in LDS (the row
+//      above: r times the workgroup's lanes and 4 or 8 bytes, up to bit 15 narrow
+//      or 16 wide), from bit 16 or 17 on the shift of the fields above and below;
 //   y: bits 0-5 and 8-13 the same shifts plus the flipped part's bit t (0:
 //      x, star; 1: z, plaquette), 16-20 2 - 2t, 24-31 the flipped part's bits
 //      of the four gathered codes (missing neighbours left out under
 //      bit/phase flips, where their padding would count).
-template <int NOISE, bool WIDE>
+template <int NOISE, bool WIDE, int LANES>
 __device__ uint2 site_entry(int L, int s) {
   const int nstar = L * (L - 1);
   const bool star = s < nstar;
@@ -80,7 +91,8 @@ __device__ uint2 site_entry(int L, int s) {
     if (!star && i == L - 1) own &= ~0x0Cu;
   }
   uint2 e;
-  e.x = (uint32_t)pair | ((uint32_t)(r * (WIDE ? 512 : 256))) | ((uint32_t)single << 16);
+  e.x = (uint32_t)pair | ((uint32_t)(r * LANES * (WIDE ? 8 : 4))) |
+        ((uint32_t)single << (WIDE ? 17 : 16));
   e.y = (uint32_t)(pair + t) | ((uint32_t)(single + t) << 8) | ((uint32_t)(2 - 2 * t) << 16) |
         (own << 24);
   return e;
@@ -116,10 +128,14 @@ struct Step {
   int32_t q;
 };
 
-template <int NOISE, bool WIDE>
-__global__ void __launch_bounds__(RS_LANES) __attribute__((amdgpu_waves_per_eu(4)))
+template <int NOISE, bool WIDE, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4)))
 chains_random_kernel(const RunArgs a) {
   using Row = typename RowWord<WIDE>::type;
+  constexpr int RS_LANES = 64 * WAVES;
+  constexpr uint32_t kSingle = WIDE ? 17 : 16;
+  constexpr uint32_t kRowMask =
+      ((1u << kSingle) - 1u) & ~(uint32_t)(RS_LANES * sizeof(Row) - 1);
   extern __shared__ __align__(16) uint32_t rs_lds[];
   const GroupDesc g = a.g0;
   const int L = g.L;
@@ -130,7 +146,7 @@ chains_random_kernel(const RunArgs a) {
   const int lane = threadIdx.x;
   Row* rows = reinterpret_cast<Row*>(rs_lds);   // [R + 2][RS_LANES], aligned as a row offset
   uint2* sites = reinterpret_cast<uint2*>(rows + (R + 2) * RS_LANES);
-  for (int s = lane; s < nstab; s += RS_LANES) sites[s] = site_entry<NOISE, WIDE>(L, s);
+  for (int s = lane; s < nstab; s += RS_LANES) sites[s] = site_entry<NOISE, WIDE, RS_LANES>(L, s);
   __syncthreads();
 
   const int64_t t = (int64_t)blockIdx.x * RS_LANES + lane;
@@ -222,7 +238,7 @@ chains_random_kernel(const RunArgs a) {
 #pragma unroll
       for (int k = 0; k < RS_BATCH; ++k) {
         const uint2 e = slot[k].site;
-        const LdsRow p = (LdsRow)(uintptr_t)((e.x & (WIDE ? 0x7E00u : 0x7F00u)) | column);
+        const LdsRow p = (LdsRow)(uintptr_t)((e.x & kRowMask) | column);
         const Row up = p[0], mid = p[RS_LANES], down = p[2 * RS_LANES];
         __builtin_amdgcn_sched_barrier(0);
         // while they arrive: half a block, and the slot that is free again
@@ -243,12 +259,12 @@ chains_random_kernel(const RunArgs a) {
         // the four codes: above, below, the pair
         uint32_t code;
         if constexpr (WIDE) {
-          const uint32_t single = e.x >> 16;
+          const uint32_t single = e.x >> kSingle;
           code = (((uint32_t)(mid >> (e.x & kShift)) & 15u) << 2) |
                  ((uint32_t)(down >> (single & kShift)) & 3u);
           code = (code << 2) | ((uint32_t)(up >> (single & kShift)) & 3u);
         } else {
-          const uint32_t single = e.x >> 16;
+          const uint32_t single = e.x >> kSingle;
           code = (__builtin_amdgcn_ubfe(mid, e.x, 4) << 2) | __builtin_amdgcn_ubfe(down, single, 2);
           code = (code << 2) | __builtin_amdgcn_ubfe(up, single, 2);
         }
@@ -291,31 +307,46 @@ chains_random_kernel(const RunArgs a) {
   }
 }
 
-template <int NOISE, bool WIDE>
-hipError_t launch_random(const RunArgs& a, unsigned blocks, size_t lds, hipStream_t s) {
-  hipLaunchKernelGGL((chains_random_kernel<NOISE, WIDE>), dim3(blocks), dim3(RS_LANES), lds, s, a);
+size_t random_scan_lds_bytes(int L, int waves) {
+  const size_t row = L <= RS_NARROW_L_MAX ? 4 : 8;
+  return (size_t)(2 * L * (L - 1)) * sizeof(uint2) + (size_t)(2 * L + 1) * 64 * waves * row;
+}
+
+template <int NOISE, bool WIDE, int WAVES>
+hipError_t launch_random(const RunArgs& a, hipStream_t s) {
+  auto* fn = chains_random_kernel<NOISE, WIDE, WAVES>;
+  const int64_t blocks = (a.g0.n_tasks + 64 * WAVES - 1) / (64 * WAVES);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  const size_t lds = random_scan_lds_bytes(a.g0.L, WAVES);
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(fn, dim3((unsigned)blocks), dim3(64 * WAVES), lds, s, a);
   return hipGetLastError();
+}
+
+template <int WAVES>
+hipError_t launch_random_waves(const RunArgs& a, hipStream_t s) {
+  const bool wide = a.g0.L > RS_NARROW_L_MAX;
+  if (a.noise == MCMC_NOISE_BITPHASE)
+    return wide ? launch_random<1, true, WAVES>(a, s) : launch_random<1, false, WAVES>(a, s);
+  return wide ? launch_random<0, true, WAVES>(a, s) : launch_random<0, false, WAVES>(a, s);
 }
 
 }  // namespace
 
-size_t random_scan_lds_bytes(int L) {
-  const size_t row = L <= RS_NARROW_L_MAX ? 4 : 8;
-  return (size_t)(2 * L * (L - 1)) * sizeof(uint2) + (size_t)(2 * L + 1) * RS_LANES * row;
-}
-
 hipError_t launch_chains_random(const RunArgs& a, hipStream_t s) {
-  const int64_t T = a.g0.n_tasks;
-  if (T == 0) return hipSuccess;
-  const int64_t blocks = (T + RS_LANES - 1) / RS_LANES;
-  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  const size_t lds = random_scan_lds_bytes(a.g0.L);
-  const bool wide = a.g0.L > RS_NARROW_L_MAX;
-  if (a.noise == MCMC_NOISE_BITPHASE)
-    return wide ? launch_random<1, true>(a, (unsigned)blocks, lds, s)
-                : launch_random<1, false>(a, (unsigned)blocks, lds, s);
-  return wide ? launch_random<0, true>(a, (unsigned)blocks, lds, s)
-              : launch_random<0, false>(a, (unsigned)blocks, lds, s);
+  if (a.g0.n_tasks == 0) return hipSuccess;
+  // waves that a compute unit's LDS holds at once in workgroups of four or one
+  const size_t lds = 160 * 1024;
+  const int64_t fours = RS_WAVES * (int64_t)(lds / random_scan_lds_bytes(a.g0.L, RS_WAVES));
+  const int64_t ones = (int64_t)(lds / random_scan_lds_bytes(a.g0.L, 1));
+  const int64_t waves = (a.g0.n_tasks + 63) / 64, cus = device_cus();
+  if (waves > cus && (fours >= std::min<int64_t>(ones, 16) || waves <= fours * cus))
+    return launch_random_waves<RS_WAVES>(a, s);
+  return launch_random_waves<1>(a, s);
 }
 
 }  // namespace mcmc

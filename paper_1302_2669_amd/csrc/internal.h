@@ -98,7 +98,7 @@ struct RunArgs {
 };
 
 // Persistent chain kernels, one per L range, each with the register budget
-// of its largest code: L 2..13 (6 waves per SIMD), 14..16 (5), and the
+// of its largest code: L 2..13 and 14..16 (5 waves per SIMD), and the
 // two-word-row ranges 17..19, 20..22, 23..25 (3).  `waves` is the persistent
 // grid in waves, `wg` the workgroup size (64, 128 or 256).
 constexpr int N_RANGES = 5;
@@ -137,9 +137,8 @@ hipError_t launch_chains_split_flip(const RunArgs& a, bool wide, int waves, hipS
 constexpr int LONE_L_MIN = 6;
 hipError_t launch_chains_lone(const RunArgs& a, hipStream_t s);
 // Random-scan chains of a uniform batch (g0, table0, a.noise; no trace):
-// one 64-lane workgroup per 64 chains, each lane's state in LDS.
+// one lane per chain, each lane's state in LDS.
 hipError_t launch_chains_random(const RunArgs& a, hipStream_t s);
-size_t random_scan_lds_bytes(int L);
 hipError_t launch_zero(uint32_t* p, int64_t n, hipStream_t s);
 
 // Class starts of syndromes given either implicitly (L, n: syndrome s at

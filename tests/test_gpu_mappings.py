@@ -219,3 +219,18 @@ def test_matching_problems_alone(L):
         torch.cuda.synchronize()
         assert torch.equal(reps[lo:hi], small), (lo, hi)
     assert n == len(syn)
+
+
+# random scan in workgroups of four waves, and of one where those hold more
+# waves (full batches from L = 19 on): one sweep against a small batch's
+@pytest.mark.parametrize("L,n,chains,noise", [(13, 65, 4, 1), (18, 65, 4, 0), (19, 1200, 55, 0),
+                                              (22, 1100, 60, 1)])
+def test_random_scan_workgroups(L, n, chains, noise):
+    syn, _, _ = mc.sample_errors(L, 0.08, 13, n, noise=noise)
+    args = dict(chains=chains, noise=noise, random_scan=True, want_sums=True)
+    big = to_np(mc.decode_batch(syn, L, 0.08, 1, 13, **args))
+    lo = n - 20
+    small = to_np(mc.decode_batch(syn[lo:].contiguous(), L, 0.08, 1, 13,
+                                  syndrome_ids=torch.arange(lo, n), **args))
+    for k in small:
+        assert np.array_equal(big[k][lo:], small[k]), k
