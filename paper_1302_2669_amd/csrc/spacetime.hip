@@ -25,7 +25,7 @@
 // run in the exact sequential order above, so the chains are bit-identical to
 // a sequential implementation.
 //
-// For L <= ST_FAST_L_MAX and up to 16 rounds every interval of a chain sits on a
+// For L <= ST_LANES_L_MAX and up to 16 rounds every interval of a chain sits on a
 // lane of its own, whole in registers (spacetime_lanes.h); the kernels here and
 // in spacetime_win.h take the rest.  For L <= ST_FAST_L_MAX with more rounds (or
 // thresholds at the top of the 32-bit range) a kernel templated on L keeps the
@@ -374,8 +374,9 @@ hipError_t dispatch_fast(const SpaceTimeArgs& a, hipStream_t s) {
 hipError_t launch_spacetime_chains(const SpaceTimeArgs& a, hipStream_t s) {
   if (a.n_tasks == 0) return hipSuccess;
   if (spacetime_lanes_take(a))
-    return a.L <= ST_LANES_SMALL_L_MAX ? launch_spacetime_lanes_small(a, s)
-                                       : launch_spacetime_lanes_large(a, s);
+    return a.L <= ST_LANES_SMALL_L_MAX   ? launch_spacetime_lanes_small(a, s)
+           : a.L <= ST_LANES_LARGE_L_MAX ? launch_spacetime_lanes_large(a, s)
+                                         : launch_spacetime_lanes_largest(a, s);
   if (a.L <= ST_FAST_L_MAX) return dispatch_fast<2>(a, s);
   return dispatch_window<SPACETIME_WIN_L_MIN>(a, s);
 }

@@ -1,5 +1,5 @@
 // Space-time chains with one lane per interval (Sec. VI), codes up to
-// SPACETIME_FAST_L_MAX and at most ST_LANES_T_MAX rounds.  Same moves, order
+// ST_LANES_L_MAX and at most ST_LANES_T_MAX rounds.  Same moves, order
 // and draws as the register-interval kernel of spacetime.hip, so the chains
 // are bit-identical.
 //
@@ -36,7 +36,12 @@
 // positions between groups so that the bit indices stay constants.  L = 7, 2048
 // histories of 7 rounds, 4 chains, 784 sweeps: 204 ms one lane per chain, 43.4
 // ms here (63 of 64 lanes, 3.56 waves per SIMD).  Unrolled, 300 histories of 12
-// rounds at L = 12 take 6.7 ms, rolled 4.7; 1000 of 9 rounds at L = 9 5.7, 5.5.
+// rounds at L = 12 take 6.7 ms, rolled 4.7; 1000 of 9 rounds at L = 9 5.7, 5.5.  At L = 13
+// to 15 the spatial half alone outgrows the cache (100 KB of code and more) and
+// some registers spill, yet it beats the streaming window of spacetime_win.h at
+// every batch: 60 histories of 13 rounds at L = 13, 145 sweeps, 260 ms there, 13
+// here; 3000 of 14 at L = 14 8.2, 2.9; 16000 of 9 at L = 15 11.3, 7.6; 30000 of 3
+// at L = 13 7.0, 5.4 (with 3 waves per SIMD and fewer spills 13, 2.9, 8.0, 5.5).
 #pragma once
 
 #include "spacetime_common.h"
@@ -49,8 +54,9 @@ constexpr int ST_LANES_T_MAX = 16;
 // not "always" reach 2^32 - 1 (see above) or T is larger.
 bool spacetime_lanes_take(const SpaceTimeArgs& a);
 hipError_t launch_spacetime_lanes_small(const SpaceTimeArgs& a, hipStream_t s);   // L <= 9
-hipError_t launch_spacetime_lanes_large(const SpaceTimeArgs& a, hipStream_t s);
-constexpr int ST_LANES_SMALL_L_MAX = 9;
+hipError_t launch_spacetime_lanes_large(const SpaceTimeArgs& a, hipStream_t s);   // L <= 12
+hipError_t launch_spacetime_lanes_largest(const SpaceTimeArgs& a, hipStream_t s);
+constexpr int ST_LANES_SMALL_L_MAX = 9, ST_LANES_LARGE_L_MAX = 12, ST_LANES_L_MAX = 15;
 
 namespace {
 

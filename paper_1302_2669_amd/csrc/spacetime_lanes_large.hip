@@ -4,7 +4,7 @@
 namespace mcmc {
 
 hipError_t launch_spacetime_lanes_large(const SpaceTimeArgs& a, hipStream_t s) {
-  return dispatch_lanes<ST_LANES_SMALL_L_MAX + 1, SPACETIME_FAST_L_MAX>(a, s);
+  return dispatch_lanes<ST_LANES_SMALL_L_MAX + 1, ST_LANES_LARGE_L_MAX>(a, s);
 }
 
 }  // namespace mcmc

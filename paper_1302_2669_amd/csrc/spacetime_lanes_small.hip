@@ -8,7 +8,7 @@ hipError_t launch_spacetime_lanes_small(const SpaceTimeArgs& a, hipStream_t s) {
 }
 
 bool spacetime_lanes_take(const SpaceTimeArgs& a) {
-  if (a.L > SPACETIME_FAST_L_MAX || a.T > ST_LANES_T_MAX) return false;
+  if (a.L > ST_LANES_L_MAX || a.T > ST_LANES_T_MAX) return false;
   if (a.sp_thr[0] == 0xFFFFFFFFu) return false;
   for (int e = 0; e < 25; ++e)
     if (!((a.t_always >> e) & 1u) && a.t_thr[e] == 0xFFFFFFFFu) return false;

@@ -174,12 +174,14 @@ def test_estimator_full_batches():
             assert np.array_equal(big[k][lo:lo + 1000], small[k]), k
 
 
-# space-time chains, one lane per interval up to L = 12 and 16 rounds: the skew
+# space-time chains, one lane per interval up to L = 15 and 16 rounds: the skew
 # spans two words from round 8 on, lanes are left over where T does not divide
 # 64, and 17 rounds fall back to one lane per chain
 @pytest.mark.parametrize("L,T,n,chains", [(2, 16, 3, 3), (3, 9, 2, 4), (5, 8, 2, 2), (6, 7, 3, 1),
                                           (7, 7, 3, 2), (8, 16, 1, 1), (9, 13, 1, 1), (10, 5, 1, 2),
-                                          (12, 16, 1, 1), (4, 17, 2, 1), (9, 1, 5, 3)])
+                                          (12, 16, 1, 1), (4, 17, 2, 1), (9, 1, 5, 3),
+                                          (13, 16, 1, 1), (14, 9, 2, 1), (15, 2, 3, 2),
+                                          (15, 16, 1, 1), (16, 3, 1, 1)])
 def test_spacetime_lanes(L, T, n, chains):
     p, pm, sweeps = 0.06, 0.09, 3 if L < 8 else 2
     obs, _, _, _ = stm.sample(geometry.Lattice(L), p, pm, T, SEED_L9 + L, np.arange(n))
