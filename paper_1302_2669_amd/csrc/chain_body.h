@@ -80,15 +80,27 @@ __device__ __forceinline__ uint32_t c_plaq_of(uint32_t v) {
   else return c_plaq(v);
 }
 
-// u >= thr ? bit : 0: one compare and one select, both in their short (4-byte)
-// encodings, which issue faster than the 8-byte ones; so `bit` sits in a VGPR.
+// u >= thr ? bit : 0.  A mask (VCC or an SGPR pair) is not read before the third
+// instruction after the VALU one that writes it: the compiler sees to that in its
+// own code, an asm statement has to do it itself.
 __device__ __forceinline__ uint32_t reject_bit(uint32_t u, uint32_t thr, uint32_t bit) {
-  uint32_t r;
-  asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_cndmask_b32 %0, 0, %3, vcc"
-      : "=v"(r)
-      : "v"(u), "v"(thr), "v"(bit)
+  return u >= thr ? bit : 0u;
+}
+// Two sites at once, one wait state left to fill.  For L >= 23: there the plain
+// form costs 8 to 10% at L = 25 (registers; 589824 chains x 24 sweeps 10.8 ms, in
+// pairs 9.6), while below pairs cost up to 3% (two of the four instructions take 8
+// bytes; 320000 chains x 72 sweeps at L = 17 12.4 and 12.9 ms).
+constexpr int REJECT_PAIR_L_MIN = 23;
+__device__ __forceinline__ uint32_t reject_pair(uint32_t u0, uint32_t thr0, uint32_t bit0,
+                                                uint32_t u1, uint32_t thr1, uint32_t bit1) {
+  uint32_t r0, r1;
+  uint64_t mask;
+  asm("v_cmp_ge_u32 vcc, %3, %4\n\tv_cmp_ge_u32 %2, %6, %7\n\ts_nop 0\n\t"
+      "v_cndmask_b32 %0, 0, %5, vcc\n\tv_cndmask_b32 %1, 0, %8, %2"
+      : "=&v"(r0), "=&v"(r1), "=&s"(mask)
+      : "v"(u0), "v"(thr0), "v"(bit0), "v"(u1), "v"(thr1), "v"(bit1)
       : "vcc");
-  return r;
+  return r0 | r1;
 }
 
 // Top bits of the nibbles of the sites of one row in word w: sites j = par,
@@ -254,7 +266,8 @@ __device__ __forceinline__ void run_chain(const RunArgs& a, const GroupDesc& g, 
       constexpr int par = decltype(PAR)::value, nsite = decltype(NSITE)::value;
       constexpr int d0 = decltype(D0)::value, limit = decltype(LIMIT)::value;
       uint32_t rej[W];
-      uint32_t held = 0;   // the even site's bit, until its pair's joins it
+      uint32_t held = 0;   // the even site's bit (or its draw), until its pair's joins it
+      [[maybe_unused]] uint32_t held_thr = 0;
       static_for<W>([&](auto WW) { rej[decltype(WW)::value] = 0; });
       static_for<nsite>([&](auto MM) {
         constexpr int m = decltype(MM)::value;
@@ -284,14 +297,24 @@ __device__ __forceinline__ void run_chain(const RunArgs& a, const GroupDesc& g, 
         if constexpr ((d & 3) == 0) blk = rng.template block<d / 4>();
 #endif
         const uint32_t thr = lds_tbl[(sum[w] >> (4 * nib)) & 15u][lane];
-        const uint32_t r = reject_bit(word_of(blk, d & 3), thr, site_bit[nib]);
+        const uint32_t u = word_of(blk, d & 3);
         if constexpr (nib % 2 == 0 && m + 1 < nsite) {
-          held = r;
+          if constexpr (L >= REJECT_PAIR_L_MIN) {
+            held = u;
+            held_thr = thr;
+          } else {
+            held = reject_bit(u, thr, site_bit[nib]);
+          }
         } else if constexpr (nib % 2 == 1 && m > 0) {
-          if constexpr (nib == 1) rej[w] = held | r;
-          else rej[w] = rej[w] | held | r;
+          uint32_t r;
+          if constexpr (L >= REJECT_PAIR_L_MIN)
+            r = reject_pair(held, held_thr, site_bit[nib - 1], u, thr, site_bit[nib]);
+          else
+            r = held | reject_bit(u, thr, site_bit[nib]);
+          if constexpr (nib == 1) rej[w] = r;
+          else rej[w] |= r;
         } else {
-          rej[w] = rej[w] | r;
+          rej[w] |= reject_bit(u, thr, site_bit[nib]);
         }
       });
       static_for<W>([&](auto WW) {

@@ -108,14 +108,18 @@ __device__ __forceinline__ uint4 keyed_round(uint4 c, uint32_t k0, uint32_t k1) 
   return make_uint4(bitop3<0x96>(h1, c.y, k0), l1, bitop3<0x96>(h0, c.w, k1), l0);
 }
 
-// How many of the four thresholds u stays below.
+// How many of the four thresholds u stays below.  A mask (VCC or an SGPR pair) is
+// read from the third instruction after the one that writes it, at the earliest:
+// the other compares and adds fill that gap (8.23 ms on the launch above; with wait
+// states 9.18, as the compiler orders it 8.91).
 __device__ __forceinline__ int32_t count_below(uint32_t u, const uint32_t thr[4]) {
   int32_t q;
-  asm("v_cmp_lt_u32 vcc, %1, %2\n\tv_cndmask_b32 %0, 0, 1, vcc\n\t"
-      "v_cmp_lt_u32 vcc, %1, %3\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
-      "v_cmp_lt_u32 vcc, %1, %4\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
-      "v_cmp_lt_u32 vcc, %1, %5\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
-      : "=&v"(q)
+  uint64_t m0, m1;
+  asm("v_cmp_lt_u32 vcc, %3, %4\n\tv_cmp_lt_u32 %1, %3, %5\n\t"
+      "v_cmp_lt_u32 %2, %3, %6\n\tv_cndmask_b32 %0, 0, 1, vcc\n\t"
+      "v_cmp_lt_u32 vcc, %3, %7\n\tv_addc_co_u32 %0, %1, 0, %0, %1\n\t"
+      "v_addc_co_u32 %0, %2, 0, %0, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
+      : "=&v"(q), "=&s"(m0), "=&s"(m1)
       : "v"(u), "v"(thr[0]), "v"(thr[1]), "v"(thr[2]), "v"(thr[3])
       : "vcc");
   return q;

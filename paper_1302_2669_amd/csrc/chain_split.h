@@ -56,14 +56,41 @@ __device__ __forceinline__ uint32_t lane_below(uint32_t v, uint32_t edge) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, 0x138, 0xf, 0xf, false);
 }
 
-// acc + (u >= thr).
-__device__ __forceinline__ uint32_t count_reached(uint32_t acc, uint32_t u, uint32_t thr) {
-  asm("v_cmp_ge_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
-      : "+v"(acc)
-      : "v"(u), "v"(thr)
-      : "vcc");
+// acc plus how many of the four thresholds u reaches.  A mask (VCC or an SGPR pair)
+// is read from the third instruction after the VALU one that writes it, at the
+// earliest.  FILLED: other compares and adds fill that gap, four of the eight
+// instructions in their 8-byte encoding; else one mask beside VCC and a few wait
+// states, which other waves' instructions fill.  Measured against a gap left open:
+// 16 x 1000 syndromes at L = 3 0.96 of the time, 4001 x 16 chains at L = 13, 17 and
+// 25 with flips 1.03, 1.05, 1.03 filled and 1.01, 1.02, 0.99 with waits, 200 x 16
+// at L = 13 0.98 and 1.02 (wait states alone: 1.10 there, 0.98 at 4001).
+template <bool FILLED>
+__device__ __forceinline__ uint32_t count_reached(uint32_t acc, uint32_t u,
+                                                  const uint32_t (&thr)[4]) {
+  uint64_t m0;
+  if constexpr (FILLED) {
+    uint64_t m1;
+    asm("v_cmp_ge_u32 vcc, %3, %4\n\tv_cmp_ge_u32 %1, %3, %5\n\t"
+        "v_cmp_ge_u32 %2, %3, %6\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+        "v_cmp_ge_u32 vcc, %3, %7\n\tv_addc_co_u32 %0, %1, 0, %0, %1\n\t"
+        "v_addc_co_u32 %0, %2, 0, %0, %2\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
+        : "+&v"(acc), "=&s"(m0), "=&s"(m1)
+        : "v"(u), "v"(thr[0]), "v"(thr[1]), "v"(thr[2]), "v"(thr[3])
+        : "vcc");
+  } else {
+    asm("v_cmp_ge_u32 vcc, %2, %3\n\tv_cmp_ge_u32 %1, %2, %4\n\ts_nop 0\n\t"
+        "v_addc_co_u32 %0, vcc, 0, %0, vcc\n\tv_cmp_ge_u32 vcc, %2, %5\n\t"
+        "v_addc_co_u32 %0, %1, 0, %0, %1\n\ts_nop 0\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc\n\t"
+        "v_cmp_ge_u32 vcc, %2, %6\n\ts_nop 1\n\tv_addc_co_u32 %0, vcc, 0, %0, vcc"
+        : "+&v"(acc), "=&s"(m0)
+        : "v"(u), "v"(thr[0]), "v"(thr[1]), "v"(thr[2]), "v"(thr[3])
+        : "vcc");
+  }
   return acc;
 }
+// The filled form where a wave waits for itself: one chain per wave, and the codes
+// whose few draws leave waves idle (up to L = 9 it also wins in full batches).
+constexpr int FILLED_L_MAX = 9;
 
 // G lanes per chain: its rows on the first L, its draws on all of them.
 template <int L, int G>
@@ -179,7 +206,7 @@ __device__ __forceinline__ void run_split(const RunArgs& a, const GroupDesc& g, 
       static_for<4>([&](auto DD) {
         constexpr int d = 3 - decltype(DD)::value;
         if constexpr (d < 3) q <<= 4;
-        static_for<4>([&](auto TT) { q = count_reached(q, word_of(v, d), thr[decltype(TT)::value]); });
+        q = count_reached<G == 64 || L <= FILLED_L_MAX>(q, word_of(v, d), thr);
       });
       drawn[G * k] = (uint16_t)q;
     });
