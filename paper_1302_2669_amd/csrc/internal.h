@@ -159,18 +159,19 @@ hipError_t launch_init(const StartArgs& a, hipStream_t s);
 hipError_t launch_init_matching(const StartArgs& a, hipStream_t s);
 // Exact minimum-weight matching starts (MCMC_INIT_MWPM): one workgroup per
 // syndrome, dynamic LDS sized for the largest L.  The launches of the larger
-// capacities go to a per-device side stream forked from and joined to s; the
-// first call on a device that is not capturing creates it when may_create
-// (callers that must not create runtime objects pass false: then, as under a
-// capture before the stream exists, every launch goes to s in order).
+// capacities go to a side stream forked from and joined to s, which a call that
+// is not capturing may create when may_create (callers that must not create
+// runtime objects pass false).  Where there is none free every launch goes to s
+// in order.
 hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create = true);
-// Creates the current device's side stream now (for callers that may only
-// launch inside a capture).
+// Creates a side stream on the current device if it has none (for callers that
+// may only launch inside a capture).
 hipError_t prepare_side_stream();
-// The current device's side stream, held by one caller at a time: fork() makes
-// it follow what s holds, join() makes s follow it.  stream() is null where
-// there is none: not creatable, another caller's capture holds it, or s is
-// being captured and in_capture is false.
+// A side stream of the current device for a caller on s: fork() makes it follow
+// what s holds, join() makes s follow it (the destructor does if the caller did
+// not).  Never one that other streams' work or another capture still holds;
+// stream() is null where there is none free, none may be created, or s is being
+// captured and in_capture is false.
 class SideStream {
  public:
   SideStream(hipStream_t s, bool may_create, bool in_capture);
@@ -184,6 +185,7 @@ class SideStream {
  private:
   hipStream_t s_, side_ = nullptr;
   hipEvent_t fork_ = nullptr, join_ = nullptr;
+  bool forked_ = false;
 };
 // The start kernel of an MCMC_INIT_* mode.
 hipError_t launch_init_mode(uint32_t init, const StartArgs& a, hipStream_t s,

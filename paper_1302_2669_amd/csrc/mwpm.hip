@@ -335,7 +335,7 @@ hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create) 
   // syndromes at L = 15 take 1.16 ms instead of 0.92); the smaller ones, largest
   // first, on s; without a side stream, in order on s
   hipError_t e = hipSuccess;
-  SideStream side(s, may_create, true);
+  SideStream side(s, may_create, true);   // joined on every return
   if (side.stream()) {
     if ((e = side.fork()) != hipSuccess) return e;
     const int first_aside = full > mid ? nt - 2 : nt - 1;
