@@ -270,10 +270,9 @@ hipError_t launch_sample_items(const ItemDesc* items, const GroupDesc* groups, i
                                hipStream_t s);
 
 // ---- imperfect measurements (space-time hypotheses) ---------------------------
-// LDS of one 64-chain workgroup of the space-time kernel (lattice tables)
-// must stay within this.
-// Codes up to this L run the register-interval kernel, larger ones the
-// streaming-window kernel (spacetime_win.h, one translation unit per L).
+// Chains that do not run one lane per interval (spacetime_lanes.h): codes up to
+// this L in the register-interval kernel, larger ones in the streaming-window
+// kernel (spacetime_win.h, one translation unit per L).
 constexpr int SPACETIME_FAST_L_MAX = 12;
 constexpr int SPACETIME_WIN_L_MIN = SPACETIME_FAST_L_MAX + 1;
 constexpr int SPACETIME_WIN_L_MAX = MCMC_L_MAX;

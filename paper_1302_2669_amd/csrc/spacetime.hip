@@ -27,8 +27,9 @@
 //
 // For L <= ST_LANES_L_MAX and up to 16 rounds every interval of a chain sits on a
 // lane of its own, whole in registers (spacetime_lanes.h); the kernels here and
-// in spacetime_win.h take the rest.  For L <= ST_FAST_L_MAX with more rounds (or
-// thresholds at the top of the 32-bit range) a kernel templated on L keeps the
+// in spacetime_win.h take the rest.  For L <= ST_FAST_L_MAX with more rounds, in
+// full batches of small codes (spacetime_choice.h) or with thresholds at the top of
+// the 32-bit range a kernel templated on L keeps the
 // words of the current interval (spatial half) or of intervals t, t+1 and round t's
 // outcomes (time half) in registers, where every qubit, site and stabilizer
 // index is a compile-time constant; the buffer is then read and written once

@@ -51,7 +51,8 @@ namespace mcmc {
 constexpr int ST_LANES_T_MAX = 16;
 
 // The chains of an L in this family's range; false where thresholds that are
-// not "always" reach 2^32 - 1 (see above) or T is larger.
+// not "always" reach 2^32 - 1 (see above), T is larger, or one lane per chain is
+// faster (spacetime_choice.h).
 bool spacetime_lanes_take(const SpaceTimeArgs& a);
 hipError_t launch_spacetime_lanes_small(const SpaceTimeArgs& a, hipStream_t s);   // L <= 9
 hipError_t launch_spacetime_lanes_large(const SpaceTimeArgs& a, hipStream_t s);   // L <= 12
