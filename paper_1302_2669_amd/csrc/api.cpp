@@ -248,7 +248,7 @@ static hipError_t launch_both(const RunArgs& a, int h, SideStream& side, hipStre
   lanes.n_tiles = (int64_t)h * 4 * cus;
   rest.split_from = lanes.n_tiles * TILE;
   rest.n_tiles = (a.g0.n_tasks - rest.split_from + split_tile(L) - 1) / split_tile(L);
-  rest.queue = a.queue + 1;
+  rest.queue = a.queue + kQueueRest;
   const int64_t waves = std::min<int64_t>(lanes.n_tiles, default_waves(range, cus));
   const int64_t split_waves = std::min<int64_t>(rest.n_tiles, (int64_t)cus * 4 * SPLIT_WAVES);
   hipError_t e = side.fork();

@@ -649,7 +649,7 @@ int gated_decode_device(mcmc_gated* g, const float* d_params, const uint8_t* d_s
   const int64_t waves = std::min<int64_t>(max_tiles, (int64_t)device_cus() * 4 * RANGE_WAVES[r]);
   // the chains that the plan splits run beside the others
   RunArgs rest = a;
-  rest.queue = queue + N_RANGES;
+  rest.queue = queue + kQueueRest;
   rest.n_tiles = (n * per_item + split_tile(c.L) - 1) / split_tile(c.L);   // at most
   const int split_waves =
       (int)std::min<int64_t>(rest.n_tiles, (int64_t)device_cus() * 4 * SPLIT_WAVES);

@@ -12,11 +12,15 @@ namespace mcmc {
 
 constexpr size_t kAlign = 256;
 
-// Tile-queue counters at the head of every workspace, one per chain kernel
-// range; all of them are zeroed before each launch sequence.
+// Tile-queue counters at the head of every workspace, one per launch of a chain
+// kernel; all of them are zeroed before each launch sequence.  A plan's: kernel
+// range r under noise model m at m N_RANGES + r, then the pair launches by noise
+// model, then the split ones by noise model and row width.  A uniform batch and a
+// gated decode have one range, and their split rest at kQueueRest.
 constexpr int kQueueSlots = 16;
-static_assert(kQueueSlots >= 2 * N_RANGES + 2,
-              "one queue counter per kernel range and noise model, and per pair launch");
+constexpr int kQueueRest = N_RANGES;
+constexpr int kQueuePair = 2 * N_RANGES, kQueueSplit = kQueuePair + 2;
+static_assert(kQueueSlots >= kQueueSplit + 4, "a counter for every launch of a plan");
 
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 

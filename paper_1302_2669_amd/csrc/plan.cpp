@@ -210,7 +210,7 @@ int enqueue(mcmc_plan* p, const uint8_t* syn, double* prob, double* mean_n, int6
     ra.tiles = p->d_tiles + p->split_first[k];
     ra.n_tiles = p->split_tiles[k];
     ra.n_split = p->split_groups[k];
-    ra.queue = queue + mcmc_plan::kSlots + 2 + k;
+    ra.queue = queue + kQueueSplit + k;
     const int64_t waves = std::min<int64_t>(ra.n_tiles, (int64_t)cus * 4 * SPLIT_WAVES);
     return hip_status(launch_chains_split(ra, wide != 0, (int)waves, on));
   };
@@ -223,7 +223,7 @@ int enqueue(mcmc_plan* p, const uint8_t* syn, double* prob, double* mean_n, int6
       ra.noise = m;
       ra.tiles = p->d_tiles + p->pair_first[m];
       ra.n_tiles = p->pair_tiles[m];
-      ra.queue = queue + mcmc_plan::kSlots + m;
+      ra.queue = queue + kQueuePair + m;
       ra.lmin = 2;
       ra.lmax = PAIR_L_MAX;
       const int per_simd = std::max(1, PAIR_WAVES + tu.occ_narrow);
