@@ -94,11 +94,11 @@ MW_FN uint64_t splitmix64(uint64_t state) {
   return z ^ (z >> 31);
 }
 
-// vertex capacity of a problem at distance L (a multiple of 4, so that the
-// regions below keep 8-byte alignment)
+// vertex capacity of a problem at distance L (a multiple of 4)
 MW_HD int capacity(int L) { return ((L * (L - 1) + 2) + 3) & ~3; }
 
-// bytes of one problem's state (nodes: nn = cap + cap / 2)
+// bytes of one problem's state (nodes: nn = cap + cap / 2), a multiple of 8: the
+// states of a workgroup's waves lie one after the other
 MW_HD size_t region_bytes(int cap) {
   // int64: u, best, key [cap], z [cap/2] (blossom b at z[b - cap])
   // uint32: pos [cap]
@@ -107,7 +107,7 @@ MW_HD size_t region_bytes(int cap) {
   //        tid [nn]
   //        stack [2 nn] ((node, vertex) pairs; recompute's S list [cap] outside
   //        the rotations)
-  return (size_t)cap * 83;
+  return ((size_t)cap * 83 + 7) & ~(size_t)7;
 }
 
 // U: vertices a lane takes at once in the passes over them.  A pass is a short
