@@ -260,14 +260,14 @@ int mcmc_decode_batch_noalloc(const uint8_t* d_syndromes, const uint32_t* d_synd
  * tie); boundary matches are straight strings and NEAR-FAR is the logical
  * string (X on grid row 0, Z on grid column 0).
  *
- * Resources: the syndromes too large for the first launches of the matching
- * starts are solved on a non-blocking stream of the library's, forked from
- * `stream` and joined back to it with two events.  Part of the chains of
+ * Resources: the syndromes too large for the first launch of the matching
+ * starts are solved on one or two non-blocking streams of the library's, forked
+ * from `stream` and joined back to it with two events.  Part of the chains of
  * mcmc_decode_batch and of mcmc_gated_decode (batches of some waves per SIMD,
  * any start mode, outside a capture) runs on one as well.  At most four such
  * streams with their events exist per device.  A call that is not under a
  * stream capture creates one when it finds none free (mcmc_plan_create and
- * mcmc_gated_create with MCMC_INIT_MWPM create the first), and they are kept
+ * mcmc_gated_create with MCMC_INIT_MWPM create two), and they are kept
  * until the process ends.  One is only used while it holds no other stream's
  * work and no other capture, so calls on different streams never wait for each
  * other; a call that finds none free (mcmc_decode_batch_noalloc creates none)

@@ -453,7 +453,7 @@ int mcmc_gated_create(const mcmc_gate_config* h_cfg, mcmc_gated** out) {
     free_gated(g);
     return st != MCMC_OK ? st : MCMC_EDEVICE;
   }
-  if (c.init == MCMC_INIT_MWPM) (void)prepare_side_stream();
+  if (c.init == MCMC_INIT_MWPM) (void)prepare_side_streams(MWPM_SIDES);
   *out = g;
   return MCMC_OK;
 }

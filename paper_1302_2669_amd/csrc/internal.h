@@ -159,17 +159,18 @@ hipError_t launch_init(const StartArgs& a, hipStream_t s);
 hipError_t launch_init_matching(const StartArgs& a, hipStream_t s);
 // Exact minimum-weight matching starts (MCMC_INIT_MWPM): one workgroup per
 // syndrome, dynamic LDS sized for the largest L.  The launches of the larger
-// capacities go to a side stream forked from and joined to s, which a call that
-// is not capturing may create when may_create (callers that must not create
-// runtime objects pass false).  Where there is none free every launch goes to s
-// in order.
+// capacities go to side streams forked from and joined to s, which a call that is
+// not capturing may create when may_create (callers that must not create runtime
+// objects pass false).  Where there is none free every launch goes to s in order.
 hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create = true);
-// Creates a side stream on the current device if it has none (for callers that
-// may only launch inside a capture).
-hipError_t prepare_side_stream();
+constexpr int MWPM_SIDES = 2;   // side streams it uses at most
+// Creates side streams on the current device until it has `count` (for callers
+// that may only launch inside a capture).
+hipError_t prepare_side_streams(int count);
 // A side stream of the current device for a caller on s: fork() makes it follow
 // what s holds, join() makes s follow it (the destructor does if the caller did
-// not).  Never one that other streams' work or another capture still holds;
+// not).  Never one that other streams' work, another capture or another
+// SideStream of the caller's still holds;
 // stream() is null where there is none free, none may be created, or s is being
 // captured and in_capture is false.
 class SideStream {
@@ -185,7 +186,7 @@ class SideStream {
  private:
   hipStream_t s_, side_ = nullptr;
   hipEvent_t fork_ = nullptr, join_ = nullptr;
-  bool forked_ = false;
+  bool forked_ = false, *taken_ = nullptr;
 };
 // The start kernel of an MCMC_INIT_* mode.
 hipError_t launch_init_mode(uint32_t init, const StartArgs& a, hipStream_t s,

@@ -22,8 +22,12 @@
 // in LDS (at large L one wave takes both types in turn, in small batches four
 // waves take one problem each), XOR their parts into
 // bit planes, and the workgroup packs the four class starts.  Up to five
-// launches by problem size (capacity tiers); the largest two, which hold few
-// syndromes but long solves, run on a side stream beside the others.
+// launches by problem size (capacity tiers), on up to two side streams beside the
+// first one's.
+
+#include <limits.h>
+
+#include <optional>
 
 #include "device_common.h"
 #include "host_common.h"
@@ -278,6 +282,15 @@ init_mwpm_kernel(const StartArgs a, int cap_arg, int waves, int lo, int hi) {
 namespace {
 
 constexpr int kMaxTiers = 5;
+// Capacities between the first and the middle tier, two thirds as large as the latter
+// or less, so that a compute unit's LDS holds 10 and 6 workgroups instead of 3 (middle
+// tier of L = 25).  For batches of four rounds of those 3: before that the tails of
+// the launches cost more.  Time against none between, L = 25, p = 0.05 / 0.08 / 0.1:
+// 512 syndromes 1.64 / 1.33 / 0.87, 1024 1.17 / 0.97 / 0.71, 1536 1.08 / 1.08 /
+// 0.84, 3072 0.81 / 0.85 / 0.75, 8192 0.57 / 0.66 / 0.67; L = 18 at 3072 1.01 / 0.98
+// / 0.88 and at 16384 1.05 / 0.94 / 0.91.
+constexpr int MWPM_BETWEEN_CAPS[2] = {88, MWPM_WIDE_CAP};
+constexpr int64_t MWPM_BETWEEN_PER_CU = 12;
 
 // the capacity compiled in only where the launch's is exactly that one
 // (smaller codes have smaller single-tier capacities)
@@ -309,45 +322,55 @@ hipError_t launch_init_mwpm(const StartArgs& a, hipStream_t s, bool may_create) 
   if (a.n == 0) return hipSuccess;
   const int L = a.items ? a.max_L : a.L;
   if (L < MCMC_L_MIN || L > MCMC_L_MAX) return hipErrorInvalidValue;
-  // capacity tiers: the 7-wave launch, the typical syndromes of the larger
-  // codes, a fully lit code.  Batches of many rounds of the middle one (its LDS
-  // holds 3 workgroups per compute unit at L = 25) also take the capacities
-  // between at which 10 and 6 fit: 4096 syndromes at L = 25 need 40 to 190
-  // vertices depending on p, and each further launch only costs its workgroups'
-  // look at the syndrome (18 us) and its own tail, which a small batch feels.
+  // capacity tiers: the 7-wave launch, the typical syndromes of the larger codes, a
+  // fully lit code, and for large batches those between
+  struct Tier {
+    int cap;
+    hipStream_t on;
+  };
+  Tier tiers[kMaxTiers];
   const int full = mw::capacity(L), mid = mwpm_small_capacity(L);
-  int caps[kMaxTiers], nt = 0;
-  if (mid > MWPM_FAST_CAP) caps[nt++] = MWPM_FAST_CAP;
-  if (a.n >= 3072)
-    for (int c : {88, MWPM_WIDE_CAP})
-      if (2 * mid >= 3 * c) caps[nt++] = c;
-  caps[nt++] = mid;
-  if (full > mid) caps[nt++] = full;
-  int lo[kMaxTiers], hi[kMaxTiers];
-  for (int t = 0; t < nt; ++t) {
-    lo[t] = t ? caps[t - 1] : 0;
-    hi[t] = t + 1 < nt ? caps[t] : 0x7fffffff;
-  }
-  if (nt == 1) return launch_tier(a, caps[0], lo[0], hi[0], s);
-  // the middle tier and then the full code's on the side stream, launched first
-  // so that their few long workgroups start at once (the full code's last: its
-  // workgroups' look at every syndrome holds the most LDS; first it made 8000
-  // syndromes at L = 15 take 1.16 ms instead of 0.92); the smaller ones, largest
-  // first, on s; without a side stream, in order on s
+  if (full <= MWPM_FAST_CAP) return launch_tier(a, full, 0, INT_MAX, s);
+  // Each launch ends in a tail of few long solves, so they run beside each other:
+  // the middle tier and after it the full code's on one side stream (the full
+  // code's look at every syndrome holds the most LDS: first it made 8000 syndromes
+  // at L = 15 take 1.16 ms instead of 0.92), the capacities between on another,
+  // the first on s last, after their few long workgroups have started.  (3072
+  // syndromes at L = 18, p = 0.05, between and first in turn on s 737 us, beside
+  // each other 513; without the tiers between 508.)
   hipError_t e = hipSuccess;
   SideStream side(s, may_create, true);   // joined on every return
+  std::optional<SideStream> between;
+  int nt = 0;
+  tiers[nt++] = {MWPM_FAST_CAP, s};
   if (side.stream()) {
     if ((e = side.fork()) != hipSuccess) return e;
-    const int first_aside = full > mid ? nt - 2 : nt - 1;
-    for (int t = first_aside; t < nt; ++t)
-      if ((e = launch_tier(a, caps[t], lo[t], hi[t], side.stream())) != hipSuccess) return e;
-    for (int t = first_aside - 1; t >= 0; --t)
-      if ((e = launch_tier(a, caps[t], lo[t], hi[t], s)) != hipSuccess) return e;
-    return side.join();
+    if (a.n >= MWPM_BETWEEN_PER_CU * device_cus() && 2 * mid >= 3 * MWPM_BETWEEN_CAPS[0]) {
+      between.emplace(s, may_create, true);
+      if (between->stream()) {
+        if ((e = between->fork()) != hipSuccess) return e;
+        for (int c : MWPM_BETWEEN_CAPS)
+          if (2 * mid >= 3 * c) tiers[nt++] = {c, between->stream()};
+      }
+    }
   }
-  for (int t = 0; t < nt; ++t)
-    if ((e = launch_tier(a, caps[t], lo[t], hi[t], s)) != hipSuccess) return e;
-  return hipSuccess;
+  const hipStream_t aside = side.stream() ? side.stream() : s;
+  tiers[nt++] = {mid, aside};
+  if (full > mid) tiers[nt++] = {full, aside};
+  auto launch = [&](int t) {
+    return launch_tier(a, tiers[t].cap, t ? tiers[t - 1].cap : 0,
+                       t + 1 < nt ? tiers[t].cap : INT_MAX, tiers[t].on);
+  };
+  if (!side.stream()) {
+    for (int t = 0; t < nt && e == hipSuccess; ++t) e = launch(t);
+    return e;
+  }
+  const int first_aside = full > mid ? nt - 2 : nt - 1;
+  for (int t = first_aside; t < nt && e == hipSuccess; ++t) e = launch(t);
+  for (int t = first_aside - 1; t >= 0 && e == hipSuccess; --t) e = launch(t);
+  if (e == hipSuccess && between && between->stream()) e = between->join();
+  if (e == hipSuccess) e = side.join();
+  return e;
 }
 
 }  // namespace mcmc

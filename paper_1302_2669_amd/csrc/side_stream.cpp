@@ -18,16 +18,16 @@ namespace {
 
 // A side stream, the events that fork it from and join it to a caller's stream,
 // and that stream.  Created when a caller outside a stream capture finds none free
-// (or by prepare_side_stream), at most kSides per device, and kept until the
+// (or by prepare_side_streams), at most kSides per device, and kept until the
 // process ends; the mutex orders concurrent callers' fork-launch-join sequences.
 struct Side {
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  bool used = false;
-  hipStream_t user = nullptr;   // of the last use outside a capture
+  bool used = false, taken = false;   // taken: by a living SideStream
+  hipStream_t user = nullptr;         // of the last use outside a capture
 };
 constexpr int kDevices = 64, kSides = 4;
-std::mutex g_mu;
+std::recursive_mutex g_mu;   // a caller may hold two at once
 Side g_sides[kDevices][kSides];
 int g_count[kDevices];
 
@@ -81,10 +81,13 @@ bool idle(hipStream_t s) {
 
 }  // namespace
 
-hipError_t prepare_side_stream() {
-  std::lock_guard<std::mutex> lock(g_mu);
+hipError_t prepare_side_streams(int count) {
+  std::lock_guard<std::recursive_mutex> lock(g_mu);
   const int dev = device();
-  return dev >= 0 && (g_count[dev] > 0 || create(dev)) ? hipSuccess : hipErrorOutOfMemory;
+  if (dev < 0) return hipErrorInvalidDevice;
+  while (g_count[dev] < count)
+    if (!create(dev)) return hipErrorOutOfMemory;
+  return hipSuccess;
 }
 
 SideStream::SideStream(hipStream_t s, bool may_create, bool in_capture) : s_(s) {
@@ -98,6 +101,7 @@ SideStream::SideStream(hipStream_t s, bool may_create, bool in_capture) : s_(s) 
   bool own = false;
   for (int k = 0; k < g_count[dev] && !own; ++k) {
     Side& o = g_sides[dev][k];
+    if (o.taken) continue;
     const bool held = capturing(o.side, &other);
     if (cap) {
       // what a free stream still runs is no part of this capture; one that this
@@ -113,6 +117,8 @@ SideStream::SideStream(hipStream_t s, bool may_create, bool in_capture) : s_(s) 
   }
   if (!take && may_create && !cap) take = create(dev);
   if (!take) return;
+  take->taken = true;
+  taken_ = &take->taken;
   if (!cap) {
     take->used = true;
     take->user = s;
@@ -124,6 +130,7 @@ SideStream::SideStream(hipStream_t s, bool may_create, bool in_capture) : s_(s) 
 
 SideStream::~SideStream() {
   if (forked_) (void)join();
+  if (taken_) *taken_ = false;
   g_mu.unlock();
 }
 

@@ -147,10 +147,10 @@ def test_batch_of_both_mappings_in_a_capture():
         torch.cuda.synchronize()
 
 
-def test_two_captures_at_once():
-    # the matching starts fork a side stream into a capture: a second capture, and
-    # eager calls beside both, take another one or none
-    L, n = 13, 700
+@pytest.mark.parametrize("L,n", [(13, 700), (18, 3100)])
+def test_two_captures_at_once(L, n):
+    # the matching starts fork a side stream (two in large batches) into a capture: a
+    # second capture, and eager calls beside both, take others or none
     sets = [mc.sample_errors(L, 0.18, 40 + k, n, device=DEV)[0] for k in range(3)]
     nq = mc.geometry(L)[0]
     want = [mc.init_representatives(s, L, mc.MCMC_INIT_MWPM).clone() for s in sets]
