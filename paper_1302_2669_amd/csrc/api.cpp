@@ -353,25 +353,21 @@ static int decode_batch(const uint8_t* syndromes, const uint32_t* syndrome_ids, 
   } else {
     const int range = range_of(L), cus = device_cus();
     const int64_t total = a.g0.sweep_end - a.g0.sweep_begin;
-    const int both = a.trace ? 0 : both_waves(L, T, total, 4 * cus);
-    bool launched = false;
-    if (both > 0) {
-      SideStream side(s, may_create, false);
-      if (side.stream()) {
-        st = hip_status(launch_both(a, both, side, s));
-        launched = true;
-      }
-    }
     // traces come from the one-lane kernels alone
-    if (launched) {
-      // done
-    } else if (!a.trace && lone_pays(L, T, total, 4 * cus)) {
+    ChainChoice c{CHAINS_ONE_LANE, 0};
+    if (!a.trace) c = chain_choice(L, T, total, 4 * cus, true);
+    if (c.mapping == CHAINS_BOTH) {
+      SideStream side(s, may_create, false);
+      if (side.stream()) st = hip_status(launch_both(a, c.waves, side, s));
+      else c = chain_choice(L, T, total, 4 * cus, false);
+    }
+    if (c.mapping == CHAINS_LONE) {
       st = hip_status(launch_chains_lone(a, s));
-    } else if (!a.trace && split_pays(L, T, total, 4 * cus)) {
+    } else if (c.mapping == CHAINS_SPLIT) {
       a.n_tiles = (T + split_tile(L) - 1) / split_tile(L);
       const int64_t waves = std::min<int64_t>(a.n_tiles, (int64_t)cus * 4 * SPLIT_WAVES);
       st = hip_status(launch_chains_split(a, range_is_wide(range), (int)waves, s));
-    } else {
+    } else if (c.mapping == CHAINS_ONE_LANE) {
       const int64_t waves = std::min<int64_t>(a.n_tiles, default_waves(range, cus));
       st = hip_status(launch_chains(range, a, (int)waves, 256, s));
     }
@@ -502,6 +498,17 @@ int mcmc_sample_errors(int32_t L, double p, uint64_t seed, const uint32_t* sampl
                        uint8_t* errors, void* stream) {
   return mcmc_sample_errors_model(L, MCMC_NOISE_DEPOLARIZING, p, seed, sample_ids, id_base, n,
                                   syndromes, true_class, errors, stream);
+}
+
+// The mapping that the chains of a uniform batch without a trace run under: a
+// ChainMapping, and *waves one-lane waves per SIMD of CHAINS_BOTH.  lone = 0: as the
+// device-built plan of a gated decode decides, with no wave per chain.  For tests.
+int mcmc_chain_mapping(int32_t L, int64_t chains, int64_t sweeps, int32_t simds, int32_t beside,
+                       int32_t lone, int32_t* waves) {
+  ChainChoice c = chain_choice(L, chains, sweeps, simds, beside != 0);
+  if (c.mapping == CHAINS_LONE && !lone) c.mapping = CHAINS_SPLIT;
+  if (waves) *waves = c.waves;
+  return c.mapping;
 }
 
 }  // extern "C"

@@ -83,4 +83,18 @@ inline bool lone_pays(int L, int64_t chains, int64_t sweeps, int simds) {
          split_pays(L, chains, sweeps, simds);
 }
 
+// The mapping of a uniform batch; beside: its split rest may run on another stream.
+enum ChainMapping { CHAINS_ONE_LANE, CHAINS_SPLIT, CHAINS_LONE, CHAINS_BOTH };
+struct ChainChoice {
+  ChainMapping mapping;
+  int waves;   // CHAINS_BOTH: one-lane waves per SIMD
+};
+inline ChainChoice chain_choice(int L, int64_t chains, int64_t sweeps, int simds, bool beside) {
+  const int both = beside ? both_waves(L, chains, sweeps, simds) : 0;
+  if (both > 0) return {CHAINS_BOTH, both};
+  if (lone_pays(L, chains, sweeps, simds)) return {CHAINS_LONE, 0};
+  if (split_pays(L, chains, sweeps, simds)) return {CHAINS_SPLIT, 0};
+  return {CHAINS_ONE_LANE, 0};
+}
+
 }  // namespace mcmc

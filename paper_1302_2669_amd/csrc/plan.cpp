@@ -909,4 +909,12 @@ int mcmc_plan_autotune(mcmc_plan* p, const uint8_t* syndromes, double* class_pro
   return MCMC_OK;
 }
 
+// The groups of a plan that run split over lanes, and all of them.  For tests.
+int mcmc_plan_split_groups(const mcmc_plan* p, int32_t* groups) {
+  int split = 0;
+  for (char g : p->group_split) split += g != 0;
+  if (groups) *groups = (int32_t)p->group_split.size();
+  return split;
+}
+
 }  // extern "C"
