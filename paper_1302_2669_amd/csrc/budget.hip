@@ -1,10 +1,10 @@
 // Device-built plan for a batch of one code size whose syndromes each carry a
 // sweep budget (route 0: no counted sweep, 1: short, 2: full), as set by the
 // gate.  Three groups in descending cost (full, short, none), the full one's
-// chains under the mappings that a uniform batch of as many would take; the
-// items of a group are written in whatever order the atomics give, which changes no
-// result: every chain is keyed by its syndrome id, class, temperature and
-// replica, and every output goes to the syndrome's own slots.
+// chains one per lane, split or both side by side as a uniform batch of as many
+// would run; the items of a group are written in whatever order the atomics give,
+// which changes no result: every chain is keyed by its syndrome id, class,
+// temperature and replica, and every output goes to the syndrome's own slots.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -64,14 +64,14 @@ __global__ void budget_finalize_kernel(const BudgetArgs a) {
     a.counts[4 + g] = first;        // cursor of the group's items
     first += ng;
     if (g == 0) {
-      // the full budget under the mapping of a uniform batch: its first items
-      // one chain per lane, the others split
+      // the full budget under the mapping of a uniform batch, but for one chain per
+      // wave: its first items one chain per lane, the others split
       const int64_t per_item = 4 * (int64_t)a.K * a.C;
       const int64_t tasks = d.n_tasks, sweeps = d.sweep_end;
-      const int h = both_waves(a.L, tasks, sweeps, a.simds);
+      const ChainChoice c = lanes_choice(a.L, tasks, sweeps, a.simds, true);
       int64_t keep = ng;
-      if (h > 0) keep = (int64_t)h * a.simds * TILE / per_item;
-      else if (split_pays(a.L, tasks, sweeps, a.simds)) keep = 0;
+      if (c.mapping == CHAINS_BOTH) keep = (int64_t)c.waves * a.simds * TILE / per_item;
+      else if (c.mapping == CHAINS_SPLIT) keep = 0;
       GroupDesc rest = d;
       rest.first_item = (int32_t)(d.first_item + keep);
       rest.n_items = (int32_t)(ng - keep);

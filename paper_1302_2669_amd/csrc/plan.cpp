@@ -393,8 +393,21 @@ int build_plan(mcmc_plan* p, const mcmc_item* items, int64_t n) {
   return st;
 }
 
-// Which groups run split over lanes.  A plan of one group decides as a uniform
-// batch.  With several the longest ones are split, as many as give the
+// SIMD cycles per update of 64 chains among launches that share the chip: the issue of
+// one chain per lane, a tile of it with another wave on its SIMD, and split.
+// (Fitted to whole executions; the figures of chain_choice.h are of one launch alone,
+// with them 96 ms instead of 75 for 18000 syndromes of L = 17, 21 and 25.)
+double mixed_issue(int L) { return (64.0 + 500.0 / (L * L)) * (L > 16 ? 1.07 : 1.0); }
+double mixed_tile(int L) { return 3.1 * mixed_issue(L); }
+double mixed_split(int L) {
+  return (250.0 * (L / 2) + 4.0 * (110.0 * words_per_row(L) + 26.0)) * TILE /
+         ((double)split_tile(L) * n_stab(L));
+}
+
+// Which groups run split over lanes.  A plan of one group splits it where a uniform
+// batch does better split than one chain per lane (its launches take neither one
+// chain per wave nor both mappings side by side).  With several the longest ones are
+// split, as many as give the
 // shortest estimated execution.  The work spreads over all SIMDs; beside it run
 // the one-lane tiles of the two-word-row ranges and of the first launch on the
 // caller's stream, the longest of which shares its SIMD with other waves.  The
@@ -408,8 +421,9 @@ void choose_split(mcmc_plan* p) {
   const int simds = 4 * device_cus();
   p->group_split.assign(n, 0);
   if (n == 1) {
-    p->group_split[0] =
-        split_pays(p->groups[0].L, p->groups[0].n_tasks, p->groups[0].sweep_end, simds);
+    p->group_split[0] = lanes_choice(p->groups[0].L, p->groups[0].n_tasks,
+                                     p->groups[0].sweep_end, simds, false)
+                            .mapping == CHAINS_SPLIT;
     return;
   }
   auto updates = [&](size_t gi) {
@@ -417,11 +431,16 @@ void choose_split(mcmc_plan* p) {
   };
   double work = 0.0;
   for (size_t gi = 0; gi < n; ++gi)
-    work += (double)p->groups[gi].n_tasks / TILE * updates(gi) * one_lane_issue(p->groups[gi].L);
+    work += (double)p->groups[gi].n_tasks / TILE * updates(gi) * mixed_issue(p->groups[gi].L);
   // the estimate with groups 0 .. k - 1 split
   auto estimate = [&](size_t k) {
     bool split_narrow = false;
-    for (size_t gi = 0; gi < k; ++gi) split_narrow |= p->groups[gi].L <= 16;
+    double tiles = 0.0;
+    for (size_t gi = 0; gi < k; ++gi) {
+      const GroupDesc& g = p->groups[gi];
+      split_narrow |= g.L <= 16;
+      tiles += (double)g.n_tasks / split_tile(g.L);
+    }
     // longest tiles: the two-word-row ranges, then the launches of the caller's
     // stream but for the split one, which comes second
     double wide = 0.0, range1 = 0.0, pair = 0.0, range0 = 0.0;
@@ -431,7 +450,7 @@ void choose_split(mcmc_plan* p) {
                         : L <= PAIR_L_MAX  ? pair
                         : range_of(L) == 1 ? range1
                                            : range0;
-      longest = std::max(longest, updates(gi) * one_lane_cycles(L, 2.0));
+      longest = std::max(longest, updates(gi) * mixed_tile(L));
     }
     double beside = wide, behind = 0.0;
     bool first = true;
@@ -442,7 +461,9 @@ void choose_split(mcmc_plan* p) {
       first = false;
     }
     const double t = std::max(work / simds, beside);
-    return k == 0 ? std::max(t, behind) : t + behind;
+    if (k == 0) return std::max(t, behind);
+    // short runs last as long as the split tiles take to hand out, one in 13 ns
+    return std::max(t + behind, 31.0 * tiles);
   };
   // groups are in descending cost: the longest one-lane tile is the first
   // group's that is not split
@@ -456,7 +477,7 @@ void choose_split(mcmc_plan* p) {
     }
     if (k == n) break;
     const GroupDesc& g = p->groups[k];
-    work += (double)g.n_tasks / TILE * updates(k) * (split_cycles(g.L) - one_lane_issue(g.L));
+    work += (double)g.n_tasks / TILE * updates(k) * (mixed_split(g.L) - mixed_issue(g.L));
   }
   for (size_t gi = 0; gi < best_count; ++gi) p->group_split[gi] = 1;
 }

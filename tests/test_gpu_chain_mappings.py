@@ -87,10 +87,10 @@ def test_one_chain_per_wave(L, noise):
     check(LONE, L, 2, 5, 2, noise)
 
 
-@pytest.mark.parametrize("L,noise,chains", [(2, 0, 83), (3, 1, 80), (4, 0, 105), (5, 1, 80),
-                                            (6, 0, 201), (8, 1, 80), (9, 0, 105), (11, 1, 80),
-                                            (13, 0, 80), (14, 1, 105), (16, 0, 80), (16, 1, 105),
-                                            (17, 0, 71), (20, 1, 80), (23, 0, 80), (25, 1, 57)])
+@pytest.mark.parametrize("L,noise,chains", [(2, 0, 71), (3, 1, 71), (4, 0, 105), (5, 1, 78),
+                                            (6, 0, 201), (8, 1, 78), (9, 0, 105), (11, 1, 78),
+                                            (13, 0, 71), (14, 1, 105), (16, 0, 80), (16, 1, 105),
+                                            (17, 0, 71), (20, 1, 78), (23, 0, 80), (25, 1, 57)])
 def test_one_lane_waves_and_a_split_rest(L, noise, chains):
     check(BOTH, L, 513, chains, 1, noise)
 
@@ -99,7 +99,7 @@ def test_each_mapping_of_a_gated_decode():
     # the full budget's chains one per lane, all split, whole waves with a split rest
     seen = set()
     for L, n, chains, full in ((9, 8192, 2, 1), (9, 8192, 2, 12), (5, 700, 3, 40), (5, 9001, 4, 60),
-                               (13, 9001, 6, 10), (17, 2500, 11, 5)):
+                               (13, 9001, 6, 10), (17, 2500, 11, 30)):
         syn = mc.sample_errors(L, 0.1, 3, n)[0]
         prm = torch.from_numpy(test_gpu_gated.spread_params(L, 17)).to(DEV)
         g = gate.GatedDecoder(L, 0.1, 21, max_batch=n, sweeps_short=1, sweeps_full=full,
@@ -122,7 +122,7 @@ def test_each_mapping_of_a_gated_decode():
                                           ((9, 11, 13, 15), 900, True), ((7, 8), 30000, False)])
 def test_groups_of_a_plan(Ls, per, split):
     syns = [mc.sample_errors(L, 0.1, 5, per)[0] for L in Ls]
-    items = [dict(L=L, p=0.1, sweeps=max(2, L * L // 16), burn=0, chains=3, n_temps=1,
+    items = [dict(L=L, p=0.1, sweeps=L * L // 4, burn=0, chains=3, n_temps=1,
                   syndrome_id=i) for L in Ls for i in range(per)]
     plan = mc.MixedPlan(items, seed=9)
     groups = ctypes.c_int32()
@@ -131,7 +131,7 @@ def test_groups_of_a_plan(Ls, per, split):
     out = plan.execute(torch.cat([s.reshape(-1) for s in syns]), want_sums=True)
     torch.cuda.synchronize()
     for j, L in enumerate(Ls):
-        u = mc.decode_batch(syns[j], L, 0.1, max(2, L * L // 16), 9, chains=3, want_sums=True,
+        u = mc.decode_batch(syns[j], L, 0.1, L * L // 4, 9, chains=3, want_sums=True,
                             init=mc.MCMC_INIT_MATCHING, trace=True)
         lo, hi = j * per, (j + 1) * per
         a, b = plan.chain_offsets[lo], plan.chain_offsets[hi]
