@@ -354,7 +354,7 @@ static int decode_batch(const uint8_t* syndromes, const uint32_t* syndrome_ids, 
     const int range = range_of(L), cus = device_cus();
     const int64_t total = a.g0.sweep_end - a.g0.sweep_begin;
     // traces come from the one-lane kernels alone
-    ChainChoice c{CHAINS_ONE_LANE, 0};
+    ChainChoice c{CHAINS_ONE_LANE, 0, 0.0};
     if (!a.trace) c = chain_choice(L, T, total, 4 * cus, true);
     if (c.mapping == CHAINS_BOTH) {
       SideStream side(s, may_create, false);

@@ -68,7 +68,8 @@ __global__ void budget_finalize_kernel(const BudgetArgs a) {
       // wave: its first items one chain per lane, the others split
       const int64_t per_item = 4 * (int64_t)a.K * a.C;
       const int64_t tasks = d.n_tasks, sweeps = d.sweep_end;
-      const ChainChoice c = lanes_choice(a.L, tasks, sweeps, a.simds, true);
+      ChainChoice c{CHAINS_ONE_LANE, 0, 0.0};
+      if (a.split) c = lanes_choice(a.L, tasks, sweeps, a.simds, true);
       int64_t keep = ng;
       if (c.mapping == CHAINS_BOTH) keep = (int64_t)c.waves * a.simds * TILE / per_item;
       else if (c.mapping == CHAINS_SPLIT) keep = 0;

@@ -68,14 +68,16 @@ __host__ __device__ inline double both_cycles(int L, int h, double rest) {
 enum ChainMapping { CHAINS_ONE_LANE, CHAINS_SPLIT, CHAINS_LONE, CHAINS_BOTH };
 struct ChainChoice {
   ChainMapping mapping;
-  int waves;   // CHAINS_BOTH: one-lane waves per SIMD
+  int waves;     // CHAINS_BOTH: one-lane waves per SIMD
+  double gain;   // cycles less than one chain per lane, by the estimate
 };
 __host__ __device__ inline ChainChoice lanes_choice(int L, int64_t chains, int64_t sweeps,
                                                     int simds, bool beside) {
   const double W = (double)chains / ((double)TILE * simds);
   const double updates = (double)sweeps * 2.0 * L * (L - 1);
-  ChainChoice c{CHAINS_ONE_LANE, 0};
-  double best = 0.947 * one_lane_cycles(L, ceil(W)) * updates;
+  ChainChoice c{CHAINS_ONE_LANE, 0, 0.0};
+  const double lanes = 0.947 * one_lane_cycles(L, ceil(W)) * updates;
+  double best = lanes;
   const double all = split_run(L, (double)chains / split_tile(L), split_cycles(L, W) * updates, false);
   if (all < best) {
     best = all;
@@ -88,10 +90,23 @@ __host__ __device__ inline ChainChoice lanes_choice(int L, int64_t chains, int64
     const double t = split_run(L, rest, both_cycles(L, h, W - h) * updates, true);
     if (t < best) {
       best = t;
-      c = ChainChoice{CHAINS_BOTH, h};
+      c.mapping = CHAINS_BOTH;
+      c.waves = h;
     }
   }
+  c.gain = lanes - best;
   return c;
+}
+
+// Whether a batch of which any part may run `sweeps` sweeps (the rest fewer, in the
+// one-lane launch) gets a launch for split chains, forked from and joined to the
+// caller's stream: if that saves some part of it more than its 20 us (2000
+// syndromes x 16 chains at L = 5 with 5 sweeps: 222 us beside an empty launch, 164
+// alone; one at L = 3 133 and 105).
+inline bool batch_splits(int L, int64_t n, int64_t per_item, int64_t sweeps, int simds) {
+  for (int64_t part = n; part > 0; part /= 2)
+    if (lanes_choice(L, part * per_item, sweeps, simds, true).gain > 48000.0) return true;
+  return false;
 }
 
 // One chain per wave (codes whose draws fill the lanes, LONE_L_MIN) beats L lanes
@@ -112,7 +127,7 @@ inline bool lone_pays(int L, int64_t chains, int64_t sweeps) {
 // The mapping of a uniform batch; beside: its split rest may run on another stream.
 inline ChainChoice chain_choice(int L, int64_t chains, int64_t sweeps, int simds, bool beside) {
   if (lone_fits(L, chains, sweeps, simds))
-    return {lone_pays(L, chains, sweeps) ? CHAINS_LONE : CHAINS_ONE_LANE, 0};
+    return {lone_pays(L, chains, sweeps) ? CHAINS_LONE : CHAINS_ONE_LANE, 0, 0.0};
   return lanes_choice(L, chains, sweeps, simds, beside);
 }
 

@@ -389,6 +389,9 @@ __device__ __forceinline__ void split_persistent(const RunArgs& a) {
   __shared__ __align__(16) uint32_t lds[split_words<LMIN, LMAX>()];
   const int lane = threadIdx.x & 63;
   const int64_t n_tiles = a.tile_cum ? (int64_t)a.tile_cum[3] : a.n_tiles;
+  // a device-built plan may have fewer tiles than waves, or none: the waves beyond
+  // leave the counter alone (4096 of them asking in vain are 53 us)
+  if ((int64_t)blockIdx.x >= n_tiles) return;
   while (true) {
     uint32_t tile = 0;
     if (lane == 0) tile = atomicAdd(a.queue, 1u);

@@ -8,6 +8,7 @@
 #include <new>
 #include <vector>
 
+#include "chain_choice.h"
 #include "device_common.h"
 #include "host_common.h"
 
@@ -612,6 +613,8 @@ int gated_decode_device(mcmc_gated* g, const float* d_params, const uint8_t* d_s
   ba.sweeps[1] = c.sweeps_short;
   ba.sweeps[2] = 0;
   ba.simds = 4 * device_cus();
+  const int64_t per_item = 4 * (int64_t)c.n_temps * c.chains;
+  ba.split = batch_splits(c.L, n, per_item, (int64_t)c.burn + c.sweeps_full, ba.simds);
   ba.counts = g->d_counts;
   ba.groups = g->d_groups;
   ba.items = g->d_items;
@@ -626,7 +629,6 @@ int gated_decode_device(mcmc_gated* g, const float* d_params, const uint8_t* d_s
   if (st != MCMC_OK) return st;
 
   const int r = range_of(c.L);
-  const int64_t per_item = 4 * (int64_t)c.n_temps * c.chains;
   const int64_t max_tiles = (n * per_item + TILE - 1) / TILE + 3;
   RunArgs a{};
   a.groups = g->d_groups;
@@ -653,7 +655,10 @@ int gated_decode_device(mcmc_gated* g, const float* d_params, const uint8_t* d_s
   rest.n_tiles = (n * per_item + split_tile(c.L) - 1) / split_tile(c.L);   // at most
   const int split_waves =
       (int)std::min<int64_t>(rest.n_tiles, (int64_t)device_cus() * 4 * SPLIT_WAVES);
-  {
+  if (!ba.split) {
+    st = hip_status(launch_chains(r, a, (int)waves, 256, s));
+    if (st != MCMC_OK) return st;
+  } else {
     SideStream side(s, true, false);
     const bool beside = side.stream() != nullptr;
     if (beside) st = hip_status(side.fork());
@@ -820,6 +825,12 @@ int mcmc_gated_decode(mcmc_gated* g, const float* d_params, const uint8_t* d_syn
   // the staging buffers are reused by the next call
   if (hipStreamSynchronize(s) != hipSuccess) return MCMC_EDEVICE;
   return MCMC_OK;
+}
+
+// Whether a gated decode of n syndromes, `chains` chains each, has a launch for split
+// chains.  For tests.
+int mcmc_gated_splits(int32_t L, int64_t n, int64_t chains, int64_t sweeps, int32_t simds) {
+  return batch_splits(L, n, chains, sweeps, simds);
 }
 
 }  // extern "C"

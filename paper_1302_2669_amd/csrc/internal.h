@@ -322,6 +322,7 @@ struct BudgetArgs {
   int32_t sweeps[3];
   uint32_t* counts;             // [8] scratch, cleared here
   int32_t simds;
+  int32_t split;                // whether a launch for split chains follows
   GroupDesc* groups;            // [4] out: the last is the part of the first that runs split
   ItemDesc* items;              // [n] out
   uint32_t* tile_cum;           // [4] out: cumulative tiles of groups 0..2, split tiles of group 3

@@ -65,3 +65,12 @@ def test_no_mapping_far_from_the_fastest_is_taken(L, chains, sweeps, us):
 def test_without_a_sweep_the_chains_stay_on_lanes(L):
     for chains in (4, 1000, 100000, 10 ** 7):
         assert choice(L, chains, 0) == (ONE_LANE, 0)
+
+
+@pytest.mark.parametrize("L,n,sweeps,splits", [(3, 1, 9, 0), (3, 2000, 9, 0), (5, 2000, 5, 0),
+                                               (9, 2000, 1, 0), (3, 20000, 9, 0), (13, 1, 169, 1),
+                                               (13, 20000, 169, 1), (5, 2000, 400, 1),
+                                               (25, 100, 25, 1)])
+def test_gated_batches_split_where_it_pays(L, n, sweeps, splits):
+    assert _lib._lib().mcmc_gated_splits(L, ctypes.c_int64(n), ctypes.c_int64(16),
+                                         ctypes.c_int64(sweeps), SIMDS) == splits
