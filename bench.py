@@ -675,13 +675,25 @@ def bench_bitphase(args, mc, torch, dev):
     print(json.dumps(line), flush=True)
 
 
+def spacetime_kernel(L, T, n_chains, sweeps):
+    """The kernel that the library runs this batch's space-time chains in."""
+    import ctypes
+    import torch
+    from paper_1302_2669_amd import _lib
+    simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    if _lib._lib().mcmc_spacetime_mapping(L, T, ctypes.c_int64(n_chains), ctypes.c_int64(sweeps),
+                                          simds):
+        return f"st_chain_lanes_kernel<{L}>"
+    return f"st_chain_fast_kernel<{L}>" if L <= 12 else f"st_chain_win_kernel<{L}>"
+
+
 def bench_spacetime(args, mc, torch, dev):
     """Imperfect measurements (Sec. VI): L = 7, T = 7 rounds (the last one
     perfect), depolarizing p = 0.02 per interval and outcome error p_M = 0.02,
     4 classes x 4 chains, 784 = 16 L^2 sweeps of every spatial and time move
     (the local moves relax slowly in space-time), 32768 histories per step
-    (524288 chains: 8192 one-wave workgroups, 8 waves on each of the 1024
-    SIMDs, the register-resident kernel's full residency).
+    (524288 chains of one lane per interval: 57 waves' worth on each of the
+    1024 SIMDs, 4 resident).
     Also the logical error of decoding the last round alone with the
     single-round decoder (L^2 sweeps), on the same histories."""
     Ls, T, p, pm, chains, sweeps = ST_L, ST_T, ST_P, ST_PM, ST_CHAINS, ST_SWEEPS
@@ -759,8 +771,8 @@ def bench_spacetime(args, mc, torch, dev):
         "logical_error": {"rate": fails / total, "samples": total,
                           "last_round_only": last_fail / total},
         "roofline": {"bound": "alu",
-                     "kernel": (f"st_chain_lanes_kernel<{Ls}>" if Ls <= 12 else
-                                f"st_chain_win_kernel<{Ls}>") + " (space-time chains)",
+                     "kernel": spacetime_kernel(Ls, T, n * 4 * chains, sweeps) +
+                               " (space-time chains)",
                      "achieved": achieved, "peak": PEAK_INT_OPS / 1e12, "unit": "Tops/s",
                      "frac": achieved / (PEAK_INT_OPS / 1e12), "traffic": None,
                      "chain_ms_per_launch": chain_ms, "ops_per_update": OPS_PER_UPDATE,

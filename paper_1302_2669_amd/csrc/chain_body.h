@@ -29,7 +29,7 @@
 //   the row's weight change as one 8 x 4-bit dot product,
 //   and the upper neighbours' c carried over from the row above.
 // Together 20.7 -> 17.6 VALU instructions per update at L = 13; 65536
-// syndromes x 16 chains x 169 sweeps 26.8 -> 23.7 ms.
+// syndromes x 16 chains x 169 sweeps 26.8 -> 23.5 ms.
 //
 // Accumulation: n after every colour phase of a counted sweep is added to S
 // (int64); A counts accepted moves.  No cross-lane reduction is needed.

@@ -43,10 +43,12 @@ __host__ __device__ inline double split_cycles(int L, double W) {
 }
 
 // A run of `cycles` split, with what its tiles cost beyond a one-lane launch's: each
-// comes from one counter, which hands out one in 13 ns, and waits for its rows and
-// its stores.  Short runs last as long as that takes, long ones hide most of it
-// (65536 chains at L = 13: 363 us for 3 sweeps as for 6, 410 for 14; one lane per
-// chain 161, 217, 360).
+// spills at its start (0.7 to 2.2 KB a lane: 0.7 GB for 64016 chains at L = 13), comes
+// from one counter, and waits for its rows and its stores.  Short runs last as long
+// as that takes, some 13 ns a tile, long ones hide most of it (64000 chains at L = 13:
+// 363 us for 3 sweeps as for 6, 411 for 14; one lane per chain 161, 217, 360; with
+// tiles by wave number instead of the counter 288 for 3, but 10% more for long runs of
+// a ragged batch).
 __host__ __device__ inline double split_run(int L, double tiles, double cycles, bool beside) {
   const double start = fmin(25600.0, 6000.0 + 88.0 * tiles);
   return fmax(start + (beside ? 24.0 : 68.0) * tiles + 165.0 * L * L,

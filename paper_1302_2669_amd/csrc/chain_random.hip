@@ -26,7 +26,7 @@
 // A lone wave issues an instruction in about 4.7 cycles whatever it waits for,
 // so the count of them is the time: 90 a step with the batch copied and 77 now.
 // 4096 syndromes x 16 chains x 169 sweeps at L = 13, one wave per SIMD: 25.8 ->
-// 8.6 ms, 1175 -> 391 cycles per step.
+// 8.0 ms, 1175 -> 362 cycles per step.
 //
 // Randomness: step t of a sweep uses block t >> 1 of Philox4x32-10 at counter
 // (t >> 1, sweep, syndrome_id, 2<<30 | cls<<28 | temp<<20 | chain): word
@@ -110,8 +110,8 @@ __device__ __forceinline__ uint4 keyed_round(uint4 c, uint32_t k0, uint32_t k1) 
 
 // How many of the four thresholds u stays below.  A mask (VCC or an SGPR pair) is
 // read from the third instruction after the one that writes it, at the earliest:
-// the other compares and adds fill that gap (8.23 ms on the launch above; with wait
-// states 9.18, as the compiler orders it 8.91).
+// the other compares and adds fill that gap (the decode with the launch above 8.23
+// ms; with wait states 9.18, as the compiler orders it 8.91).
 __device__ __forceinline__ int32_t count_below(uint32_t u, const uint32_t thr[4]) {
   int32_t q;
   uint64_t m0, m1;

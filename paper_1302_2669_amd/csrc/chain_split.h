@@ -10,8 +10,8 @@
 // rows it shares with its neighbours move by one-lane DPP shifts (a star row
 // reads the even row of lane i + 1 and flips it, a plaquette row the odd row
 // of lane i - 1).  A phase is then a few dozen instructions instead of L rows
-// of them: 16 chains at L = 13 take 1.9 us per sweep, 4001 x 16 chains 3.6 ms
-// instead of 5.3 with flips and 169 sweeps.
+// of them: 1952 chains at L = 13 take 1.4 us per sweep (19 one per lane), 64016 3.2
+// ms instead of 5.3 with flips and 169 sweeps.
 //
 // Draws.  The 2 L (L - 1) draws of a sweep are the L (L - 1) / 2 Philox
 // blocks of the one-lane kernel, block b on lane b mod L, so no block is
@@ -24,7 +24,7 @@
 // rows' counts as nibble strings at any alignment, and a whole row is decided
 // by four word operations: no threshold lookup is left on the serial path.
 //
-// Against the one-lane kernel it issues about 1.5 times the instructions per
+// Against the one-lane kernel it issues 1.5 to 1.7 times the instructions per
 // update (idle lanes when L does not divide 64, eight compares per draw), so
 // full batches stay there (chain_choice.h).  Counting the far two thresholds
 // only when some lane's draw of a block reaches that low saves a seventh of the
@@ -390,7 +390,8 @@ __device__ __forceinline__ void split_persistent(const RunArgs& a) {
   const int lane = threadIdx.x & 63;
   const int64_t n_tiles = a.tile_cum ? (int64_t)a.tile_cum[3] : a.n_tiles;
   // a device-built plan may have fewer tiles than waves, or none: the waves beyond
-  // leave the counter alone (4096 of them asking in vain are 53 us)
+  // leave the counter alone (2000 syndromes at L = 5 with 1 sweep, none of them split,
+  // 227 us beside 4096 waves asking in vain, now 136)
   if ((int64_t)blockIdx.x >= n_tiles) return;
   while (true) {
     uint32_t tile = 0;

@@ -462,7 +462,7 @@ void choose_split(mcmc_plan* p) {
     }
     const double t = std::max(work / simds, beside);
     if (k == 0) return std::max(t, behind);
-    // short runs last as long as the split tiles take to hand out, one in 13 ns
+    // short runs last as long as the split tiles take to start, some 13 ns each
     return std::max(t + behind, 31.0 * tiles);
   };
   // groups are in descending cost: the longest one-lane tile is the first
