@@ -52,7 +52,7 @@ def violations(code):
     return bad
 
 
-def test_checker_counts_instructions_and_nops():
+def test_violations_count_instructions_and_nops():
     cmp_, use = "v_cmp_ge_u32 vcc, %1, %2", "v_cndmask_b32 %0, 0, %3, vcc"
     assert violations([cmp_, use]) and violations([cmp_, "s_nop 0", use])
     assert not violations([cmp_, "s_nop 1", use])
